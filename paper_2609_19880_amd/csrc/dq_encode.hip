@@ -38,66 +38,129 @@ constexpr int kEncWaves = 4;
 constexpr int kEncThreads = kEncWaves * kWave;
 constexpr int kD = 128;           // head_dim of the heads in a per-token stream
 
-// Unnormalized FWHT of each group of 64 * SPAN values (a whole stream, or one
-// attention head of a per-token stream); lane l holds elements l + 64 k, group
-// k / SPAN.  Stages run h = 1, 2, ..., 32 SPAN as in the definition.
-template <int VPL, int SPAN = VPL>
+__device__ __forceinline__ uint32_t lo32(double v) { return (uint32_t)__double_as_longlong(v); }
+__device__ __forceinline__ uint32_t hi32(double v) { return (uint32_t)((uint64_t)__double_as_longlong(v) >> 32); }
+__device__ __forceinline__ double join(uint32_t lo, uint32_t hi) {
+    return __longlong_as_double((long long)((uint64_t)lo | ((uint64_t)hi << 32)));
+}
+
+// v of lane l ^ HH (dq_common.h's xor_lane) for doubles.
+template <int HH>
+__device__ __forceinline__ double xor_lane64(double v, int lane) {
+    return join(__float_as_uint(xor_lane<HH>(__uint_as_float(lo32(v)), lane)),
+                __float_as_uint(xor_lane<HH>(__uint_as_float(hi32(v)), lane)));
+}
+
+// Exchanges a's upper half-wavefront with b's lower one (swap_halves), or a's
+// odd rows of 16 lanes with b's even ones (swap_rows).
+__device__ __forceinline__ void swap_halves(double& a, double& b) {
+    const auto l = __builtin_amdgcn_permlane32_swap(lo32(a), lo32(b), false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(hi32(a), hi32(b), false, false);
+    a = join(l[0], h[0]);
+    b = join(l[1], h[1]);
+}
+__device__ __forceinline__ void swap_rows(double& a, double& b) {
+    const auto l = __builtin_amdgcn_permlane16_swap(lo32(a), lo32(b), false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi32(a), hi32(b), false, false);
+    a = join(l[0], h[0]);
+    b = join(l[1], h[1]);
+}
+
+// Stage HH of the transform across lanes: the lower lane of a pair (a, b)
+// takes a + b, the upper a - b, as partner + (own value, negated in the upper
+// lane), which is the same rounding.
+template <int HH>
+__device__ __forceinline__ void lane_stage(double& v, int lane) {
+    const double own = join(lo32(v), hi32(v) ^ ((lane & HH) ? 0x80000000u : 0u));
+    v = xor_lane64<HH>(v, lane) + own;
+}
+
+__device__ __forceinline__ void pair_stage(double& a, double& b) {
+    const double s = a + b, d = a - b;
+    a = s;
+    b = d;
+}
+
+// Channel of a 128-value head that register r of lane l holds before the
+// rotation (head_channel) and after it (l + 64 r).  The transform moves the
+// register index from channel bit 4 to bit 6: stages 1 to 8 are lane stages,
+// stage 16 is inside the lane, and before stages 32 and 64 one swap of rows or
+// halves brings the pair into one lane.  42 VALU instructions and no LDS
+// traffic per head, against 72 and 24 LDS permutes for lane stages throughout.
+__device__ __forceinline__ int head_channel(int lane, int r) { return (lane & 15) | (r << 4) | ((lane >> 4) << 5); }
+
+__device__ __forceinline__ void fwht_head(double& a, double& b, int lane) {
+    lane_stage<1>(a, lane);
+    lane_stage<1>(b, lane);
+    lane_stage<2>(a, lane);
+    lane_stage<2>(b, lane);
+    lane_stage<4>(a, lane);
+    lane_stage<4>(b, lane);
+    lane_stage<8>(a, lane);
+    lane_stage<8>(b, lane);
+    pair_stage(a, b);
+    swap_rows(a, b);
+    pair_stage(a, b);
+    swap_halves(a, b);
+    pair_stage(a, b);
+}
+
+// Unnormalized FWHT of a stream of 64 VPL values (head_dim 64 or 256); lane l
+// holds elements l + 64 k.  Stages run h = 1, 2, ..., 32 VPL as in the
+// definition.
+template <int VPL>
 __device__ __forceinline__ void fwht_wave(double (&v)[VPL], int lane) {
 #pragma unroll
-    for (int h = 1; h < kWave; h <<= 1) {
-#pragma unroll
-        for (int k = 0; k < VPL; ++k) {
-            double pv = __shfl_xor(v[k], h);
-            v[k] = (lane & h) ? (pv - v[k]) : (v[k] + pv);
-        }
+    for (int k = 0; k < VPL; ++k) {
+        lane_stage<1>(v[k], lane);
+        lane_stage<2>(v[k], lane);
+        lane_stage<4>(v[k], lane);
+        lane_stage<8>(v[k], lane);
+        lane_stage<16>(v[k], lane);
+        lane_stage<32>(v[k], lane);
     }
 #pragma unroll
-    for (int s = 1; s < SPAN; s <<= 1) {
+    for (int s = 1; s < VPL; s <<= 1) {
 #pragma unroll
-        for (int k = 0; k < VPL; ++k) {
-            if (!(k & s)) {
-                double a = v[k], b = v[k + s];
-                v[k] = a + b;
-                v[k + s] = a - b;
-            }
-        }
+        for (int k = 0; k < VPL; ++k)
+            if (!(k & s)) pair_stage(v[k], v[k + s]);
     }
 }
 
-// Fold-in-halves sum of the n = 64 VPL values (v[i] += v[i + len/2] until
-// one is left); every lane ends with the total.
+// Fold-in-halves sums of the n = 64 VPL values of P and of Q (v[i] += v[i +
+// len/2] until one is left).  After the first lane step the lower half of the
+// wavefront carries P's sums and the upper half Q's.
 template <int VPL>
-__device__ __forceinline__ double fold_sum(const double (&v)[VPL]) {
-    double w[VPL];
+__device__ __forceinline__ void fold_sums(const double (&P)[VPL], const double (&Q)[VPL], int lane, double& sp,
+                                          double& sq) {
+    double p[VPL], q[VPL];
 #pragma unroll
-    for (int k = 0; k < VPL; ++k) w[k] = v[k];
+    for (int k = 0; k < VPL; ++k) {
+        p[k] = P[k];
+        q[k] = Q[k];
+    }
 #pragma unroll
     for (int len = VPL; len > 1; len >>= 1) {
 #pragma unroll
-        for (int k = 0; k < len / 2; ++k) w[k] = w[k] + w[k + len / 2];
+        for (int k = 0; k < len / 2; ++k) {
+            p[k] = p[k] + p[k + len / 2];
+            q[k] = q[k] + q[k + len / 2];
+        }
     }
-    double s = w[0];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) s = s + __shfl_xor(s, off);
-    return s;
-}
-
-// rotate = 0: the input is already in the rotated basis (prerotated tables).
-template <int VPL>
-__device__ __forceinline__ void load_rotated(const uint16_t* src, double (&v)[VPL], int lane, int rotate) {
-#pragma unroll
-    for (int k = 0; k < VPL; ++k) v[k] = (double)bf16_to_f32(src[lane + kWave * k]);
-    if (rotate) fwht_wave<VPL>(v, lane);
-}
-
-// Per-token stream (head_dim 128): head g's channels c = lane + 64 i are
-// elements k = 2 g + i, each head rotated on its own.
-template <int VPL>
-__device__ __forceinline__ void load_token_rotated(const uint16_t* src, int64_t sh, double (&v)[VPL], int lane,
-                                                   int rotate) {
-#pragma unroll
-    for (int k = 0; k < VPL; ++k) v[k] = (double)bf16_to_f32(src[(int64_t)(k / 2) * sh + lane + kWave * (k % 2)]);
-    if (rotate) fwht_wave<VPL, 2>(v, lane);
+    swap_halves(p[0], q[0]);
+    double s = p[0] + q[0], t = s;
+    swap_rows(s, t);
+    s = s + t;
+    s = s + xor_lane64<8>(s, lane);
+    s = s + xor_lane64<4>(s, lane);
+    s = s + xor_lane64<2>(s, lane);
+    s = s + xor_lane64<1>(s, lane);
+    auto at = [&](int l) {
+        return join((uint32_t)__builtin_amdgcn_readlane((int)lo32(s), l),
+                    (uint32_t)__builtin_amdgcn_readlane((int)hi32(s), l));
+    };
+    sp = at(0);
+    sq = at(32);
 }
 
 struct DriftCtx {
@@ -145,6 +208,23 @@ __device__ __forceinline__ double wave_ext_nn(double v) {
     v = op(v, dpp_copy<0x142, 0xA>(v));
     v = op(v, dpp_copy<0x143, 0xC>(v));
     return lane63(v);
+}
+
+// Wavefront minimum and maximum of non-NaN doubles as one reduction of
+// max(-x) and max(x) (the sign of a zero result is not kept).
+__device__ __forceinline__ void wave_minmax_nn(double& mn, double& mx, int lane) {
+    double a = join(lo32(mn), hi32(mn) ^ 0x80000000u), b = mx;
+    swap_halves(a, b);
+    double v = max_nn(a, b), t = v;
+    swap_rows(v, t);
+    v = max_nn(v, t);
+    v = max_nn(v, dpp_copy<0xB1, 0xF>(v));
+    v = max_nn(v, dpp_copy<0x4E, 0xF>(v));
+    v = max_nn(v, dpp_copy<0x141, 0xF>(v));
+    v = max_nn(v, dpp_copy<0x140, 0xF>(v));
+    mn = join((uint32_t)__builtin_amdgcn_readlane((int)lo32(v), 0),
+              (uint32_t)__builtin_amdgcn_readlane((int)hi32(v), 0) ^ 0x80000000u);
+    mx = lane63(v);
 }
 
 // Assignment at one lambda: each value takes argmin_m D_im + lambda r_m (ties to
@@ -306,59 +386,321 @@ __device__ void drift(const double (&x)[VPL], double s, double o, int64_t budget
     }
 }
 
+// ------------------------------------------------------------ folded drift
+//
+// The same assignment without trying every level at every step.  With the
+// symmetric tables of Sec. 4.2 a value's level depends only on its distance
+// from the middle of the grid, c = o + s (M - 1) / 2: for |x - c| = y, moving
+// from one level to the next one outward changes the Lagrangian cost by
+//     (D + lambda r)(outer) - (D + lambda r)(inner) = -(z - T_j),
+//     z = 2 s y,   T_j = 2 s^2 (j + 1 or j + 1/2) + lambda (r_outer - r_inner),
+// so while the T_j increase in j the level is the number of T_j below z, and
+// the code length of the stream is n r_centre + sum_j (r_outer - r_inner)
+// #{i: z_i > T_j}: one comparison per value and threshold, a population count
+// and a scalar multiply-add per threshold, against five VALU instructions per
+// value and level before.  A convex rate makes the T_j increase for every
+// lambda; at most the outermost level may break it (its frequency is rounded up
+// to an integer), and then the level before it drops out where T_last < T_last-1,
+// both thresholds taking the mean.
+//
+// The thresholds decide in exact arithmetic, the format in fp64 with Alg. 1's
+// operation order.  The two agree wherever no z lies within delta of its
+// threshold, delta bounding both sides' rounding: with K >= |x|, |u_m|, the
+// fp64 costs are off by at most 2^-53 (14 K^2 + 30 lambda) and z - T_j by
+// 2^-50 (K^2 + 16 lambda); delta = 2^-44 (K^2 + 16 lambda) leaves a factor of
+// 16.  fold_drift therefore searches with the thresholds and then certifies
+// what Alg. 1's bisection returns, U:
+//  * at U no z is within delta of a threshold (the counts at T_j - delta and
+//    at T_j + delta are equal), and the code length fits;
+//  * one grid step below U it does not fit, whatever the values within delta
+//    of a threshold do (the count at T_j + delta).
+// The other points that the bisection visits are at least one grid step
+// (0.68 %) away, and there a value's fp64 choice m against its certain choice g
+// at U (or a step below) obeys (lambda - lambda_U) (r_m - r_g) <= 2 E, E the
+// error of a cost near the minimum, at most 2^-53 (6 K S + 22 K sqrt(lambda) +
+// 30 lambda) with S = s + the distance of the values from the grid.  Rates are
+// multiples of 2^-16, so r_m <= r_g (>= below U) once lambda >= 2^-25 K S:
+// every point above U fits and every point below does not, and the bisection
+// ends at U.  When already the nearest levels fit, the bisection goes down to
+// its last grid point: the counts at T_j(0) - delta and T_j(lambda_top) + delta
+// have to be equal for lambda_top = 2^-29 K S, below which every assignment is
+// then the same and above which the bound holds.
+// A stream that does not pass (a value within 2^-44 of a tie, no certain
+// bracket) goes through drift() as it is.
+constexpr int kFoldMax = (DQ_MAX_LEVELS - 1) / 2;
+struct FoldArgs {
+    int32_t J;             // thresholds, (M - 1) / 2
+    int32_t base;          // n R_centre
+    int32_t pool;          // the outermost rate difference is below the one before
+    int32_t even;          // M even: the centre is a boundary between two levels
+    double off;            // distance of the first threshold from the centre in steps: 1 or 1/2
+    int32_t W[kFoldMax];   // R_outer - R_inner (Q16)
+    double w[kFoldMax];    // the same as a rate
+};
+
+// Code length at thresholds T_j + d, and the number of (value, threshold)
+// pairs with z above; COUNT: that number per value in cnt.
+// JM: thresholds held in registers (B), 0: f.J of them formed one at a time.
+template <int VPL, int JM, bool COUNT>
+__device__ __forceinline__ int fold_cost(const double (&z)[VPL], const double (&B)[JM > 0 ? JM : 1], double ss,
+                                         double lam, double d, const FoldArgs& f, int& total, int (&cnt)[VPL]) {
+    int cost = f.base, tot = 0;
+    auto add = [&](double T, int W) {
+        int c = 0;
+#pragma unroll
+        for (int k = 0; k < VPL; ++k) {
+            const bool above = fabs(z[k]) > T;
+            c += (int)__popcll(__ballot(above));
+            if (COUNT) cnt[k] += above ? 1 : 0;
+        }
+        cost += c * W;
+        tot += c;
+    };
+    if constexpr (JM > 0) {
+        double T[JM];
+#pragma unroll
+        for (int j = 0; j < JM; ++j) T[j] = __builtin_fma(lam, f.w[j], B[j]);
+        if (JM > 1 && f.pool) {
+            const double m = 0.5 * (T[JM > 1 ? JM - 2 : 0] + T[JM - 1]);
+            T[JM > 1 ? JM - 2 : 0] = min_nn(T[JM > 1 ? JM - 2 : 0], m);
+            T[JM - 1] = max_nn(T[JM - 1], m);
+        }
+#pragma unroll
+        for (int j = 0; j < JM; ++j) add(T[j] + d, f.W[j]);
+    } else {
+        for (int j = 0; j < f.J; ++j) {
+            double T = __builtin_fma(lam, f.w[j], ss * ((double)j + f.off));
+            if (f.pool && j >= f.J - 2) {
+                const int o = 2 * f.J - 3 - j;              // the other one of the last two
+                const double To = __builtin_fma(lam, f.w[o], ss * ((double)o + f.off)), m = 0.5 * (T + To);
+                T = j < o ? min_nn(T, m) : max_nn(T, m);
+            }
+            add(T + d, f.W[j]);
+        }
+    }
+    total = tot;
+    return cost;
+}
+
+// ceil(log2(8 d)) of a positive normal double held in scalar registers.
+__device__ __forceinline__ int ceil_log2_8(double d) {
+    const uint64_t u = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)lo32(d)) |
+                       ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)hi32(d)) << 32);
+    return (int)((u - 1) >> 52) - 1022 + 3;
+}
+
+__device__ __forceinline__ bool uniform_all(bool c) { return __ballot(c) == ~0ull; }
+
+// Drift by thresholds; false if the result is not certain (m is then not
+// set).  xmin, xmax: extrema of the stream.
+template <int VPL, int JM>
+__device__ __forceinline__ bool fold_drift(const double (&x)[VPL], double xmin, double xmax, double s, double o,
+                                           int64_t budget, const DriftCtx& c, const FoldArgs& f, int (&m)[VPL]) {
+    const int M = c.M;
+    const double top = s * (double)(M - 1), uM = o + top;
+    const double K = max_nn(fabs(xmin), fabs(xmax)) + fabs(o) + top;
+    const double out = max_nn(o - xmin, xmax - uM), S = s + max_nn(out, 0.0);
+    // (also false for a scale of 0 and for infinities and NaN)
+    if (!uniform_all(s > 0.0 && K <= 65536.0 * s)) return false;
+    // max D and min D as Alg. 1 computes them: u_m and x - u_m round
+    // monotonically, so the largest distortion is that of an extreme value at
+    // an extreme level; the smallest lies between 0 and those of the extreme
+    // values at their own ends, and is computed only where that leaves the
+    // bracket open
+    auto sq = [](double e) { return e * e; };
+    const double dmax = max_nn(max_nn(sq(xmax - o), sq(xmin - o)), max_nn(sq(xmax - uM), sq(xmin - uM)));
+    double dlow = min_nn(sq(xmin - o), sq(xmax - uM));
+    if (!uniform_all(dmax - dlow > 1e-280)) return false;
+    int hi = ceil_log2_8(dmax - dlow);
+    if (hi != ceil_log2_8(dmax)) {
+        for (int mm = 0; mm < M; ++mm) {
+            const double t = s * (double)mm;
+            const double u = o + t;
+#pragma unroll
+            for (int k = 0; k < VPL; ++k) dlow = min_nn(dlow, sq(x[k] - u));
+        }
+        dlow = wave_ext_nn<false>(dlow);
+        hi = ceil_log2_8(dmax - dlow);
+    }
+    const int u0 = hi * kLambdaSteps - kBracketUnits;
+    const int budget32 = (int)(budget < INT_MAX ? budget : INT_MAX);
+
+    const double s2 = s + s, ss = s2 * s, ctr = o + s * (0.5 * (double)(M - 1));
+    double z[VPL], B[JM > 0 ? JM : 1];
+#pragma unroll
+    for (int k = 0; k < VPL; ++k) z[k] = (x[k] - ctr) * s2;
+    if constexpr (JM > 0) {
+#pragma unroll
+        for (int j = 0; j < JM; ++j) B[j] = ss * ((double)j + f.off);
+    }
+    const double d0 = K * K * 0x1p-44;
+    auto delta = [&](double lam) { return __builtin_fma(lam, 0x1p-40, d0); };
+    auto lam_at = [&](int k) {                 // lambda of grid point k of the bracket, as Alg. 1 has it
+        const int u = u0 + 5 * k;
+        return ldexp((double)c.lam[u & (kLambdaSteps - 1)], u >> 9);
+    };
+    int cnt[VPL], none[VPL], t0, t1;
+#pragma unroll
+    for (int k = 0; k < VPL; ++k) cnt[k] = 0;
+    double dc = d0;                            // certainty of the sign of x - c
+    if (fold_cost<VPL, JM, true>(z, B, ss, 0.0, -d0, f, t0, cnt) <= budget32) {
+        // the nearest levels fit: the last grid point
+        const double lt = max_nn(0x1p-29 * K * S, 2.0 * lam_at(1));
+        fold_cost<VPL, JM, false>(z, B, ss, lt, delta(lt), f, t1, none);
+        if (t0 != t1 || !uniform_all(16.0 * lt <= ss)) return false;
+    } else {
+        // the bracket's upper 20 octaves: lambda goes with the bisection, the
+        // factors 2^(+-10), 2^(+-5), ... of its steps exact to rounding (the
+        // end points below use the grid's values)
+        int klo = 2048, khi = 4096, k = 3072;
+        double lam = ldexp(1.0, hi - 10);
+        constexpr double kUp[11] = {
+            32.0, 5.656854249492381, 2.378414230005442, 1.5422108254079407,
+            1.241857812073484, 1.1143867425958924, 1.0556451783605572, 1.0274459491187637,
+            1.0136300849514894, 1.0067919769999607, 1.0033902416308227};
+        constexpr double kDn[11] = {
+            0.03125, 0.1767766952966369, 0.42044820762685725, 0.6484197773255048,
+            0.8052451659746271, 0.8973545375015536, 0.9472879907934828, 0.9732872087896166,
+            0.9865531961276172, 0.9932538427449537, 0.9966212132726022};
+#pragma unroll
+        for (int it = 0; it < 11; ++it) {
+            const bool fits = fold_cost<VPL, JM, false>(z, B, ss, lam, 0.0, f, t1, none) <= budget32;
+            if (fits) khi = k;
+            else klo = k;
+            lam *= fits ? kDn[it] : kUp[it];
+            k = (klo + khi) >> 1;
+        }
+        if (khi == 4096) return false;
+        const double lg = lam_at(khi), lb = lam_at(khi - 1), dg = delta(lg);
+#pragma unroll
+        for (int q = 0; q < VPL; ++q) cnt[q] = 0;
+        const int cg = fold_cost<VPL, JM, true>(z, B, ss, lg, -dg, f, t0, cnt);
+        fold_cost<VPL, JM, false>(z, B, ss, lg, dg, f, t1, none);
+        int tb;
+        const int cb = fold_cost<VPL, JM, false>(z, B, ss, lb, delta(lb), f, tb, none);
+        if (t0 != t1 || cg > budget32 || cb <= budget32) return false;
+        if (!uniform_all(lb >= 0x1p-25 * K * S)) return false;
+        if (f.pool) {
+            // the outermost thresholds are not about to trade places, and a
+            // pooled pair stays above the one before it
+            const int j = f.J - 1;
+            const double wa = f.w[j - 1], wb = f.w[j];
+            const double gap_g = ss + lg * (wb - wa), gap_b = ss + lb * (wb - wa);
+            bool ok = fabs(gap_g) > 8.0 * dg && fabs(gap_b) > 8.0 * dg;
+            if (j >= 2) ok = ok && 1.5 * ss + lg * (0.5 * (wa + wb) - f.w[j - 2]) > 8.0 * dg;
+            if (!uniform_all(ok)) return false;
+        }
+        dc = dg;
+    }
+    if (f.even) {
+        uint64_t near = 0;
+#pragma unroll
+        for (int k = 0; k < VPL; ++k) near |= __ballot(fabs(z[k]) <= dc);
+        if (near) return false;
+    }
+    const int below = (M - 1) / 2, above = M / 2;
+#pragma unroll
+    for (int k = 0; k < VPL; ++k) m[k] = z[k] < 0.0 ? below - cnt[k] : above + cnt[k];
+    return true;
+}
+
 __device__ __forceinline__ uint16_t f64_to_half_bits(double v) {
     return __half_as_ushort(__float2half_rn((float)v));
 }
 
+// Input channel of register k of lane l of a head (or of a 64- or 256-value
+// stream): the channels fwht_head starts from, or with rotate = 0 (the input
+// is already in the rotated basis) the ones it ends with.
 template <int VPL>
-__global__ __launch_bounds__(kWave) void key_mean_kernel(const uint16_t* __restrict__ kv,
+__device__ __forceinline__ int in_channel(int lane, int k, int rotate) {
+    return VPL == 2 && rotate ? head_channel(lane, k) : lane + kWave * k;
+}
+
+template <int VPL>
+__device__ __forceinline__ void load_raw(const uint16_t* src, uint16_t (&r)[VPL], int lane, int rotate) {
+#pragma unroll
+    for (int k = 0; k < VPL; ++k) r[k] = src[in_channel<VPL>(lane, k, rotate)];
+}
+
+template <int VPL>
+__device__ __forceinline__ void rotated(const uint16_t (&r)[VPL], double (&v)[VPL], int lane, int rotate) {
+#pragma unroll
+    for (int k = 0; k < VPL; ++k) v[k] = (double)bf16_to_f32(r[k]);
+    if (rotate) {
+        if constexpr (VPL == 2) fwht_head(v[0], v[1], lane);
+        else fwht_wave<VPL>(v, lane);
+    }
+}
+
+// Key means: a workgroup of eight wavefronts per (window, KV head, sequence).
+// Each wavefront requests its 16 tokens up front and rotates them two at a
+// time; every 16 rotated tokens go through LDS (two buffers, one barrier each)
+// to thread j < n, which adds channel j's values in token order.  One wavefront
+// per window, rotating and adding 128 tokens in turn, was bound by that chain.
+constexpr int kMeanWaves = 8;
+constexpr int kMeanBatch = 2 * kMeanWaves;         // tokens per buffer
+constexpr int kMeanRounds = DQ_MEAN_WINDOW / kMeanBatch;
+
+template <int VPL>
+__global__ __launch_bounds__(kMeanWaves* kWave) void key_mean_kernel(const uint16_t* __restrict__ kv,
                                                          int64_t sb, int64_t st, int64_t sh, int H,
                                                          int t0, int t_cap, Pages pg,
                                                          int8_t* __restrict__ mean_q,
                                                          uint16_t* __restrict__ mean_scale,
                                                          uint32_t* status, int rotate) {
     constexpr int n = kWave * VPL;
+    __shared__ double buf[2][kMeanBatch][n];
+    __shared__ double s_max[kMeanWaves];
     const int w = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-    const int lane = threadIdx.x;
-    double acc[VPL];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const uint16_t* base = kv + (int64_t)b * sb + (int64_t)h * sh + (int64_t)w * DQ_MEAN_WINDOW * st;
+    uint16_t raw[kMeanRounds][2][VPL];
 #pragma unroll
-    for (int k = 0; k < VPL; ++k) acc[k] = 0.0;
-    const uint16_t* base = kv + (int64_t)b * sb + (int64_t)h * sh;
-    const int tw = w * DQ_MEAN_WINDOW;
-    for (int t = 0; t < DQ_MEAN_WINDOW; ++t) {
-        double v[VPL];
-        load_rotated<VPL>(base + (int64_t)(tw + t) * st, v, lane, rotate);
+    for (int r = 0; r < kMeanRounds; ++r)
 #pragma unroll
-        for (int k = 0; k < VPL; ++k) acc[k] = acc[k] + v[k];
+        for (int u = 0; u < 2; ++u)
+            load_raw<VPL>(base + (int64_t)(r * kMeanBatch + 2 * wave + u) * st, raw[r][u], lane, rotate);
+    double acc = 0.0;
+#pragma unroll
+    for (int r = 0; r < kMeanRounds; ++r) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            double v[VPL];
+            rotated<VPL>(raw[r][u], v, lane, rotate);
+#pragma unroll
+            for (int k = 0; k < VPL; ++k) buf[r & 1][2 * wave + u][lane + kWave * k] = v[k];
+        }
+        __syncthreads();
+        if (tid < n) {
+#pragma unroll
+            for (int t = 0; t < kMeanBatch; ++t) acc = acc + buf[r & 1][t][tid];
+        }
     }
-    double mu[VPL];
+    const double mu = acc / (double)DQ_MEAN_WINDOW;
+    const bool mine = tid < n;
+    const double wmax = wave_max(mine ? fmax(0.0, fabs(mu)) : 0.0);
+    if (lane == 0) s_max[wave] = wmax;
+    const int nonfinite = __syncthreads_or(mine && !isfinite(mu));
     double amax = 0.0;
-    bool finite = true;
 #pragma unroll
-    for (int k = 0; k < VPL; ++k) {
-        mu[k] = acc[k] / (double)DQ_MEAN_WINDOW;
-        amax = fmax(amax, fabs(mu[k]));
-        finite = finite && isfinite(mu[k]);
-    }
-    amax = wave_max(amax);
+    for (int i = 0; i < VPL; ++i) amax = fmax(amax, s_max[i]);
     const uint16_t sbits = f64_to_half_bits(amax / 127.0);
     const double sc = (double)__half2float(__ushort_as_half(sbits));
     bool bad_page = false;
     const int64_t widx = window_index(pg, H, t_cap, b, h, t0 / DQ_MEAN_WINDOW + w, bad_page);
     if (bad_page) {             // nothing is written through a block-table entry outside the pool
-        if (lane == 0 && status) atomicOr(status, DQ_STATUS_PAGE);
+        if (tid == 0 && status) atomicOr(status, DQ_STATUS_PAGE);
         return;
     }
-    int8_t* dst = mean_q + widx * n;
-#pragma unroll
-    for (int k = 0; k < VPL; ++k) {
+    if (mine) {
         double qv = 0.0;
-        if (sc > 0.0) qv = fmin(127.0, fmax(-127.0, rint(mu[k] / sc)));
-        dst[lane + kWave * k] = (int8_t)qv;
+        if (sc > 0.0) qv = fmin(127.0, fmax(-127.0, rint(mu / sc)));
+        mean_q[widx * n + tid] = (int8_t)qv;
     }
-    if (lane == 0) mean_scale[widx] = sbits;
-    const bool bad = __any(!finite) || !isfinite(sc);
-    if (bad && lane == 0 && status) atomicOr(status, DQ_STATUS_RANGE);
+    if (tid == 0) {
+        mean_scale[widx] = sbits;
+        if ((nonfinite || !isfinite(sc)) && status) atomicOr(status, DQ_STATUS_RANGE);
+    }
 }
 
 struct EncArgs {
@@ -366,6 +708,7 @@ struct EncArgs {
     const uint16_t* kv;
     int64_t sb, st, sh;
     int H, t0, n_new, t_cap;
+    int ns;                      // streams per workgroup, a power of two
     Pages pg;                    // records and key means: contiguous or paged
     int rec_stride;              // per-token records: bytes per record slot (multiple of 16)
     uint8_t* records;
@@ -373,39 +716,43 @@ struct EncArgs {
     const uint16_t* mean_scale;
     uint32_t* status;
     int rotate;                  // 0: the input is already in the rotated basis
+    FoldArgs f;
 };
 
-// x = rotated stream of cache token t minus the dequantized window mean (keys).
-// TOK: the stream spans every KV head (head g in elements 2 g, 2 g + 1).
-template <int VPL, bool TOK>
-__device__ __forceinline__ void stream_values(const EncArgs& a, int b, int h, int t,
-                                              double (&x)[VPL], int lane) {
-    const int64_t ti = t - a.t0;   // position in the input
-    if (TOK) {
-        load_token_rotated<VPL>(a.kv + (int64_t)b * a.sb + ti * a.st, a.sh, x, lane, a.rotate);
-        if (a.mean_q) {
-            bool bad = false;      // (a bad entry reads page 0; the record write then skips it)
-#pragma unroll
-            for (int g = 0; g < VPL / 2; ++g) {
-                const int64_t wi = window_index(a.pg, a.H, a.t_cap, b, g, t / DQ_MEAN_WINDOW, bad);
-                const double sc = (double)__half2float(__ushort_as_half(a.mean_scale[wi]));
-                const int8_t* mq = a.mean_q + wi * kD;
-                x[2 * g] = x[2 * g] - sc * (double)mq[lane];
-                x[2 * g + 1] = x[2 * g + 1] - sc * (double)mq[lane + kWave];
-            }
-        }
-        return;
-    }
-    load_rotated<VPL>(a.kv + (int64_t)b * a.sb + ti * a.st + (int64_t)h * a.sh, x, lane, a.rotate);
-    if (a.mean_q) {
-        constexpr int n = kWave * VPL;
-        bool bad = false;          // (a bad entry reads page 0; the record write then skips it)
-        const int64_t wi = window_index(a.pg, a.H, a.t_cap, b, h, t / DQ_MEAN_WINDOW, bad);
-        const double sc = (double)__half2float(__ushort_as_half(a.mean_scale[wi]));
-        const int8_t* mq = a.mean_q + wi * n;
-#pragma unroll
-        for (int k = 0; k < VPL; ++k) x[k] = x[k] - sc * (double)mq[lane + kWave * k];
-    }
+// LDS of a workgroup: fixed arrays, then per stream the symbols (one padding
+// dword per row: the coder's lanes read the same position of 64 rows, which
+// then fall in different banks) and the record bytes as the coder emits them,
+// from the row's end backwards (an odd number of dwords per row).
+struct EncLayout {
+    int rate, cost, lam, ent, mean, budget, s16, o16, flag, state, emitted, sym, rec, total;
+    int sym_row, rec_row;
+};
+
+__host__ __device__ inline EncLayout enc_layout(int n, int C, int ns, bool tok) {
+    EncLayout L;
+    int off = 0;
+    auto take = [&](int bytes) {
+        const int at = off;
+        off = (off + bytes + 15) & ~15;
+        return at;
+    };
+    L.rate = take(8 * DQ_MAX_LEVELS);
+    L.cost = take(4 * DQ_MAX_LEVELS);
+    L.lam = take(4 * kLambdaSteps);
+    L.ent = take(16 * DQ_MAX_LEVELS);
+    L.mean = take(tok ? 4 * n : 0);
+    L.budget = take(8 * ns);
+    L.s16 = take(2 * ns);
+    L.o16 = take(2 * ns);
+    L.flag = take(4 * ns);
+    L.state = take(4 * ns);
+    L.emitted = take(4 * ns);
+    L.sym_row = n + 4;
+    L.rec_row = 4 * (((C + 3) / 4) | 1);
+    L.sym = take(ns * L.sym_row);
+    L.rec = take(ns * L.rec_row + 8);
+    L.total = off;
+    return L;
 }
 
 // Nearest level on the grid (o, s): argmin_m (x - (o + s m))^2, the same
@@ -433,51 +780,91 @@ __device__ __forceinline__ void nearest(const double (&x)[VPL], double s, double
     }
 }
 
+// Wavefronts per SIMD that the registers are held to.
+__host__ __device__ constexpr int enc_waves(int vpl, int mb, bool tok, int jm) {
+    return tok || mb == 16 ? 3 : jm >= 0 ? (vpl <= 2 ? 6 : 4) : 1;
+}
+
+// JM: thresholds of the folded drift in registers (fold_drift), 0: any number,
+// -1: the rates do not allow it, every step tries every level (drift with MB).
 // FIXED: the fixed-width comparator of App. B -- the same preprocessing and
 // refit with nearest-level rounding in place of both drifts, and b-bit
 // symbols (M = 2^b, b = 8 (C - 4) / n rounded down) packed after the 4-byte
 // header, least significant bit first, instead of the rANS payload.
 // Per-token streams and 16 levels in registers: three workgroups per CU (at
-// most 168 VGPRs; the per-token LDS staging, about 48 KB, fits three).
-template <int VPL, int MB, bool TOK, bool FIXED = false>
-__global__ __launch_bounds__(kEncThreads, (TOK || MB == 16) ? 3 : 1) void encode_kernel(EncArgs a) {
+// most 168 VGPRs; the per-token LDS staging, about 50 KB, fits three).
+template <int VPL, int MB, bool TOK, int JM, bool FIXED = false>
+__global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void encode_kernel(EncArgs a) {
     constexpr int n = kWave * VPL;
-    constexpr int NS = enc_streams(TOK);
+    constexpr int HV = TOK ? 2 : VPL;             // registers per head
+    constexpr int NH = VPL / HV;                  // heads per stream
     extern __shared__ __align__(16) uint8_t smem[];
-    // layout: rate[64] f64 | cost[64] | lam[512] | budget[64] i64 | s16[64] | o16[64]
-    //         | flag[64] | (f, c, rcp, rsh)[64] | sym[64][n] | rec[64][C]
-    double* s_rate = reinterpret_cast<double*>(smem);
-    int32_t* s_cost = reinterpret_cast<int32_t*>(s_rate + DQ_MAX_LEVELS);
-    float* s_lam = reinterpret_cast<float*>(s_cost + DQ_MAX_LEVELS);
-    int64_t* s_budget = reinterpret_cast<int64_t*>(s_lam + kLambdaSteps);
-    uint16_t* s_s16 = reinterpret_cast<uint16_t*>(s_budget + NS);
-    uint16_t* s_o16 = s_s16 + NS;
-    int32_t* s_flag = reinterpret_cast<int32_t*>(s_o16 + NS);
-    uint4* s_ent = reinterpret_cast<uint4*>(s_flag + NS);     // coder entry per symbol
-    uint8_t* s_sym = reinterpret_cast<uint8_t*>(s_ent + DQ_MAX_LEVELS);
-    uint8_t* s_rec = s_sym + NS * n;
-
     const TabArgs& ta = a.ta;
+    const int C = ta.C, ns = a.ns;
+    const EncLayout L = enc_layout(n, C, ns, TOK);
+    double* s_rate = reinterpret_cast<double*>(smem + L.rate);
+    int32_t* s_cost = reinterpret_cast<int32_t*>(smem + L.cost);
+    float* s_lam = reinterpret_cast<float*>(smem + L.lam);
+    uint4* s_ent = reinterpret_cast<uint4*>(smem + L.ent);    // coder entry per symbol
+    float* s_mean = reinterpret_cast<float*>(smem + L.mean);
+    int64_t* s_budget = reinterpret_cast<int64_t*>(smem + L.budget);
+    uint16_t* s_s16 = reinterpret_cast<uint16_t*>(smem + L.s16);
+    uint16_t* s_o16 = reinterpret_cast<uint16_t*>(smem + L.o16);
+    int32_t* s_flag = reinterpret_cast<int32_t*>(smem + L.flag);
+    uint32_t* s_state = reinterpret_cast<uint32_t*>(smem + L.state);
+    int32_t* s_emitted = reinterpret_cast<int32_t*>(smem + L.emitted);
+    uint8_t* s_sym = smem + L.sym;
+    uint8_t* s_rec = smem + L.rec;
+
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const int b = blockIdx.z, h = blockIdx.y;
-    const int first = a.t0 + blockIdx.x * NS;
-    const int active = min(NS, a.t0 + a.n_new - first);
-    const int C = ta.C;
+    const int first = a.t0 + blockIdx.x * ns;
+    const int active = min(ns, a.t0 + a.n_new - first);
+
+    // the wavefront's streams arrive one ahead: stream i + 4 is requested
+    // before stream i is worked on
+    const uint16_t* src = a.kv + (int64_t)b * a.sb + (TOK ? 0 : (int64_t)h * a.sh);
+    uint16_t raw[NH][HV];
+    auto load_stream = [&](int i) {
+        const uint16_t* row = src + (int64_t)(first - a.t0 + i) * a.st;
+#pragma unroll
+        for (int g = 0; g < NH; ++g) load_raw<HV>(row + (int64_t)g * a.sh, raw[g], lane, a.rotate);
+    };
+    if (wave < active) load_stream(wave);
 
     for (int i = tid; i < (FIXED ? 0 : ta.M); i += kEncThreads) {
         s_cost[i] = ta.t.cost[i];
         s_rate[i] = (double)ta.t.cost[i] * (1.0 / 65536.0);
-        // floor(x / f) = mulhi(x, rcp) >> (sh - 1) for x < 2^31, where
-        // sh = ceil(log2 f) and rcp = ceil(2^(31 + sh) / f) (f = 1: x itself)
+        // floor(x / f) = mulhi(2 x, rcp) >> sh for x < 2^30, where
+        // sh = ceil(log2 f) and rcp = ceil(2^(31 + sh) / f)
         const uint32_t f = (uint32_t)ta.t.freq[i];
         const uint32_t sh = f > 1 ? 32u - (uint32_t)__builtin_clz(f - 1u) : 0u;
-        s_ent[i] = uint4{f, (uint32_t)ta.t.cum[i], f > 1 ? (uint32_t)(((1ull << (31 + sh)) + f - 1) / f) : 0u,
-                         f > 1 ? sh - 1u : 0u};
+        s_ent[i] = uint4{((kRansL >> ta.p) << 8) * f, (1u << ta.p) - f,
+                         (uint32_t)(((1ull << (31 + sh)) + f - 1) / f), sh | ((uint32_t)ta.t.cum[i] << 8)};
     }
     for (int i = tid; i < (FIXED ? 0 : kLambdaSteps); i += kEncThreads) s_lam[i] = ta.t.lam[i];
-    for (int i = tid; i < NS; i += kEncThreads) {
+    for (int i = tid; i < ns; i += kEncThreads) {
         s_budget[i] = ta.budget;
         s_flag[i] = 0;
+    }
+    // the dequantized key means of the workgroup's window (with means t0 is a
+    // multiple of the window, so no workgroup straddles two): scale times int8
+    // is exact in fp32
+    // (a bad block-table entry reads page 0; the record write then skips it)
+    float mean[TOK ? 1 : VPL];
+    if (a.mean_q) {
+        bool bad = false;
+        if constexpr (TOK) {
+            for (int j = tid; j < n; j += kEncThreads) {
+                const int64_t wi = window_index(a.pg, a.H, a.t_cap, b, j / kD, first / DQ_MEAN_WINDOW, bad);
+                s_mean[j] = half_bits_to_f32(a.mean_scale[wi]) * (float)a.mean_q[wi * kD + j % kD];
+            }
+        } else {
+            const int64_t wi = window_index(a.pg, a.H, a.t_cap, b, h, first / DQ_MEAN_WINDOW, bad);
+            const float sc = half_bits_to_f32(a.mean_scale[wi]);
+#pragma unroll
+            for (int k = 0; k < VPL; ++k) mean[k] = sc * (float)a.mean_q[wi * n + lane + kWave * k];
+        }
     }
     __syncthreads();
     DriftCtx dc{s_rate, s_cost, s_lam, ta.M, ta.cheapest, ta.rmin};
@@ -486,75 +873,104 @@ __global__ __launch_bounds__(kEncThreads, (TOK || MB == 16) ? 3 : 1) void encode
     for (int pass = 0;; ++pass) {
         // Drift, wavefront per stream.
         for (int i = wave; i < active; i += kEncWaves) {
-            if (pass > 0 && !s_flag[i]) continue;
+            if (pass > 0) {
+                if (!s_flag[i]) continue;
+                load_stream(i);
+            }
             double x[VPL];
-            stream_values<VPL, TOK>(a, b, h, first + i, x, lane);
-            uint16_t sb16, ob16;
-            if (pass == 0) {
-                double mn = x[0], mx = x[0];
-                bool fin = true;
+#pragma unroll
+            for (int g = 0; g < NH; ++g) {
+                double v[HV];
+                rotated<HV>(raw[g], v, lane, a.rotate);
+#pragma unroll
+                for (int k = 0; k < HV; ++k) x[HV * g + k] = v[k];
+            }
+            if (pass == 0 && i + kEncWaves < active) load_stream(i + kEncWaves);
+            if (a.mean_q) {
+#pragma unroll
+                for (int k = 0; k < VPL; ++k) x[k] = x[k] - (double)(TOK ? s_mean[lane + kWave * k] : mean[TOK ? 0 : k]);
+            }
+            double mn = x[0], mx = x[0];
+            bool fin = isfinite(x[0]);
+#pragma unroll
+            for (int k = 1; k < VPL; ++k) {
+                mn = min_nn(mn, x[k]);
+                mx = max_nn(mx, x[k]);
+                fin = fin && isfinite(x[k]);
+            }
+            fin = uniform_all(fin);
+            wave_minmax_nn(mn, mx, lane);
+            if (!uniform_all(fin && mn != 0.0 && mx != 0.0)) {
+                // NaN, and which zero it is, as plain comparisons have it
+                mn = mx = x[0];
 #pragma unroll
                 for (int k = 0; k < VPL; ++k) {
                     mn = fmin(mn, x[k]);
                     mx = fmax(mx, x[k]);
-                    fin = fin && isfinite(x[k]);
                 }
                 mn = wave_min(mn);
                 mx = wave_max(mx);
-                const double s0 = (mx - mn) / (double)(ta.M - 1);
-                const double o0 = mn;
-                int m1[VPL];
-                if (FIXED)
-                    nearest<VPL>(x, s0, o0, ta.M, m1);
-                else
-                    drift<VPL, MB>(x, s0, o0, ta.budget, dc, m1);
+            }
+            // the two drifts of Alg. 1: on the min-max grid, then on the
+            // refitted grid in fp16 (a retry repeats only the second)
+            double s = 0.0, o = 0.0;
+            if (pass > 0) {
+                s = (double)half_bits_to_f32(s_s16[i]);
+                o = (double)half_bits_to_f32(s_o16[i]);
+            } else {
+                s = (mx - mn) / (double)(ta.M - 1);
+                o = mn;
+            }
+            int m[VPL];
+#pragma unroll 1
+            for (int d = pass > 0 ? 1 : 0;; ++d) {
+                if constexpr (FIXED) {
+                    nearest<VPL>(x, s, o, ta.M, m);
+                } else {
+                    int64_t budget = s_budget[i];
+                    asm volatile("" : "+v"(budget));       // (a select of the two addresses would be a flat load)
+                    if (!d) budget = ta.budget;
+                    bool done = false;
+                    if constexpr (JM >= 0) done = fin && fold_drift<VPL, JM>(x, mn, mx, s, o, budget, dc, a.f, m);
+                    if (!done) drift<VPL, MB>(x, s, o, budget, dc, m);
+                }
+                if (d) break;
                 // least-squares refit
                 int sm = 0, smm = 0;
                 double mx_[VPL];
 #pragma unroll
                 for (int k = 0; k < VPL; ++k) {
-                    sm += m1[k];
-                    smm += m1[k] * m1[k];
-                    mx_[k] = (double)m1[k] * x[k];
+                    sm += m[k];
+                    smm += m[k] * m[k];
+                    mx_[k] = (double)m[k] * x[k];
                 }
                 sm = wave_sum_i32(sm);
                 smm = wave_sum_i32(smm);
-                const double Sx = fold_sum<VPL>(x);
-                const double Smx = fold_sum<VPL>(mx_);
+                double Sx, Smx;
+                fold_sums<VPL>(x, mx_, lane, Sx, Smx);
                 const int64_t den_i = (int64_t)n * smm - (int64_t)sm * sm;
-                double s1 = s0, o1 = o0;
                 if (den_i != 0) {
                     const double den = (double)den_i;
                     const double smf = (double)sm;
-                    const double s = ((double)n * Smx - smf * Sx) / den;
-                    const double o = (Sx - s * smf) / (double)n;
-                    if (isfinite(s) && s > 0.0) {
-                        s1 = s;
-                        o1 = o;
+                    const double s1 = ((double)n * Smx - smf * Sx) / den;
+                    const double o1 = (Sx - s1 * smf) / (double)n;
+                    if (isfinite(s1) && s1 > 0.0) {
+                        s = s1;
+                        o = o1;
                     }
                 }
-                sb16 = f64_to_half_bits(s1);
-                ob16 = f64_to_half_bits(o1);
-                const float sf = __half2float(__ushort_as_half(sb16));
-                const float of = __half2float(__ushort_as_half(ob16));
-                if (__any(!fin) || !isfinite(sf) || !isfinite(of)) range_bad = true;
+                const uint16_t sb16 = f64_to_half_bits(s), ob16 = f64_to_half_bits(o);
+                const float sf = half_bits_to_f32(sb16), of = half_bits_to_f32(ob16);
+                if (!fin || !isfinite(sf) || !isfinite(of)) range_bad = true;
                 if (lane == 0) {
                     s_s16[i] = sb16;
                     s_o16[i] = ob16;
                 }
-            } else {
-                sb16 = s_s16[i];
-                ob16 = s_o16[i];
+                s = (double)sf;
+                o = (double)of;
             }
-            const double s16 = (double)__half2float(__ushort_as_half(sb16));
-            const double o16 = (double)__half2float(__ushort_as_half(ob16));
-            int m2[VPL];
-            if (FIXED)
-                nearest<VPL>(x, s16, o16, ta.M, m2);
-            else
-                drift<VPL, MB>(x, s16, o16, s_budget[i], dc, m2);
 #pragma unroll
-            for (int k = 0; k < VPL; ++k) s_sym[i * n + lane + kWave * k] = (uint8_t)m2[k];
+            for (int k = 0; k < VPL; ++k) s_sym[i * L.sym_row + lane + kWave * k] = (uint8_t)m[k];
         }
         __syncthreads();
 
@@ -562,13 +978,14 @@ __global__ __launch_bounds__(kEncThreads, (TOK || MB == 16) ? 3 : 1) void encode
             // b-bit symbols after the header, lane per stream
             if (tid < active) {
                 const int i = tid;
-                uint8_t* rec = s_rec + i * C;
+                uint8_t* rec = s_rec + i * L.rec_row;
+                const uint8_t* sym = s_sym + i * L.sym_row;
                 const int bb = 31 - __builtin_clz(ta.M);
                 for (int k = 0; k < C - 4; ++k) {
                     uint32_t v = 0;
                     for (int t = 0; t < 8; ++t) {
                         const int g = 8 * k + t, j = g / bb;
-                        if (j < n) v |= (uint32_t)((s_sym[i * n + j] >> (g - j * bb)) & 1) << t;
+                        if (j < n) v |= (uint32_t)((sym[j] >> (g - j * bb)) & 1) << t;
                     }
                     rec[4 + k] = (uint8_t)v;
                 }
@@ -581,32 +998,40 @@ __global__ __launch_bounds__(kEncThreads, (TOK || MB == 16) ? 3 : 1) void encode
             __syncthreads();
             break;
         }
-        // Backward rANS, lane per stream (Eq. rans, encoded in reverse).
+        // Backward rANS, lane per stream (Eq. rans, encoded in reverse).  The
+        // symbols of four steps and their entries are read ahead of the chain,
+        // a step's byte is stored whether or not it counts, and the record is
+        // put together when it is written out.
         if (tid < active && (pass == 0 || s_flag[tid])) {
             const int i = tid;
-            uint8_t* rec = s_rec + i * C;
+            uint8_t* end = s_rec + i * L.rec_row + C - 1;
+            const uint32_t* sym4 = reinterpret_cast<const uint32_t*>(s_sym + i * L.sym_row);
             const int cap = C - kPayloadOffset;
-            const uint32_t xmax_unit = (kRansL >> ta.p) << 8;
+            // x < 256 L and x_max = (L >> p) 256 f: one byte brings x below
+            // x_max when p <= 8, two when p <= 12
+            const bool two = ta.p > 8;
             uint32_t xs = kRansL;
             int emitted = 0;
-            const uint32_t P = 1u << ta.p;
-            for (int j = n - 1; j >= 0; --j) {
-                const int m = s_sym[i * n + j];
-                const uint4 ent = s_ent[m];
-                const uint32_t f = ent.x, c = ent.y, rcp = ent.z, rsh = ent.w;
-                const uint32_t xmax = xmax_unit * f;
+            auto emit = [&](uint32_t xmax) {
+                const bool e = xs >= xmax;
+                end[-min(emitted, C - 1)] = (uint8_t)xs;
+                emitted += e ? 1 : 0;
+                xs = e ? xs >> 8 : xs;
+            };
+            for (int j = n / 4 - 1; j >= 0; --j) {
+                const uint32_t w = sym4[j];
+                uint4 ent[4];
 #pragma unroll
-                for (int r = 0; r < 2; ++r) {
-                    if (xs >= xmax) {
-                        if (emitted < cap) rec[C - 1 - emitted] = (uint8_t)(xs & 0xFF);
-                        ++emitted;
-                        xs >>= 8;
-                    }
+                for (int u = 0; u < 4; ++u) ent[u] = s_ent[(w >> (8 * u)) & 0xFFu];
+#pragma unroll
+                for (int u = 3; u >= 0; --u) {
+                    emit(ent[u].x);
+                    if (two) emit(ent[u].x);
+                    // Enc(x, m) = floor(x / f) 2^p + (x mod f) + c = x + q (2^p - f) + c;
+                    // after renormalization x < 2^29 and q < 2^(29 - p)
+                    const uint32_t q = __umulhi(xs << 1, ent[u].z) >> (ent[u].w & 31u);
+                    xs = __umul24(q, ent[u].y) + xs + (ent[u].w >> 8);
                 }
-                // Enc(x, m) = floor(x / f) 2^p + (x mod f) + c = x + q (2^p - f) + c;
-                // after renormalization x < 256 L = 2^29
-                const uint32_t q = f > 1 ? __umulhi(xs, rcp) >> rsh : xs;
-                xs = xs + q * (P - f) + c;
             }
             if (emitted > cap) {
                 // Defensive: with L = 2^21 the coded length is at most
@@ -618,24 +1043,15 @@ __global__ __launch_bounds__(kEncThreads, (TOK || MB == 16) ? 3 : 1) void encode
                 s_budget[i] -= (int64_t)8 * 65536;
                 if (s_budget[i] < (int64_t)n * ta.rmin) {
                     s_flag[i] = 0;
-                    for (int k = 0; k < C; ++k) rec[k] = 0;
+                    s_s16[i] = s_o16[i] = 0;
+                    s_state[i] = 0;
+                    s_emitted[i] = 0;
                     if (a.status) atomicOr(a.status, DQ_STATUS_OVERFLOW);
                 }
             } else {
                 s_flag[i] = 0;
-                // move the payload from the end of the record to offset 8
-                const int src = C - emitted;
-                for (int k = 0; k < emitted; ++k) rec[kPayloadOffset + k] = rec[src + k];
-                for (int k = kPayloadOffset + emitted; k < C; ++k) rec[k] = 0;
-                const uint16_t sb = s_s16[i], ob = s_o16[i];
-                rec[0] = (uint8_t)(sb & 0xFF);
-                rec[1] = (uint8_t)(sb >> 8);
-                rec[2] = (uint8_t)(ob & 0xFF);
-                rec[3] = (uint8_t)(ob >> 8);
-                rec[4] = (uint8_t)(xs & 0xFF);
-                rec[5] = (uint8_t)((xs >> 8) & 0xFF);
-                rec[6] = (uint8_t)((xs >> 16) & 0xFF);
-                rec[7] = (uint8_t)(xs >> 24);
+                s_state[i] = xs;
+                s_emitted[i] = emitted;
             }
         }
         const int again = __syncthreads_or(tid < active ? s_flag[tid] : 0);
@@ -643,40 +1059,41 @@ __global__ __launch_bounds__(kEncThreads, (TOK || MB == 16) ? 3 : 1) void encode
     }
     if (range_bad && lane == 0 && a.status) atomicOr(a.status, DQ_STATUS_RANGE);
 
-    // Write the records of the active streams: one contiguous span, one record
-    // at a time through the block table, or per-token records at their stride
-    // (zero-padded).
+    // Dword w of stream i's record: the header, the state, the payload (the
+    // last `emitted` bytes of the row, moved up to offset 8), zeros.
+    auto rec_dword = [&](int i, int w) -> uint32_t {
+        const uint32_t* row = reinterpret_cast<const uint32_t*>(s_rec + i * L.rec_row);
+        if (FIXED) return row[w];
+        if (w == 0) return (uint32_t)s_s16[i] | ((uint32_t)s_o16[i] << 16);
+        if (w == 1) return s_state[i];
+        const int left = s_emitted[i] - 4 * (w - 2);           // payload bytes from here on
+        if (left <= 0) return 0u;
+        const int at = C - left;
+        const uint32_t v = __builtin_amdgcn_alignbyte(row[at / 4 + 1], row[at / 4], (uint32_t)at & 3u);
+        return left >= 4 ? v : v & ((1u << (8 * left)) - 1u);
+    };
+
+    bool bad_page = false;
     if (TOK) {
-        // 64-token tiles, 8-byte chunk major: byte k of the token in row r at
-        // ((r / 64) S / 8 + k / 8) 512 + (r % 64) 8 + k % 8, the row of token
-        // t through the block table when there is one
-        bool bad_page = false;
-        for (int i = wave; i < active; i += kEncWaves) {
-            const int t = first + i;
-            bool bad = false;
-            const int64_t row = token_row(a.pg, a.t_cap, b, t, bad);
-            if (bad) {
-                bad_page = true;
-                continue;
+        // 64-token tiles, 8-byte chunk major: chunk c of the token in row r at
+        // ((r / 64) S / 8 + c) 512 + (r % 64) 8, the row of token t through
+        // the block table when there is one.  A thread serves one stream and
+        // every (threads / ns)-th chunk, neighbouring threads neighbouring rows.
+        const int i = tid & (ns - 1);
+        if (i < active) {
+            const int64_t row = token_row(a.pg, a.t_cap, b, first + i, bad_page);
+            if (!bad_page) {
+                uint8_t* tile = a.records + (row & ~(int64_t)63) * a.rec_stride + (row & 63) * 8;
+                for (int c = tid / ns; c < a.rec_stride / 8; c += kEncThreads / ns) {
+                    const uint2 v = uint2{rec_dword(i, 2 * c), rec_dword(i, 2 * c + 1)};
+                    *reinterpret_cast<uint2*>(tile + (int64_t)c * 512) = v;
+                }
             }
-            uint8_t* tile = a.records + (row & ~(int64_t)63) * a.rec_stride + (row & 63) * 8;
-            for (int k = lane; k < a.rec_stride; k += kWave)
-                tile[(k >> 3) * 512 + (k & 7)] = k < C ? s_rec[i * C + k] : (uint8_t)0;
-        }
-        if (bad_page && lane == 0 && a.status) atomicOr(a.status, DQ_STATUS_PAGE);
-    } else if (!a.pg.bt) {
-        uint8_t* dst = a.records + ((int64_t)(b * a.H + h) * a.t_cap + first) * C;
-        const int total = active * C;
-        if ((((uintptr_t)dst) & 3) == 0 && (total & 3) == 0) {
-            uint32_t* d32 = reinterpret_cast<uint32_t*>(dst);
-            const uint32_t* s32 = reinterpret_cast<const uint32_t*>(s_rec);
-            for (int k = tid; k < total / 4; k += kEncThreads) d32[k] = s32[k];
-        } else {
-            for (int k = tid; k < total; k += kEncThreads) dst[k] = s_rec[k];
         }
     } else {
-        bool bad_page = false;
-        for (int i = wave; i < active; i += kEncWaves) {
+        // sixteen lanes per record
+        const bool dwords = (C & 3) == 0 && (reinterpret_cast<uintptr_t>(a.records) & 3) == 0;
+        for (int i = tid / 16; i < active; i += kEncThreads / 16) {
             bool bad = false;
             const int64_t row = record_row(a.pg, a.H, a.t_cap, b, h, first + i, bad);
             if (bad) {
@@ -684,9 +1101,98 @@ __global__ __launch_bounds__(kEncThreads, (TOK || MB == 16) ? 3 : 1) void encode
                 continue;
             }
             uint8_t* dst = a.records + row * C;
-            for (int k = lane; k < C; k += kWave) dst[k] = s_rec[i * C + k];
+            if (dwords) {
+                for (int w = tid & 15; w < C / 4; w += 16) reinterpret_cast<uint32_t*>(dst)[w] = rec_dword(i, w);
+            } else {
+                for (int k = tid & 15; k < C; k += 16) dst[k] = (uint8_t)(rec_dword(i, k / 4) >> (8 * (k & 3)));
+            }
         }
-        if (bad_page && lane == 0 && a.status) atomicOr(a.status, DQ_STATUS_PAGE);
+    }
+    if (__any(bad_page) && lane == 0 && a.status) atomicOr(a.status, DQ_STATUS_PAGE);
+}
+
+// Streams per workgroup: as many as the coder has lanes for (64, or 32 for
+// per-token streams, whose symbols and records then take about 50 KB of LDS),
+// fewer while the grid would leave CUs without two workgroups: a small append
+// is bound by the streams that a wavefront takes in turn.
+int streams_per_group(int most, int64_t tokens, int64_t rows) {
+    int ns = most;
+    while (ns > kEncWaves && (tokens + ns - 1) / ns * rows < 2 * (int64_t)cu_count()) ns /= 2;
+    return ns;
+}
+
+// Rates the folded drift can take: symmetric, non-decreasing away from the
+// centre and convex, the outermost level excepted.
+bool fold_args(const dq_tables* tab, int n, FoldArgs& f) {
+    const int M = tab->cfg.levels, J = (M - 1) / 2;
+    const int32_t* R = tab->cost;
+    if (J < 1) return false;
+    for (int m = 0; m < M; ++m)
+        if (R[m] != R[M - 1 - m]) return false;
+    f.J = J;
+    f.base = n * R[M / 2];
+    f.pool = 0;
+    f.even = M % 2 == 0;
+    f.off = f.even ? 1.0 : 0.5;
+    for (int j = 0; j < kFoldMax; ++j) {
+        f.W[j] = j < J ? R[M / 2 + j + 1] - R[M / 2 + j] : 0;
+        f.w[j] = f.W[j] / 65536.0;
+    }
+    for (int j = 0; j < J; ++j) {
+        if (f.W[j] < 0) return false;
+        if (j > 0 && f.W[j] < f.W[j - 1]) {
+            if (j < J - 1) return false;
+            f.pool = 1;
+        }
+    }
+    return true;
+}
+
+template <int VPL, int MB, bool TOK, int JM>
+int launch_encode_as(const EncArgs& a, dim3 grid, hipStream_t stream) {
+    const int smem = enc_layout(kWave * VPL, a.ta.C, a.ns, TOK).total;
+    if (int rc = hip_check("hipFuncSetAttribute",
+                           hipFuncSetAttribute(reinterpret_cast<const void*>(&encode_kernel<VPL, MB, TOK, JM>),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, smem)))
+        return rc;
+    encode_kernel<VPL, MB, TOK, JM><<<grid, kEncThreads, smem, stream>>>(a);
+    return hip_check("encode launch", hipGetLastError());
+}
+
+// Thresholds in registers for up to 8 levels (9 and 10 with two values per
+// lane too), else formed one at a time; the distortions of drift() in registers
+// for up to 8 levels (16 with two values per lane) where every step needs them.
+template <int VPL, bool TOK>
+int launch_encode_vpl(const EncArgs& a, bool fold, dim3 grid, hipStream_t stream) {
+    if (fold) {
+        switch (a.f.J) {
+            case 2: return launch_encode_as<VPL, 0, TOK, 2>(a, grid, stream);
+            case 3: return launch_encode_as<VPL, 0, TOK, 3>(a, grid, stream);
+            case 4:
+                if constexpr (VPL == 2) return launch_encode_as<VPL, 0, TOK, 4>(a, grid, stream);
+        }
+        return launch_encode_as<VPL, 0, TOK, 0>(a, grid, stream);
+    }
+    if constexpr (VPL <= 4)
+        if (a.ta.M <= 8) return launch_encode_as<VPL, 8, TOK, -1>(a, grid, stream);
+    if constexpr (VPL <= 2)
+        if (a.ta.M <= 16) return launch_encode_as<VPL, 16, TOK, -1>(a, grid, stream);
+    return launch_encode_as<VPL, 0, TOK, -1>(a, grid, stream);
+}
+
+template <int VPL>
+int launch_key_mean(const EncArgs& a, int B, int8_t* mean_q, uint16_t* mean_scale, hipStream_t stream) {
+    key_mean_kernel<VPL><<<dim3(a.n_new / DQ_MEAN_WINDOW, a.H, B), kMeanWaves * kWave, 0, stream>>>(
+        a.kv, a.sb, a.st, a.sh, a.H, a.t0, a.t_cap, a.pg, mean_q, mean_scale, a.status, a.rotate);
+    return hip_check("key_mean launch", hipGetLastError());
+}
+
+int launch_key_mean(int vpl, const EncArgs& a, int B, int8_t* mean_q, uint16_t* mean_scale, hipStream_t stream) {
+    switch (vpl) {
+        case 1: return launch_key_mean<1>(a, B, mean_q, mean_scale, stream);
+        case 2: return launch_key_mean<2>(a, B, mean_q, mean_scale, stream);
+        case 4: return launch_key_mean<4>(a, B, mean_q, mean_scale, stream);
+        default: return DQ_ERR_INVALID_ARG;
     }
 }
 
@@ -699,17 +1205,6 @@ int launch_encode(const dq_tables* tab, const Pages& pg, const uint16_t* kv, int
     const bool tok = token_stride > 0;
     const int n = tab->cfg.head_dim;
     const int vpl = n / kWave;
-    const int rotate = tab->cfg.prerotated ? 0 : 1;
-    if (mean_q) {
-        dim3 grid(n_new / DQ_MEAN_WINDOW, H, B);
-        switch (tok ? kD / kWave : vpl) {
-            case 1: key_mean_kernel<1><<<grid, kWave, 0, stream>>>(kv, sb, st, sh, H, t0, t_cap, pg, mean_q, mean_scale, status, rotate); break;
-            case 2: key_mean_kernel<2><<<grid, kWave, 0, stream>>>(kv, sb, st, sh, H, t0, t_cap, pg, mean_q, mean_scale, status, rotate); break;
-            case 4: key_mean_kernel<4><<<grid, kWave, 0, stream>>>(kv, sb, st, sh, H, t0, t_cap, pg, mean_q, mean_scale, status, rotate); break;
-            default: return DQ_ERR_INVALID_ARG;
-        }
-        if (int rc = hip_check("key_mean launch", hipGetLastError())) return rc;
-    }
     EncArgs a;
     a.ta = tab_args(tab);
     a.kv = kv;
@@ -726,48 +1221,22 @@ int launch_encode(const dq_tables* tab, const Pages& pg, const uint16_t* kv, int
     a.mean_q = mean_q;
     a.mean_scale = mean_scale;
     a.status = status;
-    a.rotate = rotate;
-    const int ns = enc_streams(tok);
-    const size_t smem = sizeof(double) * DQ_MAX_LEVELS + sizeof(int32_t) * DQ_MAX_LEVELS +
-                        sizeof(float) * kLambdaSteps + sizeof(int64_t) * ns +
-                        2 * sizeof(uint16_t) * ns + sizeof(int32_t) * ns +
-                        sizeof(uint4) * DQ_MAX_LEVELS +
-                        (size_t)ns * n + (size_t)ns * a.ta.C;
-    dim3 grid((n_new + ns - 1) / ns, tok ? 1 : H, B);
-    // distortions held in registers for up to 8 levels (16 with two values per
-    // lane); longer streams recompute them
-    const int M = tab->cfg.levels;
-    const int mb = vpl > 4 ? 0 : M <= 8 ? 8 : (M <= 16 && vpl <= 2) ? 16 : 0;
-    const void* fn = nullptr;
-#define DQ_ENC(V, MB, T)                                                                         \
-    do {                                                                                         \
-        fn = reinterpret_cast<const void*>(&encode_kernel<V, MB, T>);                            \
-        if (int rc = hip_check("hipFuncSetAttribute",                                            \
-                               hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, \
-                                                   (int)smem)))                                  \
-            return rc;                                                                           \
-        encode_kernel<V, MB, T><<<grid, kEncThreads, smem, stream>>>(a);                         \
-    } while (0)
-    switch ((tok ? 10000 : 0) + vpl * 100 + mb) {
-        case 108: DQ_ENC(1, 8, false); break;
-        case 116: DQ_ENC(1, 16, false); break;
-        case 100: DQ_ENC(1, 0, false); break;
-        case 208: DQ_ENC(2, 8, false); break;
-        case 216: DQ_ENC(2, 16, false); break;
-        case 200: DQ_ENC(2, 0, false); break;
-        case 408: DQ_ENC(4, 8, false); break;
-        case 400: DQ_ENC(4, 0, false); break;
-        case 10208: DQ_ENC(2, 8, true); break;
-        case 10216: DQ_ENC(2, 16, true); break;
-        case 10200: DQ_ENC(2, 0, true); break;
-        case 10408: DQ_ENC(4, 8, true); break;
-        case 10400: DQ_ENC(4, 0, true); break;
-        case 10800: DQ_ENC(8, 0, true); break;
-        case 11600: DQ_ENC(16, 0, true); break;
+    a.rotate = tab->cfg.prerotated ? 0 : 1;
+    if (mean_q)
+        if (int rc = launch_key_mean(tok ? kD / kWave : vpl, a, B, mean_q, mean_scale, stream)) return rc;
+    a.ns = streams_per_group(tok ? kEncStreamsTok : kEncStreams, n_new, (int64_t)(tok ? 1 : H) * B);
+    const bool fold = fold_args(tab, n, a.f);
+    const dim3 grid((n_new + a.ns - 1) / a.ns, tok ? 1 : H, B);
+    switch ((tok ? 100 : 0) + vpl) {
+        case 1: return launch_encode_vpl<1, false>(a, fold, grid, stream);
+        case 2: return launch_encode_vpl<2, false>(a, fold, grid, stream);
+        case 4: return launch_encode_vpl<4, false>(a, fold, grid, stream);
+        case 102: return launch_encode_vpl<2, true>(a, fold, grid, stream);
+        case 104: return launch_encode_vpl<4, true>(a, fold, grid, stream);
+        case 108: return launch_encode_vpl<8, true>(a, fold, grid, stream);
+        case 116: return launch_encode_vpl<16, true>(a, fold, grid, stream);
         default: return DQ_ERR_INVALID_ARG;
     }
-#undef DQ_ENC
-    return hip_check("kernel launch", hipGetLastError());
 }
 
 int launch_encode_fixed(int32_t n, int32_t record_bytes, const Pages& pg, const uint16_t* kv, int64_t sb,
@@ -777,15 +1246,6 @@ int launch_encode_fixed(int32_t n, int32_t record_bytes, const Pages& pg, const 
     const int vpl = n / kWave;
     const int bits = 8 * (record_bytes - 4) / n;
     if (vpl < 1 || vpl > 4 || bits < 1 || bits > 8) return DQ_ERR_INVALID_ARG;
-    if (mean_q) {
-        dim3 grid(n_new / DQ_MEAN_WINDOW, H, B);
-        switch (vpl) {
-            case 1: key_mean_kernel<1><<<grid, kWave, 0, stream>>>(kv, sb, st, sh, H, t0, t_cap, pg, mean_q, mean_scale, status, 1); break;
-            case 2: key_mean_kernel<2><<<grid, kWave, 0, stream>>>(kv, sb, st, sh, H, t0, t_cap, pg, mean_q, mean_scale, status, 1); break;
-            default: key_mean_kernel<4><<<grid, kWave, 0, stream>>>(kv, sb, st, sh, H, t0, t_cap, pg, mean_q, mean_scale, status, 1); break;
-        }
-        if (int rc = hip_check("key_mean launch", hipGetLastError())) return rc;
-    }
     EncArgs a{};
     a.ta.n = n;
     a.ta.M = 1 << bits;
@@ -805,16 +1265,15 @@ int launch_encode_fixed(int32_t n, int32_t record_bytes, const Pages& pg, const 
     a.mean_scale = mean_scale;
     a.status = status;
     a.rotate = 1;
-    const size_t smem = sizeof(double) * DQ_MAX_LEVELS + sizeof(int32_t) * DQ_MAX_LEVELS +
-                        sizeof(float) * kLambdaSteps + sizeof(int64_t) * kEncStreams +
-                        2 * sizeof(uint16_t) * kEncStreams + sizeof(int32_t) * kEncStreams +
-                        sizeof(uint4) * DQ_MAX_LEVELS +
-                        (size_t)kEncStreams * n + (size_t)kEncStreams * record_bytes;
-    dim3 grid((n_new + kEncStreams - 1) / kEncStreams, H, B);
+    if (mean_q)
+        if (int rc = launch_key_mean(vpl, a, B, mean_q, mean_scale, stream)) return rc;
+    a.ns = streams_per_group(kEncStreams, n_new, (int64_t)H * B);
+    const dim3 grid((n_new + a.ns - 1) / a.ns, H, B);
+    const int smem = enc_layout(n, record_bytes, a.ns, false).total;
     switch (vpl) {
-        case 1: encode_kernel<1, 0, false, true><<<grid, kEncThreads, smem, stream>>>(a); break;
-        case 2: encode_kernel<2, 0, false, true><<<grid, kEncThreads, smem, stream>>>(a); break;
-        default: encode_kernel<4, 0, false, true><<<grid, kEncThreads, smem, stream>>>(a); break;
+        case 1: encode_kernel<1, 0, false, -1, true><<<grid, kEncThreads, smem, stream>>>(a); break;
+        case 2: encode_kernel<2, 0, false, -1, true><<<grid, kEncThreads, smem, stream>>>(a); break;
+        default: encode_kernel<4, 0, false, -1, true><<<grid, kEncThreads, smem, stream>>>(a); break;
     }
     return hip_check("encode_fixed launch", hipGetLastError());
 }
