@@ -44,13 +44,6 @@ __device__ __forceinline__ double join(uint32_t lo, uint32_t hi) {
     return __longlong_as_double((long long)((uint64_t)lo | ((uint64_t)hi << 32)));
 }
 
-// v of lane l ^ HH (dq_common.h's xor_lane) for doubles.
-template <int HH>
-__device__ __forceinline__ double xor_lane64(double v, int lane) {
-    return join(__float_as_uint(xor_lane<HH>(__uint_as_float(lo32(v)), lane)),
-                __float_as_uint(xor_lane<HH>(__uint_as_float(hi32(v)), lane)));
-}
-
 // Exchanges a's upper half-wavefront with b's lower one (swap_halves), or a's
 // odd rows of 16 lanes with b's even ones (swap_rows).
 __device__ __forceinline__ void swap_halves(double& a, double& b) {
@@ -66,13 +59,37 @@ __device__ __forceinline__ void swap_rows(double& a, double& b) {
     b = join(l[1], h[1]);
 }
 
-// Stage HH of the transform across lanes: the lower lane of a pair (a, b)
-// takes a + b, the upper a - b, as partner + (own value, negated in the upper
-// lane), which is the same rounding.
-template <int HH>
-__device__ __forceinline__ void lane_stage(double& v, int lane) {
-    const double own = join(lo32(v), hi32(v) ^ ((lane & HH) ? 0x80000000u : 0u));
-    v = xor_lane64<HH>(v, lane) + own;
+// Lanes hold the channels of a head so that every butterfly partner is one
+// DPP operation away: within a row of 16 lanes, channel bit 0, 1, 2, 3 is
+// flipped by lane ^ 1, ^ 2, ^ 7 (row_half_mirror), ^ 8 (row_ror:8), i.e. lane
+// bits 0 to 3 are c0 ^ c2, c1 ^ c2, c2, c3.
+__device__ __forceinline__ int row_channel(int lane) { return (lane & 60) | ((lane ^ ((lane & 4) ? 3 : 0)) & 3); }
+
+template <int BIT>
+__device__ __forceinline__ double row_partner(double v) {
+    constexpr int ctrl = BIT == 0 ? 0xB1 : BIT == 1 ? 0x4E : BIT == 2 ? 0x141 : 0x128;
+    return join((uint32_t)__builtin_amdgcn_mov_dpp((int)lo32(v), ctrl, 0xF, 0xF, false),
+                (uint32_t)__builtin_amdgcn_mov_dpp((int)hi32(v), ctrl, 0xF, 0xF, false));
+}
+
+// +1 or -1 per channel bit 0 to 3 of the lane.
+struct RowSigns {
+    double s[4];
+};
+__device__ __forceinline__ RowSigns row_signs(int lane) {
+    const int c = row_channel(lane);
+    RowSigns r;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) r.s[b] = join(0u, 0x3FF00000u | ((uint32_t)((c >> b) & 1) << 31));
+    return r;
+}
+
+// Stage of channel bit BIT across lanes: the lower lane of a pair (a, b) takes
+// a + b, the upper a - b, as partner + (+-1) own value in one fused
+// multiply-add, whose product is exact: the same rounding.
+template <int BIT>
+__device__ __forceinline__ void row_stage(double& v, const RowSigns& sg) {
+    v = __builtin_fma(v, sg.s[BIT], row_partner<BIT>(v));
 }
 
 __device__ __forceinline__ void pair_stage(double& a, double& b) {
@@ -82,22 +99,25 @@ __device__ __forceinline__ void pair_stage(double& a, double& b) {
 }
 
 // Channel of a 128-value head that register r of lane l holds before the
-// rotation (head_channel) and after it (l + 64 r).  The transform moves the
-// register index from channel bit 4 to bit 6: stages 1 to 8 are lane stages,
-// stage 16 is inside the lane, and before stages 32 and 64 one swap of rows or
-// halves brings the pair into one lane.  42 VALU instructions and no LDS
-// traffic per head, against 72 and 24 LDS permutes for lane stages throughout.
-__device__ __forceinline__ int head_channel(int lane, int r) { return (lane & 15) | (r << 4) | ((lane >> 4) << 5); }
+// rotation (head_channel) and after it (row_channel(l) + 64 r).  The transform
+// moves the register index from channel bit 4 to bit 6: stages 1 to 8 run
+// across lanes, stage 16 is inside the lane, and before stages 32 and 64 one
+// swap of rows or halves brings the pair into one lane.  34 VALU instructions
+// and no LDS traffic per head (72 and 24 LDS permutes with lane stages
+// throughout).
+__device__ __forceinline__ int head_channel(int lane, int r) {
+    return (row_channel(lane) & 15) | (r << 4) | ((lane >> 4) << 5);
+}
 
-__device__ __forceinline__ void fwht_head(double& a, double& b, int lane) {
-    lane_stage<1>(a, lane);
-    lane_stage<1>(b, lane);
-    lane_stage<2>(a, lane);
-    lane_stage<2>(b, lane);
-    lane_stage<4>(a, lane);
-    lane_stage<4>(b, lane);
-    lane_stage<8>(a, lane);
-    lane_stage<8>(b, lane);
+__device__ __forceinline__ void fwht_head(double& a, double& b, const RowSigns& sg) {
+    row_stage<0>(a, sg);
+    row_stage<0>(b, sg);
+    row_stage<1>(a, sg);
+    row_stage<1>(b, sg);
+    row_stage<2>(a, sg);
+    row_stage<2>(b, sg);
+    row_stage<3>(a, sg);
+    row_stage<3>(b, sg);
     pair_stage(a, b);
     swap_rows(a, b);
     pair_stage(a, b);
@@ -106,18 +126,23 @@ __device__ __forceinline__ void fwht_head(double& a, double& b, int lane) {
 }
 
 // Unnormalized FWHT of a stream of 64 VPL values (head_dim 64 or 256); lane l
-// holds elements l + 64 k.  Stages run h = 1, 2, ..., 32 VPL as in the
-// definition.
+// holds elements row_channel(l) + 64 k.  Stages run h = 1, 2, ..., 32 VPL as in
+// the definition.
 template <int VPL>
-__device__ __forceinline__ void fwht_wave(double (&v)[VPL], int lane) {
+__device__ __forceinline__ void fwht_wave(double (&v)[VPL], int lane, const RowSigns& sg) {
 #pragma unroll
     for (int k = 0; k < VPL; ++k) {
-        lane_stage<1>(v[k], lane);
-        lane_stage<2>(v[k], lane);
-        lane_stage<4>(v[k], lane);
-        lane_stage<8>(v[k], lane);
-        lane_stage<16>(v[k], lane);
-        lane_stage<32>(v[k], lane);
+        row_stage<0>(v[k], sg);
+        row_stage<1>(v[k], sg);
+        row_stage<2>(v[k], sg);
+        row_stage<3>(v[k], sg);
+        // (a, b) in every lane: the even and odd rows', then the halves' values
+        double a = v[k], b = v[k];
+        swap_rows(a, b);
+        const double r = a + ((lane & 16) ? -b : b);
+        a = b = r;
+        swap_halves(a, b);
+        v[k] = a + ((lane & 32) ? -b : b);
     }
 #pragma unroll
     for (int s = 1; s < VPL; s <<= 1) {
@@ -128,11 +153,10 @@ __device__ __forceinline__ void fwht_wave(double (&v)[VPL], int lane) {
 }
 
 // Fold-in-halves sums of the n = 64 VPL values of P and of Q (v[i] += v[i +
-// len/2] until one is left).  After the first lane step the lower half of the
+// len/2] until one is left; element i = row_channel(lane) + 64 k).  After the first lane step the lower half of the
 // wavefront carries P's sums and the upper half Q's.
 template <int VPL>
-__device__ __forceinline__ void fold_sums(const double (&P)[VPL], const double (&Q)[VPL], int lane, double& sp,
-                                          double& sq) {
+__device__ __forceinline__ void fold_sums(const double (&P)[VPL], const double (&Q)[VPL], double& sp, double& sq) {
     double p[VPL], q[VPL];
 #pragma unroll
     for (int k = 0; k < VPL; ++k) {
@@ -151,10 +175,10 @@ __device__ __forceinline__ void fold_sums(const double (&P)[VPL], const double (
     double s = p[0] + q[0], t = s;
     swap_rows(s, t);
     s = s + t;
-    s = s + xor_lane64<8>(s, lane);
-    s = s + xor_lane64<4>(s, lane);
-    s = s + xor_lane64<2>(s, lane);
-    s = s + xor_lane64<1>(s, lane);
+    s = s + row_partner<3>(s);
+    s = s + row_partner<2>(s);
+    s = s + row_partner<1>(s);
+    s = s + row_partner<0>(s);
     auto at = [&](int l) {
         return join((uint32_t)__builtin_amdgcn_readlane((int)lo32(s), l),
                     (uint32_t)__builtin_amdgcn_readlane((int)hi32(s), l));
@@ -212,7 +236,7 @@ __device__ __forceinline__ double wave_ext_nn(double v) {
 
 // Wavefront minimum and maximum of non-NaN doubles as one reduction of
 // max(-x) and max(x) (the sign of a zero result is not kept).
-__device__ __forceinline__ void wave_minmax_nn(double& mn, double& mx, int lane) {
+__device__ __forceinline__ void wave_minmax_nn(double& mn, double& mx) {
     double a = join(lo32(mn), hi32(mn) ^ 0x80000000u), b = mx;
     swap_halves(a, b);
     double v = max_nn(a, b), t = v;
@@ -438,14 +462,45 @@ struct FoldArgs {
     double w[kFoldMax];    // the same as a rate
 };
 
-// Code length at thresholds T_j + d, and the number of (value, threshold)
-// pairs with z above; COUNT: that number per value in cnt.
-// JM: thresholds held in registers (B), 0: f.J of them formed one at a time.
-template <int VPL, int JM, bool COUNT>
-__device__ __forceinline__ int fold_cost(const double (&z)[VPL], const double (&B)[JM > 0 ? JM : 1], double ss,
-                                         double lam, double d, const FoldArgs& f, int& total, int (&cnt)[VPL]) {
-    int cost = f.base, tot = 0;
-    auto add = [&](double T, int W) {
+// Thresholds of one lambda: JM in registers from B (JM = 0: formed one at a
+// time, the pooled pair together).
+template <int JM, bool POOL>
+struct Thresholds {
+    double B[JM > 0 ? JM : 1], ss, lam;
+    const FoldArgs& f;
+    __device__ __forceinline__ Thresholds(const FoldArgs& f_, double ss_) : ss(ss_), lam(0.0), f(f_) {
+        if constexpr (JM > 0) {
+#pragma unroll
+            for (int j = 0; j < JM; ++j) B[j] = ss * ((double)j + f.off);
+        }
+    }
+    __device__ __forceinline__ double raw(int j) const {
+        if constexpr (JM > 0) return __builtin_fma(lam, f.w[j], B[j]);
+        return __builtin_fma(lam, f.w[j], ss * ((double)j + f.off));
+    }
+    __device__ __forceinline__ int count() const { return JM > 0 ? JM : f.J; }
+    __device__ __forceinline__ double at(int j) const {
+        const double T = raw(j);
+        const int J = count();
+        if constexpr (POOL) {
+            if (j >= J - 2) {
+                const double To = raw(2 * J - 3 - j), m = 0.5 * (T + To);
+                return j == J - 2 ? min_nn(T, m) : max_nn(T, m);
+            }
+        }
+        return T;
+    }
+};
+
+// Code length at the thresholds shifted by SHIFT d, and the number of (value,
+// threshold) pairs with z above; COUNT: that number per value in cnt.
+template <int SHIFT, bool COUNT, int VPL, int JM, bool POOL>
+__device__ __forceinline__ int fold_cost(const double (&z)[VPL], const Thresholds<JM, POOL>& th, double d, int& total,
+                                         int (&cnt)[VPL]) {
+    int cost = th.f.base, tot = 0;
+    auto add = [&](int j) {
+        double T = th.at(j);
+        if constexpr (SHIFT != 0) T = SHIFT > 0 ? T + d : T - d;
         int c = 0;
 #pragma unroll
         for (int k = 0; k < VPL; ++k) {
@@ -453,30 +508,14 @@ __device__ __forceinline__ int fold_cost(const double (&z)[VPL], const double (&
             c += (int)__popcll(__ballot(above));
             if (COUNT) cnt[k] += above ? 1 : 0;
         }
-        cost += c * W;
+        cost += c * th.f.W[j];
         tot += c;
     };
     if constexpr (JM > 0) {
-        double T[JM];
 #pragma unroll
-        for (int j = 0; j < JM; ++j) T[j] = __builtin_fma(lam, f.w[j], B[j]);
-        if (JM > 1 && f.pool) {
-            const double m = 0.5 * (T[JM > 1 ? JM - 2 : 0] + T[JM - 1]);
-            T[JM > 1 ? JM - 2 : 0] = min_nn(T[JM > 1 ? JM - 2 : 0], m);
-            T[JM - 1] = max_nn(T[JM - 1], m);
-        }
-#pragma unroll
-        for (int j = 0; j < JM; ++j) add(T[j] + d, f.W[j]);
+        for (int j = 0; j < JM; ++j) add(j);
     } else {
-        for (int j = 0; j < f.J; ++j) {
-            double T = __builtin_fma(lam, f.w[j], ss * ((double)j + f.off));
-            if (f.pool && j >= f.J - 2) {
-                const int o = 2 * f.J - 3 - j;              // the other one of the last two
-                const double To = __builtin_fma(lam, f.w[o], ss * ((double)o + f.off)), m = 0.5 * (T + To);
-                T = j < o ? min_nn(T, m) : max_nn(T, m);
-            }
-            add(T + d, f.W[j]);
-        }
+        for (int j = 0; j < th.f.J; ++j) add(j);
     }
     total = tot;
     return cost;
@@ -493,7 +532,7 @@ __device__ __forceinline__ bool uniform_all(bool c) { return __ballot(c) == ~0ul
 
 // Drift by thresholds; false if the result is not certain (m is then not
 // set).  xmin, xmax: extrema of the stream.
-template <int VPL, int JM>
+template <int VPL, int JM, bool POOL>
 __device__ __forceinline__ bool fold_drift(const double (&x)[VPL], double xmin, double xmax, double s, double o,
                                            int64_t budget, const DriftCtx& c, const FoldArgs& f, int (&m)[VPL]) {
     const int M = c.M;
@@ -526,13 +565,10 @@ __device__ __forceinline__ bool fold_drift(const double (&x)[VPL], double xmin, 
     const int budget32 = (int)(budget < INT_MAX ? budget : INT_MAX);
 
     const double s2 = s + s, ss = s2 * s, ctr = o + s * (0.5 * (double)(M - 1));
-    double z[VPL], B[JM > 0 ? JM : 1];
+    double z[VPL];
 #pragma unroll
     for (int k = 0; k < VPL; ++k) z[k] = (x[k] - ctr) * s2;
-    if constexpr (JM > 0) {
-#pragma unroll
-        for (int j = 0; j < JM; ++j) B[j] = ss * ((double)j + f.off);
-    }
+    Thresholds<JM, POOL> th(f, ss);
     const double d0 = K * K * 0x1p-44;
     auto delta = [&](double lam) { return __builtin_fma(lam, 0x1p-40, d0); };
     auto lam_at = [&](int k) {                 // lambda of grid point k of the bracket, as Alg. 1 has it
@@ -543,17 +579,19 @@ __device__ __forceinline__ bool fold_drift(const double (&x)[VPL], double xmin, 
 #pragma unroll
     for (int k = 0; k < VPL; ++k) cnt[k] = 0;
     double dc = d0;                            // certainty of the sign of x - c
-    if (fold_cost<VPL, JM, true>(z, B, ss, 0.0, -d0, f, t0, cnt) <= budget32) {
+    if (fold_cost<-1, false>(z, th, d0, t0, none) <= budget32) {
         // the nearest levels fit: the last grid point
+        fold_cost<-1, true>(z, th, d0, t0, cnt);
         const double lt = max_nn(0x1p-29 * K * S, 2.0 * lam_at(1));
-        fold_cost<VPL, JM, false>(z, B, ss, lt, delta(lt), f, t1, none);
+        th.lam = lt;
+        fold_cost<1, false>(z, th, delta(lt), t1, none);
         if (t0 != t1 || !uniform_all(16.0 * lt <= ss)) return false;
     } else {
         // the bracket's upper 20 octaves: lambda goes with the bisection, the
-        // factors 2^(+-10), 2^(+-5), ... of its steps exact to rounding (the
+        // factors 2^(+-5), 2^(+-2.5), ... of its steps exact to rounding (the
         // end points below use the grid's values)
         int klo = 2048, khi = 4096, k = 3072;
-        double lam = ldexp(1.0, hi - 10);
+        th.lam = ldexp(1.0, hi - 10);
         constexpr double kUp[11] = {
             32.0, 5.656854249492381, 2.378414230005442, 1.5422108254079407,
             1.241857812073484, 1.1143867425958924, 1.0556451783605572, 1.0274459491187637,
@@ -564,23 +602,21 @@ __device__ __forceinline__ bool fold_drift(const double (&x)[VPL], double xmin, 
             0.9865531961276172, 0.9932538427449537, 0.9966212132726022};
 #pragma unroll
         for (int it = 0; it < 11; ++it) {
-            const bool fits = fold_cost<VPL, JM, false>(z, B, ss, lam, 0.0, f, t1, none) <= budget32;
+            const bool fits = fold_cost<0, false>(z, th, 0.0, t1, none) <= budget32;
             if (fits) khi = k;
             else klo = k;
-            lam *= fits ? kDn[it] : kUp[it];
+            th.lam *= fits ? kDn[it] : kUp[it];
             k = (klo + khi) >> 1;
         }
         if (khi == 4096) return false;
         const double lg = lam_at(khi), lb = lam_at(khi - 1), dg = delta(lg);
-#pragma unroll
-        for (int q = 0; q < VPL; ++q) cnt[q] = 0;
-        const int cg = fold_cost<VPL, JM, true>(z, B, ss, lg, -dg, f, t0, cnt);
-        fold_cost<VPL, JM, false>(z, B, ss, lg, dg, f, t1, none);
-        int tb;
-        const int cb = fold_cost<VPL, JM, false>(z, B, ss, lb, delta(lb), f, tb, none);
-        if (t0 != t1 || cg > budget32 || cb <= budget32) return false;
+        th.lam = lb;
+        if (fold_cost<1, false>(z, th, delta(lb), t1, none) <= budget32) return false;
+        th.lam = lg;
+        fold_cost<1, false>(z, th, dg, t1, none);
+        if (fold_cost<-1, true>(z, th, dg, t0, cnt) > budget32 || t0 != t1) return false;
         if (!uniform_all(lb >= 0x1p-25 * K * S)) return false;
-        if (f.pool) {
+        if constexpr (POOL) {
             // the outermost thresholds are not about to trade places, and a
             // pooled pair stays above the one before it
             const int j = f.J - 1;
@@ -613,22 +649,25 @@ __device__ __forceinline__ uint16_t f64_to_half_bits(double v) {
 // is already in the rotated basis) the ones it ends with.
 template <int VPL>
 __device__ __forceinline__ int in_channel(int lane, int k, int rotate) {
-    return VPL == 2 && rotate ? head_channel(lane, k) : lane + kWave * k;
+    return VPL == 2 && rotate ? head_channel(lane, k) : row_channel(lane) + kWave * k;
 }
+
+// (the address space stated: the compiler loses it in some instantiations)
+#define GLOBAL_PTR(T, p) reinterpret_cast<__attribute__((address_space(1))) T*>(reinterpret_cast<uintptr_t>(p))
 
 template <int VPL>
 __device__ __forceinline__ void load_raw(const uint16_t* src, uint16_t (&r)[VPL], int lane, int rotate) {
 #pragma unroll
-    for (int k = 0; k < VPL; ++k) r[k] = src[in_channel<VPL>(lane, k, rotate)];
+    for (int k = 0; k < VPL; ++k) r[k] = GLOBAL_PTR(const uint16_t, src)[in_channel<VPL>(lane, k, rotate)];
 }
 
 template <int VPL>
-__device__ __forceinline__ void rotated(const uint16_t (&r)[VPL], double (&v)[VPL], int lane, int rotate) {
+__device__ __forceinline__ void rotated(const uint16_t (&r)[VPL], double (&v)[VPL], int lane, const RowSigns& sg, int rotate) {
 #pragma unroll
     for (int k = 0; k < VPL; ++k) v[k] = (double)bf16_to_f32(r[k]);
     if (rotate) {
-        if constexpr (VPL == 2) fwht_head(v[0], v[1], lane);
-        else fwht_wave<VPL>(v, lane);
+        if constexpr (VPL == 2) fwht_head(v[0], v[1], sg);
+        else fwht_wave<VPL>(v, lane, sg);
     }
 }
 
@@ -660,15 +699,17 @@ __global__ __launch_bounds__(kMeanWaves* kWave) void key_mean_kernel(const uint1
 #pragma unroll
         for (int u = 0; u < 2; ++u)
             load_raw<VPL>(base + (int64_t)(r * kMeanBatch + 2 * wave + u) * st, raw[r][u], lane, rotate);
+    const RowSigns sg = row_signs(lane);
+    const int ch = row_channel(lane);
     double acc = 0.0;
 #pragma unroll
     for (int r = 0; r < kMeanRounds; ++r) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             double v[VPL];
-            rotated<VPL>(raw[r][u], v, lane, rotate);
+            rotated<VPL>(raw[r][u], v, lane, sg, rotate);
 #pragma unroll
-            for (int k = 0; k < VPL; ++k) buf[r & 1][2 * wave + u][lane + kWave * k] = v[k];
+            for (int k = 0; k < VPL; ++k) buf[r & 1][2 * wave + u][ch + kWave * k] = v[k];
         }
         __syncthreads();
         if (tid < n) {
@@ -787,13 +828,14 @@ __host__ __device__ constexpr int enc_waves(int vpl, int mb, bool tok, int jm) {
 
 // JM: thresholds of the folded drift in registers (fold_drift), 0: any number,
 // -1: the rates do not allow it, every step tries every level (drift with MB).
+// POOL: the outermost two may have to share their mean.
 // FIXED: the fixed-width comparator of App. B -- the same preprocessing and
 // refit with nearest-level rounding in place of both drifts, and b-bit
 // symbols (M = 2^b, b = 8 (C - 4) / n rounded down) packed after the 4-byte
 // header, least significant bit first, instead of the rANS payload.
 // Per-token streams and 16 levels in registers: three workgroups per CU (at
 // most 168 VGPRs; the per-token LDS staging, about 50 KB, fits three).
-template <int VPL, int MB, bool TOK, int JM, bool FIXED = false>
+template <int VPL, int MB, bool TOK, int JM, bool POOL, bool FIXED = false>
 __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void encode_kernel(EncArgs a) {
     constexpr int n = kWave * VPL;
     constexpr int HV = TOK ? 2 : VPL;             // registers per head
@@ -817,6 +859,8 @@ __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void enco
     uint8_t* s_rec = smem + L.rec;
 
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const RowSigns sg = row_signs(lane);
+    const int ch = row_channel(lane);             // element of the stream: ch + 64 k in register k
     const int b = blockIdx.z, h = blockIdx.y;
     const int first = a.t0 + blockIdx.x * ns;
     const int active = min(ns, a.t0 + a.n_new - first);
@@ -835,12 +879,15 @@ __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void enco
     for (int i = tid; i < (FIXED ? 0 : ta.M); i += kEncThreads) {
         s_cost[i] = ta.t.cost[i];
         s_rate[i] = (double)ta.t.cost[i] * (1.0 / 65536.0);
-        // floor(x / f) = mulhi(2 x, rcp) >> sh for x < 2^30, where
-        // sh = ceil(log2 f) and rcp = ceil(2^(31 + sh) / f)
-        const uint32_t f = (uint32_t)ta.t.freq[i];
-        const uint32_t sh = f > 1 ? 32u - (uint32_t)__builtin_clz(f - 1u) : 0u;
-        s_ent[i] = uint4{((kRansL >> ta.p) << 8) * f, (1u << ta.p) - f,
-                         (uint32_t)(((1ull << (31 + sh)) + f - 1) / f), sh | ((uint32_t)ta.t.cum[i] << 8)};
+        // floor(x / f) = mulhi(x, rcp) >> (sh - 1) for x < 2^31, where
+        // sh = ceil(log2 f) and rcp = ceil(2^(31 + sh) / f); for f = 1 the
+        // product with 2^32 - 1 gives x - 1 (x > 0), and the addend makes up
+        // for the missing multiple
+        const uint32_t f = (uint32_t)ta.t.freq[i], P = 1u << ta.p;
+        const uint32_t sh = f > 1 ? 32u - (uint32_t)__builtin_clz(f - 1u) : 1u;
+        s_ent[i] = uint4{((kRansL >> ta.p) << 8) * f, P - f,
+                         f > 1 ? (uint32_t)(((1ull << (31 + sh)) + f - 1) / f) : 0xFFFFFFFFu,
+                         (sh - 1) | (((uint32_t)ta.t.cum[i] + (f > 1 ? 0u : P - 1u)) << 8)};
     }
     for (int i = tid; i < (FIXED ? 0 : kLambdaSteps); i += kEncThreads) s_lam[i] = ta.t.lam[i];
     for (int i = tid; i < ns; i += kEncThreads) {
@@ -863,7 +910,7 @@ __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void enco
             const int64_t wi = window_index(a.pg, a.H, a.t_cap, b, h, first / DQ_MEAN_WINDOW, bad);
             const float sc = half_bits_to_f32(a.mean_scale[wi]);
 #pragma unroll
-            for (int k = 0; k < VPL; ++k) mean[k] = sc * (float)a.mean_q[wi * n + lane + kWave * k];
+            for (int k = 0; k < VPL; ++k) mean[k] = sc * (float)a.mean_q[wi * n + ch + kWave * k];
         }
     }
     __syncthreads();
@@ -881,14 +928,14 @@ __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void enco
 #pragma unroll
             for (int g = 0; g < NH; ++g) {
                 double v[HV];
-                rotated<HV>(raw[g], v, lane, a.rotate);
+                rotated<HV>(raw[g], v, lane, sg, a.rotate);
 #pragma unroll
                 for (int k = 0; k < HV; ++k) x[HV * g + k] = v[k];
             }
             if (pass == 0 && i + kEncWaves < active) load_stream(i + kEncWaves);
             if (a.mean_q) {
 #pragma unroll
-                for (int k = 0; k < VPL; ++k) x[k] = x[k] - (double)(TOK ? s_mean[lane + kWave * k] : mean[TOK ? 0 : k]);
+                for (int k = 0; k < VPL; ++k) x[k] = x[k] - (double)(TOK ? s_mean[ch + kWave * k] : mean[TOK ? 0 : k]);
             }
             double mn = x[0], mx = x[0];
             bool fin = isfinite(x[0]);
@@ -899,7 +946,7 @@ __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void enco
                 fin = fin && isfinite(x[k]);
             }
             fin = uniform_all(fin);
-            wave_minmax_nn(mn, mx, lane);
+            wave_minmax_nn(mn, mx);
             if (!uniform_all(fin && mn != 0.0 && mx != 0.0)) {
                 // NaN, and which zero it is, as plain comparisons have it
                 mn = mx = x[0];
@@ -931,7 +978,7 @@ __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void enco
                     asm volatile("" : "+v"(budget));       // (a select of the two addresses would be a flat load)
                     if (!d) budget = ta.budget;
                     bool done = false;
-                    if constexpr (JM >= 0) done = fin && fold_drift<VPL, JM>(x, mn, mx, s, o, budget, dc, a.f, m);
+                    if constexpr (JM >= 0) done = fin && fold_drift<VPL, JM, POOL>(x, mn, mx, s, o, budget, dc, a.f, m);
                     if (!done) drift<VPL, MB>(x, s, o, budget, dc, m);
                 }
                 if (d) break;
@@ -947,11 +994,10 @@ __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void enco
                 sm = wave_sum_i32(sm);
                 smm = wave_sum_i32(smm);
                 double Sx, Smx;
-                fold_sums<VPL>(x, mx_, lane, Sx, Smx);
-                const int64_t den_i = (int64_t)n * smm - (int64_t)sm * sm;
-                if (den_i != 0) {
-                    const double den = (double)den_i;
-                    const double smf = (double)sm;
+                fold_sums<VPL>(x, mx_, Sx, Smx);
+                // (integers below 2^53: exact)
+                const double smf = (double)sm, den = (double)n * (double)smm - smf * smf;
+                if (uniform_all(den != 0.0)) {
                     const double s1 = ((double)n * Smx - smf * Sx) / den;
                     const double o1 = (Sx - s1 * smf) / (double)n;
                     if (isfinite(s1) && s1 > 0.0) {
@@ -970,7 +1016,7 @@ __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void enco
                 o = (double)of;
             }
 #pragma unroll
-            for (int k = 0; k < VPL; ++k) s_sym[i * L.sym_row + lane + kWave * k] = (uint8_t)m[k];
+            for (int k = 0; k < VPL; ++k) s_sym[i * L.sym_row + ch + kWave * k] = (uint8_t)m[k];
         }
         __syncthreads();
 
@@ -1001,21 +1047,25 @@ __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void enco
         // Backward rANS, lane per stream (Eq. rans, encoded in reverse).  The
         // symbols of four steps and their entries are read ahead of the chain,
         // a step's byte is stored whether or not it counts, and the record is
-        // put together when it is written out.
+        // put together when it is written out.  The wavefront runs at a raised
+        // issue priority: the workgroup waits for its serial chain.
         if (tid < active && (pass == 0 || s_flag[tid])) {
             const int i = tid;
-            uint8_t* end = s_rec + i * L.rec_row + C - 1;
+            uint8_t* const row = s_rec + i * L.rec_row;
+            uint8_t* at = row + C - 1;                // next byte, downwards
+            uint8_t* const low = row + kPayloadOffset - 1;
             const uint32_t* sym4 = reinterpret_cast<const uint32_t*>(s_sym + i * L.sym_row);
             const int cap = C - kPayloadOffset;
             // x < 256 L and x_max = (L >> p) 256 f: one byte brings x below
             // x_max when p <= 8, two when p <= 12
             const bool two = ta.p > 8;
             uint32_t xs = kRansL;
-            int emitted = 0;
+            bool over = false;
+            __builtin_amdgcn_s_setprio(3);
             auto emit = [&](uint32_t xmax) {
                 const bool e = xs >= xmax;
-                end[-min(emitted, C - 1)] = (uint8_t)xs;
-                emitted += e ? 1 : 0;
+                *at = (uint8_t)xs;
+                at -= e ? 1 : 0;
                 xs = e ? xs >> 8 : xs;
             };
             for (int j = n / 4 - 1; j >= 0; --j) {
@@ -1029,10 +1079,16 @@ __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void enco
                     if (two) emit(ent[u].x);
                     // Enc(x, m) = floor(x / f) 2^p + (x mod f) + c = x + q (2^p - f) + c;
                     // after renormalization x < 2^29 and q < 2^(29 - p)
-                    const uint32_t q = __umulhi(xs << 1, ent[u].z) >> (ent[u].w & 31u);
-                    xs = __umul24(q, ent[u].y) + xs + (ent[u].w >> 8);
+                    const uint32_t q = __umulhi(xs, ent[u].z) >> (ent[u].w & 31u);
+                    xs = __umul24(q, ent[u].y) + (xs + (ent[u].w >> 8));
                 }
+                // four steps store at most eight bytes: a stream past its
+                // record stays in its row
+                over = over || at < low;
+                at = at < low ? low : at;
             }
+            __builtin_amdgcn_s_setprio(0);
+            const int emitted = over ? cap + 1 : (int)(row + C - 1 - at);
             if (emitted > cap) {
                 // Defensive: with L = 2^21 the coded length is at most
                 // sum r + n (2^-17 + log2(1 + 2^p / L)) bits, under 8 bits
@@ -1148,30 +1204,36 @@ bool fold_args(const dq_tables* tab, int n, FoldArgs& f) {
     return true;
 }
 
-template <int VPL, int MB, bool TOK, int JM>
+template <int VPL, int MB, bool TOK, int JM, bool POOL = false>
 int launch_encode_as(const EncArgs& a, dim3 grid, hipStream_t stream) {
     const int smem = enc_layout(kWave * VPL, a.ta.C, a.ns, TOK).total;
     if (int rc = hip_check("hipFuncSetAttribute",
-                           hipFuncSetAttribute(reinterpret_cast<const void*>(&encode_kernel<VPL, MB, TOK, JM>),
+                           hipFuncSetAttribute(reinterpret_cast<const void*>(&encode_kernel<VPL, MB, TOK, JM, POOL>),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, smem)))
         return rc;
-    encode_kernel<VPL, MB, TOK, JM><<<grid, kEncThreads, smem, stream>>>(a);
+    encode_kernel<VPL, MB, TOK, JM, POOL><<<grid, kEncThreads, smem, stream>>>(a);
     return hip_check("encode launch", hipGetLastError());
 }
 
-// Thresholds in registers for up to 8 levels (9 and 10 with two values per
-// lane too), else formed one at a time; the distortions of drift() in registers
-// for up to 8 levels (16 with two values per lane) where every step needs them.
+// Thresholds in registers where the level counts of the default operating
+// points meet them (128 values: 5 to 10 levels; 512 and 1024 values: 5 to 8),
+// else formed one at a time; the distortions of drift() in registers for up to
+// 8 levels (16 with two values per lane) where every step needs them.
 template <int VPL, bool TOK>
 int launch_encode_vpl(const EncArgs& a, bool fold, dim3 grid, hipStream_t stream) {
     if (fold) {
-        switch (a.f.J) {
-            case 2: return launch_encode_as<VPL, 0, TOK, 2>(a, grid, stream);
-            case 3: return launch_encode_as<VPL, 0, TOK, 3>(a, grid, stream);
-            case 4:
-                if constexpr (VPL == 2) return launch_encode_as<VPL, 0, TOK, 4>(a, grid, stream);
+        if constexpr ((VPL == 2 && !TOK) || VPL >= 8) {
+            if (a.f.J == 2 && !a.f.pool) return launch_encode_as<VPL, 0, TOK, 2>(a, grid, stream);
+            if (a.f.J == 3) {
+                if constexpr (TOK)
+                    if (a.f.pool) return launch_encode_as<VPL, 0, TOK, 3, true>(a, grid, stream);
+                if (!a.f.pool) return launch_encode_as<VPL, 0, TOK, 3>(a, grid, stream);
+            }
+            if constexpr (!TOK)
+                if (a.f.J == 4 && !a.f.pool) return launch_encode_as<VPL, 0, TOK, 4>(a, grid, stream);
         }
-        return launch_encode_as<VPL, 0, TOK, 0>(a, grid, stream);
+        return a.f.pool ? launch_encode_as<VPL, 0, TOK, 0, true>(a, grid, stream)
+                        : launch_encode_as<VPL, 0, TOK, 0>(a, grid, stream);
     }
     if constexpr (VPL <= 4)
         if (a.ta.M <= 8) return launch_encode_as<VPL, 8, TOK, -1>(a, grid, stream);
@@ -1271,9 +1333,9 @@ int launch_encode_fixed(int32_t n, int32_t record_bytes, const Pages& pg, const 
     const dim3 grid((n_new + a.ns - 1) / a.ns, H, B);
     const int smem = enc_layout(n, record_bytes, a.ns, false).total;
     switch (vpl) {
-        case 1: encode_kernel<1, 0, false, -1, true><<<grid, kEncThreads, smem, stream>>>(a); break;
-        case 2: encode_kernel<2, 0, false, -1, true><<<grid, kEncThreads, smem, stream>>>(a); break;
-        default: encode_kernel<4, 0, false, -1, true><<<grid, kEncThreads, smem, stream>>>(a); break;
+        case 1: encode_kernel<1, 0, false, -1, false, true><<<grid, kEncThreads, smem, stream>>>(a); break;
+        case 2: encode_kernel<2, 0, false, -1, false, true><<<grid, kEncThreads, smem, stream>>>(a); break;
+        default: encode_kernel<4, 0, false, -1, false, true><<<grid, kEncThreads, smem, stream>>>(a); break;
     }
     return hip_check("encode_fixed launch", hipGetLastError());
 }
