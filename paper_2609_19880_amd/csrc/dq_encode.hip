@@ -187,6 +187,9 @@ __device__ __forceinline__ void fold_sums(const double (&P)[VPL], const double (
     sq = at(32);
 }
 
+__device__ __forceinline__ uint64_t ballot(bool c) { return __builtin_amdgcn_ballot_w64(c); }
+__device__ __forceinline__ bool uniform_all(bool c) { return ballot(c) == ~0ull; }
+
 struct DriftCtx {
     const double* rate;    // LDS [M]: R_m / 2^16
     const int32_t* cost;   // LDS [M]
@@ -492,12 +495,12 @@ struct Thresholds {
     }
 };
 
-// Code length at the thresholds shifted by SHIFT d, and the number of (value,
-// threshold) pairs with z above; COUNT: that number per value in cnt.
+// Code length beyond f.base at the thresholds shifted by SHIFT d, and the number
+// of (value, threshold) pairs with z above; COUNT: that number per value in cnt.
 template <int SHIFT, bool COUNT, int VPL, int JM, bool POOL>
 __device__ __forceinline__ int fold_cost(const double (&z)[VPL], const Thresholds<JM, POOL>& th, double d, int& total,
                                          int (&cnt)[VPL]) {
-    int cost = th.f.base, tot = 0;
+    int cost = 0, tot = 0;
     auto add = [&](int j) {
         double T = th.at(j);
         if constexpr (SHIFT != 0) T = SHIFT > 0 ? T + d : T - d;
@@ -505,7 +508,7 @@ __device__ __forceinline__ int fold_cost(const double (&z)[VPL], const Threshold
 #pragma unroll
         for (int k = 0; k < VPL; ++k) {
             const bool above = fabs(z[k]) > T;
-            c += (int)__popcll(__ballot(above));
+            c += (int)__popcll(ballot(above));
             if (COUNT) cnt[k] += above ? 1 : 0;
         }
         cost += c * th.f.W[j];
@@ -527,8 +530,6 @@ __device__ __forceinline__ int ceil_log2_8(double d) {
                        ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)hi32(d)) << 32);
     return (int)((u - 1) >> 52) - 1022 + 3;
 }
-
-__device__ __forceinline__ bool uniform_all(bool c) { return __ballot(c) == ~0ull; }
 
 // Drift by thresholds; false if the result is not certain (m is then not
 // set).  xmin, xmax: extrema of the stream.
@@ -562,7 +563,10 @@ __device__ __forceinline__ bool fold_drift(const double (&x)[VPL], double xmin, 
         hi = ceil_log2_8(dmax - dlow);
     }
     const int u0 = hi * kLambdaSteps - kBracketUnits;
-    const int budget32 = (int)(budget < INT_MAX ? budget : INT_MAX);
+    // what the budget leaves beyond the centre level's rate for every value (a
+    // scalar, so that the search's branches and bracket stay scalar)
+    const int room = __builtin_amdgcn_readfirstlane((int)(budget < INT_MAX / 2 ? budget : INT_MAX / 2)) - f.base;
+    const int room1 = room + 1;
 
     const double s2 = s + s, ss = s2 * s, ctr = o + s * (0.5 * (double)(M - 1));
     double z[VPL];
@@ -579,7 +583,7 @@ __device__ __forceinline__ bool fold_drift(const double (&x)[VPL], double xmin, 
 #pragma unroll
     for (int k = 0; k < VPL; ++k) cnt[k] = 0;
     double dc = d0;                            // certainty of the sign of x - c
-    if (fold_cost<-1, false>(z, th, d0, t0, none) <= budget32) {
+    if (fold_cost<-1, false>(z, th, d0, t0, none) <= room) {
         // the nearest levels fit: the last grid point
         fold_cost<-1, true>(z, th, d0, t0, cnt);
         const double lt = max_nn(0x1p-29 * K * S, 2.0 * lam_at(1));
@@ -587,34 +591,35 @@ __device__ __forceinline__ bool fold_drift(const double (&x)[VPL], double xmin, 
         fold_cost<1, false>(z, th, delta(lt), t1, none);
         if (t0 != t1 || !uniform_all(16.0 * lt <= ss)) return false;
     } else {
-        // the bracket's upper 20 octaves: lambda goes with the bisection, the
-        // factors 2^(+-5), 2^(+-2.5), ... of its steps exact to rounding (the
-        // end points below use the grid's values)
-        int klo = 2048, khi = 4096, k = 3072;
+        // the bracket's upper 20 octaves, Alg. 1's bisection less its first
+        // step: lambda goes with it by the factors 2^(+-5), 2^(+-2.5), ...,
+        // given by their high words (2e-7; the end points below use the grid's
+        // values)
+        constexpr uint32_t kUp[11] = {
+            0x40400000, 0x4016A09E, 0x400306FE, 0x3FF8ACE5, 0x3FF3DEA6, 0x3FF1D487,
+            0x3FF0E3EC, 0x3FF0706B, 0x3FF037D4, 0x3FF01BD2, 0x3FF00DE3};
+        constexpr uint32_t kDn[11] = {
+            0x3FA00000, 0x3FC6A09E, 0x3FDAE8A0, 0x3FE4BFDB, 0x3FE9C492, 0x3FECB721,
+            0x3FEE502F, 0x3FEF252B, 0x3FEF91D8, 0x3FEFC8BC, 0x3FEFE452};
+        int klo = 2048;
         th.lam = ldexp(1.0, hi - 10);
-        constexpr double kUp[11] = {
-            32.0, 5.656854249492381, 2.378414230005442, 1.5422108254079407,
-            1.241857812073484, 1.1143867425958924, 1.0556451783605572, 1.0274459491187637,
-            1.0136300849514894, 1.0067919769999607, 1.0033902416308227};
-        constexpr double kDn[11] = {
-            0.03125, 0.1767766952966369, 0.42044820762685725, 0.6484197773255048,
-            0.8052451659746271, 0.8973545375015536, 0.9472879907934828, 0.9732872087896166,
-            0.9865531961276172, 0.9932538427449537, 0.9966212132726022};
 #pragma unroll
         for (int it = 0; it < 11; ++it) {
-            const bool fits = fold_cost<0, false>(z, th, 0.0, t1, none) <= budget32;
-            if (fits) khi = k;
-            else klo = k;
-            th.lam *= fits ? kDn[it] : kUp[it];
-            k = (klo + khi) >> 1;
+            // all ones if it fits (selects on a scalar condition cost two
+            // more scalar instructions each than masking)
+            uint32_t fits;
+            asm("s_ashr_i32 %0, %1, 31" : "=s"(fits) : "s"(fold_cost<0, false>(z, th, 0.0, t1, none) - room1) : "scc");
+            klo += (1024 >> it) & ~fits;
+            th.lam *= join(0u, kUp[it] ^ ((kUp[it] ^ kDn[it]) & fits));
         }
+        const int khi = klo + 1;
         if (khi == 4096) return false;
-        const double lg = lam_at(khi), lb = lam_at(khi - 1), dg = delta(lg);
+        const double lg = lam_at(khi), lb = lam_at(klo), dg = delta(lg);
         th.lam = lb;
-        if (fold_cost<1, false>(z, th, delta(lb), t1, none) <= budget32) return false;
+        if (fold_cost<1, false>(z, th, delta(lb), t1, none) <= room) return false;
         th.lam = lg;
         fold_cost<1, false>(z, th, dg, t1, none);
-        if (fold_cost<-1, true>(z, th, dg, t0, cnt) > budget32 || t0 != t1) return false;
+        if (fold_cost<-1, true>(z, th, dg, t0, cnt) > room || t0 != t1) return false;
         if (!uniform_all(lb >= 0x1p-25 * K * S)) return false;
         if constexpr (POOL) {
             // the outermost thresholds are not about to trade places, and a
@@ -631,7 +636,7 @@ __device__ __forceinline__ bool fold_drift(const double (&x)[VPL], double xmin, 
     if (f.even) {
         uint64_t near = 0;
 #pragma unroll
-        for (int k = 0; k < VPL; ++k) near |= __ballot(fabs(z[k]) <= dc);
+        for (int k = 0; k < VPL; ++k) near |= ballot(fabs(z[k]) <= dc);
         if (near) return false;
     }
     const int below = (M - 1) / 2, above = M / 2;
@@ -898,7 +903,11 @@ __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void enco
     // multiple of the window, so no workgroup straddles two): scale times int8
     // is exact in fp32
     // (a bad block-table entry reads page 0; the record write then skips it)
-    float mean[TOK ? 1 : VPL];
+    double mean[TOK ? 1 : VPL];                   // (0 for values: x - 0 is x)
+    if constexpr (!TOK) {
+#pragma unroll
+        for (int k = 0; k < VPL; ++k) mean[k] = 0.0;
+    }
     if (a.mean_q) {
         bool bad = false;
         if constexpr (TOK) {
@@ -910,7 +919,7 @@ __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void enco
             const int64_t wi = window_index(a.pg, a.H, a.t_cap, b, h, first / DQ_MEAN_WINDOW, bad);
             const float sc = half_bits_to_f32(a.mean_scale[wi]);
 #pragma unroll
-            for (int k = 0; k < VPL; ++k) mean[k] = sc * (float)a.mean_q[wi * n + ch + kWave * k];
+            for (int k = 0; k < VPL; ++k) mean[k] = (double)(sc * (float)a.mean_q[wi * n + ch + kWave * k]);
         }
     }
     __syncthreads();
@@ -933,9 +942,14 @@ __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void enco
                 for (int k = 0; k < HV; ++k) x[HV * g + k] = v[k];
             }
             if (pass == 0 && i + kEncWaves < active) load_stream(i + kEncWaves);
-            if (a.mean_q) {
+            if constexpr (TOK) {
+                if (a.mean_q) {
 #pragma unroll
-                for (int k = 0; k < VPL; ++k) x[k] = x[k] - (double)(TOK ? s_mean[ch + kWave * k] : mean[TOK ? 0 : k]);
+                    for (int k = 0; k < VPL; ++k) x[k] = x[k] - (double)s_mean[ch + kWave * k];
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < VPL; ++k) x[k] = x[k] - mean[k];
             }
             double mn = x[0], mx = x[0];
             bool fin = isfinite(x[0]);
@@ -949,6 +963,8 @@ __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void enco
             wave_minmax_nn(mn, mx);
             if (!uniform_all(fin && mn != 0.0 && mx != 0.0)) {
                 // NaN, and which zero it is, as plain comparisons have it
+                // (rare: kept a branch)
+                asm volatile("" : "+v"(x[0]));
                 mn = mx = x[0];
 #pragma unroll
                 for (int k = 0; k < VPL; ++k) {
