@@ -23,6 +23,8 @@
 #include <float.h>
 #include <limits.h>
 
+#include <type_traits>
+
 #include "dq_common.h"
 
 namespace dq {
@@ -437,8 +439,7 @@ __device__ void drift(const double (&x)[VPL], double s, double o, int64_t budget
 // 2^-50 (K^2 + 16 lambda); delta = 2^-44 (K^2 + 16 lambda) leaves a factor of
 // 16.  fold_drift therefore searches with the thresholds and then certifies
 // what Alg. 1's bisection returns, U:
-//  * at U no z is within delta of a threshold (the counts at T_j - delta and
-//    at T_j + delta are equal), and the code length fits;
+//  * at U no z is within delta of a threshold, and the code length fits;
 //  * one grid step below U it does not fit, whatever the values within delta
 //    of a threshold do (the count at T_j + delta).
 // The other points that the bisection visits are at least one grid step
@@ -449,9 +450,9 @@ __device__ void drift(const double (&x)[VPL], double s, double o, int64_t budget
 // multiples of 2^-16, so r_m <= r_g (>= below U) once lambda >= 2^-25 K S:
 // every point above U fits and every point below does not, and the bisection
 // ends at U.  When already the nearest levels fit, the bisection goes down to
-// its last grid point: the counts at T_j(0) - delta and T_j(lambda_top) + delta
-// have to be equal for lambda_top = 2^-29 K S, below which every assignment is
-// then the same and above which the bound holds.
+// its last grid point: no z may lie between T_j(0) - delta and T_j(lambda_top) +
+// delta for lambda_top = 2^-29 K S, below which every assignment is then the
+// same and above which the bound holds.
 // A stream that does not pass (a value within 2^-44 of a tie, no certain
 // bracket) goes through drift() as it is.
 constexpr int kFoldMax = (DQ_MAX_LEVELS - 1) / 2;
@@ -463,56 +464,49 @@ struct FoldArgs {
     double off;            // distance of the first threshold from the centre in steps: 1 or 1/2
     int32_t W[kFoldMax];   // R_outer - R_inner (Q16)
     double w[kFoldMax];    // the same as a rate
+    float wf[kFoldMax];
 };
 
-// Thresholds of one lambda: JM in registers from B (JM = 0: formed one at a
-// time, the pooled pair together).
-template <int JM, bool POOL>
+// T_j(lambda) + d in precision F, JM of them in registers or (JM = 0) formed
+// one at a time, the pooled pair together.
+template <typename F, int JM, bool POOL>
 struct Thresholds {
-    double B[JM > 0 ? JM : 1], ss, lam;
     const FoldArgs& f;
-    __device__ __forceinline__ Thresholds(const FoldArgs& f_, double ss_) : ss(ss_), lam(0.0), f(f_) {
-        if constexpr (JM > 0) {
+    F ss;                                      // 2 s^2
+    F B[JM > 0 ? JM : 1];
+    __device__ __forceinline__ Thresholds(const FoldArgs& f_, F ss_) : f(f_), ss(ss_) {
 #pragma unroll
-            for (int j = 0; j < JM; ++j) B[j] = ss * ((double)j + f.off);
-        }
+        for (int j = 0; j < JM; ++j) B[j] = ss * ((F)j + (F)f.off);
     }
-    __device__ __forceinline__ double raw(int j) const {
-        if constexpr (JM > 0) return __builtin_fma(lam, f.w[j], B[j]);
-        return __builtin_fma(lam, f.w[j], ss * ((double)j + f.off));
+    __device__ __forceinline__ F raw(int j, F lam) const {
+        const F b = JM > 0 ? B[JM > 0 ? j : 0] : ss * ((F)j + (F)f.off);
+        if constexpr (sizeof(F) == 4) return __builtin_fmaf(lam, f.wf[j], b);
+        else return __builtin_fma(lam, f.w[j], b);
     }
     __device__ __forceinline__ int count() const { return JM > 0 ? JM : f.J; }
-    __device__ __forceinline__ double at(int j) const {
-        const double T = raw(j);
+    __device__ __forceinline__ F at(int j, F lam) const {
+        const F T = raw(j, lam);
         const int J = count();
         if constexpr (POOL) {
             if (j >= J - 2) {
-                const double To = raw(2 * J - 3 - j), m = 0.5 * (T + To);
-                return j == J - 2 ? min_nn(T, m) : max_nn(T, m);
+                const F To = raw(2 * J - 3 - j, lam), m = (F)0.5 * (T + To);
+                return j == J - 2 ? (T < m ? T : m) : (T > m ? T : m);
             }
         }
         return T;
     }
 };
 
-// Code length beyond f.base at the thresholds shifted by SHIFT d, and the number
-// of (value, threshold) pairs with z above; COUNT: that number per value in cnt.
-template <int SHIFT, bool COUNT, int VPL, int JM, bool POOL>
-__device__ __forceinline__ int fold_cost(const double (&z)[VPL], const Thresholds<JM, POOL>& th, double d, int& total,
-                                         int (&cnt)[VPL]) {
-    int cost = 0, tot = 0;
+// Code length beyond f.base at lambda.
+template <typename F, int VPL, int JM, bool POOL>
+__device__ __forceinline__ int fold_cost(const F (&z)[VPL], const Thresholds<F, JM, POOL>& th, F lam) {
+    int cost = 0;
     auto add = [&](int j) {
-        double T = th.at(j);
-        if constexpr (SHIFT != 0) T = SHIFT > 0 ? T + d : T - d;
+        const F T = th.at(j, lam);
         int c = 0;
 #pragma unroll
-        for (int k = 0; k < VPL; ++k) {
-            const bool above = fabs(z[k]) > T;
-            c += (int)__popcll(ballot(above));
-            if (COUNT) cnt[k] += above ? 1 : 0;
-        }
+        for (int k = 0; k < VPL; ++k) c += (int)__popcll(ballot(z[k] > T));
         cost += c * th.f.W[j];
-        tot += c;
     };
     if constexpr (JM > 0) {
 #pragma unroll
@@ -520,7 +514,6 @@ __device__ __forceinline__ int fold_cost(const double (&z)[VPL], const Threshold
     } else {
         for (int j = 0; j < th.f.J; ++j) add(j);
     }
-    total = tot;
     return cost;
 }
 
@@ -569,57 +562,118 @@ __device__ __forceinline__ bool fold_drift(const double (&x)[VPL], double xmin, 
     const int room1 = room + 1;
 
     const double s2 = s + s, ss = s2 * s, ctr = o + s * (0.5 * (double)(M - 1));
-    double z[VPL];
-#pragma unroll
-    for (int k = 0; k < VPL; ++k) z[k] = (x[k] - ctr) * s2;
-    Thresholds<JM, POOL> th(f, ss);
     const double d0 = K * K * 0x1p-44;
     auto delta = [&](double lam) { return __builtin_fma(lam, 0x1p-40, d0); };
     auto lam_at = [&](int k) {                 // lambda of grid point k of the bracket, as Alg. 1 has it
         const int u = u0 + 5 * k;
         return ldexp((double)c.lam[u & (kLambdaSteps - 1)], u >> 9);
     };
-    int cnt[VPL], none[VPL], t0, t1;
+    // all the search has to find is the grid point to certify: in fp32 where
+    // the z are many registers (then formed again for the certificate)
+    constexpr bool kWide = VPL <= 4;
+    using F = std::conditional_t<kWide, double, float>;
+    F zs[VPL];
+#pragma unroll
+    for (int k = 0; k < VPL; ++k) zs[k] = (F)fabs((x[k] - ctr) * s2);
+    const Thresholds<F, JM, POOL> ts(f, (F)ss);
+    const Thresholds<double, JM, POOL> th(f, ss);
+    int cnt[VPL];
 #pragma unroll
     for (int k = 0; k < VPL; ++k) cnt[k] = 0;
-    double dc = d0;                            // certainty of the sign of x - c
-    if (fold_cost<-1, false>(z, th, d0, t0, none) <= room) {
-        // the nearest levels fit: the last grid point
-        fold_cost<-1, true>(z, th, d0, t0, cnt);
-        const double lt = max_nn(0x1p-29 * K * S, 2.0 * lam_at(1));
-        th.lam = lt;
-        fold_cost<1, false>(z, th, delta(lt), t1, none);
-        if (t0 != t1 || !uniform_all(16.0 * lt <= ss)) return false;
+    double near = ss;                          // smallest distance of a z from its decisions
+    double dc = d0;                            // and what makes them certain
+    // f(z, value) over the stream, j-th threshold pair outside or inside: the
+    // z of many values are formed where they are used
+    auto each = [&](auto&& body) {
+        if constexpr (JM > 0) {
+#pragma unroll
+            for (int k = 0; k < VPL; ++k) {
+                const double z = kWide ? (double)zs[k] : fabs((x[k] - ctr) * s2);
+#pragma unroll
+                for (int j = 0; j < JM; ++j) body(k, j, z);
+            }
+        } else {
+            for (int j = 0; j < f.J; ++j) {
+#pragma unroll
+                for (int k = 0; k < VPL; ++k) body(k, j, kWide ? (double)zs[k] : fabs((x[k] - ctr) * s2));
+            }
+        }
+    };
+    if (fold_cost(zs, ts, (F)0) <= room) {
+        // the nearest levels fit: the last grid point.  No z between T_j(0) -
+        // delta and T_j(lambda_top) + delta
+        const double lt = max_nn(0x1p-29 * K * S, 2.0 * lam_at(1)), dt = delta(lt);
+        int cost = 0;
+        uint64_t between = 0;
+        each([&](int k, int j, double z) {
+            const bool above = z > th.at(j, 0.0) - d0;
+            const uint64_t a = ballot(above);
+            between |= a ^ ballot(z > th.at(j, lt) + dt);
+            cost += (int)__popcll(a) * f.W[j];
+            cnt[k] += above ? 1 : 0;
+        });
+        if (between || cost > room || !uniform_all(16.0 * lt <= ss)) return false;
     } else {
         // the bracket's upper 20 octaves, Alg. 1's bisection less its first
         // step: lambda goes with it by the factors 2^(+-5), 2^(+-2.5), ...,
-        // given by their high words (2e-7; the end points below use the grid's
-        // values)
+        // as high words of doubles (2e-7) or as fp32
         constexpr uint32_t kUp[11] = {
             0x40400000, 0x4016A09E, 0x400306FE, 0x3FF8ACE5, 0x3FF3DEA6, 0x3FF1D487,
             0x3FF0E3EC, 0x3FF0706B, 0x3FF037D4, 0x3FF01BD2, 0x3FF00DE3};
         constexpr uint32_t kDn[11] = {
             0x3FA00000, 0x3FC6A09E, 0x3FDAE8A0, 0x3FE4BFDB, 0x3FE9C492, 0x3FECB721,
             0x3FEE502F, 0x3FEF252B, 0x3FEF91D8, 0x3FEFC8BC, 0x3FEFE452};
+        constexpr uint32_t kUpF[11] = {
+            0x42000000, 0x40B504F3, 0x401837F0, 0x3FC5672A, 0x3F9EF532, 0x3F8EA43A,
+            0x3F871F62, 0x3F838359, 0x3F81BEA1, 0x3F80DE8F, 0x3F806F17};
+        constexpr uint32_t kDnF[11] = {
+            0x3D000000, 0x3E3504F3, 0x3ED744FD, 0x3F25FED7, 0x3F4E248C, 0x3F65B907,
+            0x3F728177, 0x3F79295A, 0x3F7C8EC0, 0x3F7E45E2, 0x3F7F2291};
         int klo = 2048;
-        th.lam = ldexp(1.0, hi - 10);
+        F lam = (F)ldexp(1.0, hi - 10);
 #pragma unroll
         for (int it = 0; it < 11; ++it) {
             // all ones if it fits (selects on a scalar condition cost two
             // more scalar instructions each than masking)
             uint32_t fits;
-            asm("s_ashr_i32 %0, %1, 31" : "=s"(fits) : "s"(fold_cost<0, false>(z, th, 0.0, t1, none) - room1) : "scc");
+            asm("s_ashr_i32 %0, %1, 31" : "=s"(fits) : "s"(fold_cost(zs, ts, lam) - room1) : "scc");
             klo += (1024 >> it) & ~fits;
-            th.lam *= join(0u, kUp[it] ^ ((kUp[it] ^ kDn[it]) & fits));
+            if constexpr (kWide) lam *= join(0u, kUp[it] ^ ((kUp[it] ^ kDn[it]) & fits));
+            else lam *= __uint_as_float(kUpF[it] ^ ((kUpF[it] ^ kDnF[it]) & fits));
         }
-        const int khi = klo + 1;
-        if (khi == 4096) return false;
-        const double lg = lam_at(khi), lb = lam_at(klo), dg = delta(lg);
-        th.lam = lb;
-        if (fold_cost<1, false>(z, th, delta(lb), t1, none) <= room) return false;
-        th.lam = lg;
-        fold_cost<1, false>(z, th, dg, t1, none);
-        if (fold_cost<-1, true>(z, th, dg, t0, cnt) > room || t0 != t1) return false;
+        // certify klo + 1; a value within the fp32 search's rounding of its
+        // threshold may have moved it by a grid point
+        double lg, lb, dg;
+        int cg, cb;
+        auto certify = [&]() {
+            lg = lam_at(klo + 1);
+            lb = lam_at(klo);
+            dg = delta(lg);
+            const double db = delta(lb);
+            cg = cb = 0;
+            each([&](int k, int j, double z) {
+                const double T = th.at(j, lg);
+                const bool above = z > T;
+                cg += (int)__popcll(ballot(above)) * f.W[j];
+                cb += (int)__popcll(ballot(z > th.at(j, lb) + db)) * f.W[j];
+                near = min_nn(near, fabs(z - T));
+                cnt[k] += above ? 1 : 0;
+            });
+        };
+        if (klo == 4095) return false;
+        certify();
+        if constexpr (!kWide) {
+#pragma unroll 1
+            for (int tries = 0; (cb <= room || cg > room) && tries < 2; ++tries) {
+                klo += cb <= room ? -1 : 1;
+                if (klo == 4095) return false;
+                near = ss;
+#pragma unroll
+                for (int k = 0; k < VPL; ++k) cnt[k] = 0;
+                certify();
+            }
+        }
+        if (cb <= room || cg > room) return false;
         if (!uniform_all(lb >= 0x1p-25 * K * S)) return false;
         if constexpr (POOL) {
             // the outermost thresholds are not about to trade places, and a
@@ -633,16 +687,13 @@ __device__ __forceinline__ bool fold_drift(const double (&x)[VPL], double xmin, 
         }
         dc = dg;
     }
-    if (f.even) {
-        uint64_t near = 0;
-#pragma unroll
-        for (int k = 0; k < VPL; ++k) near |= ballot(fabs(z[k]) <= dc);
-        if (near) return false;
-    }
     const int below = (M - 1) / 2, above = M / 2;
 #pragma unroll
-    for (int k = 0; k < VPL; ++k) m[k] = z[k] < 0.0 ? below - cnt[k] : above + cnt[k];
-    return true;
+    for (int k = 0; k < VPL; ++k) {
+        m[k] = x[k] < ctr ? below - cnt[k] : above + cnt[k];
+        if (f.even) near = min_nn(near, fabs((x[k] - ctr) * s2));
+    }
+    return uniform_all(near > dc);
 }
 
 __device__ __forceinline__ uint16_t f64_to_half_bits(double v) {
@@ -774,7 +825,12 @@ struct EncLayout {
     int sym_row, rec_row;
 };
 
-__host__ __device__ inline EncLayout enc_layout(int n, int C, int ns, bool tok) {
+// Symbols of per-token streams of up to 16 levels are packed, elements i and i +
+// 64 of every 128 in one byte: four workgroups of 32 1024-value streams then
+// share a CU.
+__host__ __device__ inline bool packed_symbols(bool tok, int M) { return tok && M <= 16; }
+
+__host__ __device__ inline EncLayout enc_layout(int n, int C, int ns, bool tok, int M) {
     EncLayout L;
     int off = 0;
     auto take = [&](int bytes) {
@@ -793,7 +849,7 @@ __host__ __device__ inline EncLayout enc_layout(int n, int C, int ns, bool tok) 
     L.flag = take(4 * ns);
     L.state = take(4 * ns);
     L.emitted = take(4 * ns);
-    L.sym_row = n + 4;
+    L.sym_row = (packed_symbols(tok, M) ? n / 2 : n) + 4;
     L.rec_row = 4 * (((C + 3) / 4) | 1);
     L.sym = take(ns * L.sym_row);
     L.rec = take(ns * L.rec_row + 8);
@@ -826,9 +882,14 @@ __device__ __forceinline__ void nearest(const double (&x)[VPL], double s, double
     }
 }
 
-// Wavefronts per SIMD that the registers are held to.
+// Wavefronts per SIMD that the registers are held to: for the folded search of
+// streams of up to 128 values six (two thresholds: 4 x 8192 tokens, K and V, 787
+// us, 808 with five and 837 with eight) or five (four thresholds spill with six:
+// 328 and 314 us for 2 x 4096 tokens), four for per-token streams (their LDS, 36
+// KB, fits four workgroups), three where every step tries every level of those or
+// holds 16 levels.
 __host__ __device__ constexpr int enc_waves(int vpl, int mb, bool tok, int jm) {
-    return tok || mb == 16 ? 3 : jm >= 0 ? (vpl <= 2 ? 6 : 4) : 1;
+    return tok && jm >= 0 ? 4 : tok || mb == 16 ? 3 : jm >= 0 ? (vpl > 2 ? 4 : jm == 2 ? 6 : 5) : 1;
 }
 
 // JM: thresholds of the folded drift in registers (fold_drift), 0: any number,
@@ -838,8 +899,6 @@ __host__ __device__ constexpr int enc_waves(int vpl, int mb, bool tok, int jm) {
 // refit with nearest-level rounding in place of both drifts, and b-bit
 // symbols (M = 2^b, b = 8 (C - 4) / n rounded down) packed after the 4-byte
 // header, least significant bit first, instead of the rANS payload.
-// Per-token streams and 16 levels in registers: three workgroups per CU (at
-// most 168 VGPRs; the per-token LDS staging, about 50 KB, fits three).
 template <int VPL, int MB, bool TOK, int JM, bool POOL, bool FIXED = false>
 __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void encode_kernel(EncArgs a) {
     constexpr int n = kWave * VPL;
@@ -848,7 +907,7 @@ __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void enco
     extern __shared__ __align__(16) uint8_t smem[];
     const TabArgs& ta = a.ta;
     const int C = ta.C, ns = a.ns;
-    const EncLayout L = enc_layout(n, C, ns, TOK);
+    const EncLayout L = enc_layout(n, C, ns, TOK, ta.M);
     double* s_rate = reinterpret_cast<double*>(smem + L.rate);
     int32_t* s_cost = reinterpret_cast<int32_t*>(smem + L.cost);
     float* s_lam = reinterpret_cast<float*>(smem + L.lam);
@@ -879,7 +938,7 @@ __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void enco
 #pragma unroll
         for (int g = 0; g < NH; ++g) load_raw<HV>(row + (int64_t)g * a.sh, raw[g], lane, a.rotate);
     };
-    if (wave < active) load_stream(wave);
+    if (!TOK && wave < active) load_stream(wave);
 
     for (int i = tid; i < (FIXED ? 0 : ta.M); i += kEncThreads) {
         s_cost[i] = ta.t.cost[i];
@@ -924,15 +983,14 @@ __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void enco
     }
     __syncthreads();
     DriftCtx dc{s_rate, s_cost, s_lam, ta.M, ta.cheapest, ta.rmin};
+    const bool packed = packed_symbols(TOK, ta.M);
 
     bool range_bad = false;
     for (int pass = 0;; ++pass) {
         // Drift, wavefront per stream.
         for (int i = wave; i < active; i += kEncWaves) {
-            if (pass > 0) {
-                if (!s_flag[i]) continue;
-                load_stream(i);
-            }
+            if (pass > 0 && !s_flag[i]) continue;
+            if (TOK || pass > 0) load_stream(i);
             double x[VPL];
 #pragma unroll
             for (int g = 0; g < NH; ++g) {
@@ -941,7 +999,7 @@ __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void enco
 #pragma unroll
                 for (int k = 0; k < HV; ++k) x[HV * g + k] = v[k];
             }
-            if (pass == 0 && i + kEncWaves < active) load_stream(i + kEncWaves);
+            if (!TOK && pass == 0 && i + kEncWaves < active) load_stream(i + kEncWaves);
             if constexpr (TOK) {
                 if (a.mean_q) {
 #pragma unroll
@@ -1031,8 +1089,14 @@ __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void enco
                 s = (double)sf;
                 o = (double)of;
             }
+            uint8_t* sym = s_sym + i * L.sym_row + ch;
+            if (packed) {
 #pragma unroll
-            for (int k = 0; k < VPL; ++k) s_sym[i * L.sym_row + ch + kWave * k] = (uint8_t)m[k];
+                for (int k = 0; k + 1 < VPL; k += 2) sym[kWave * (k / 2)] = (uint8_t)(m[k] | m[k + 1] << 4);
+            } else {
+#pragma unroll
+                for (int k = 0; k < VPL; ++k) sym[kWave * k] = (uint8_t)m[k];
+            }
         }
         __syncthreads();
 
@@ -1085,10 +1149,12 @@ __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void enco
                 xs = e ? xs >> 8 : xs;
             };
             for (int j = n / 4 - 1; j >= 0; --j) {
-                const uint32_t w = sym4[j];
+                // (packed: elements 64 .. 127 of every 128 in the high halves)
+                const uint32_t w = packed ? sym4[(j >> 5) * 16 + (j & 15)] >> ((j >> 4 & 1) * 4) : sym4[j];
+                const uint32_t mask = packed ? 0xFu : 0xFFu;
                 uint4 ent[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) ent[u] = s_ent[(w >> (8 * u)) & 0xFFu];
+                for (int u = 0; u < 4; ++u) ent[u] = s_ent[(w >> (8 * u)) & mask];
 #pragma unroll
                 for (int u = 3; u >= 0; --u) {
                     emit(ent[u].x);
@@ -1184,12 +1250,15 @@ __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void enco
 }
 
 // Streams per workgroup: as many as the coder has lanes for (64, or 32 for
-// per-token streams, whose symbols and records then take about 50 KB of LDS),
-// fewer while the grid would leave CUs without two workgroups: a small append
-// is bound by the streams that a wavefront takes in turn.
+// per-token streams, whose symbols and records then take 28 KB of LDS), fewer
+// while the grid would leave a CU with fewer than four workgroups: a small append
+// is bound by the streams that a wavefront takes in turn.  K and V, us, stopping
+// at one / two / four workgroups per CU: 16 x 128 tokens 164 / 121 / 108, 1 x
+// 4096 191 / 191 / 161, per-token 4 x 2048 572 / 476 / 458; below 1 x 128 tokens
+// the same.
 int streams_per_group(int most, int64_t tokens, int64_t rows) {
     int ns = most;
-    while (ns > kEncWaves && (tokens + ns - 1) / ns * rows < 2 * (int64_t)cu_count()) ns /= 2;
+    while (ns > kEncWaves && (tokens + ns - 1) / ns * rows < 4 * (int64_t)cu_count()) ns /= 2;
     return ns;
 }
 
@@ -1209,6 +1278,7 @@ bool fold_args(const dq_tables* tab, int n, FoldArgs& f) {
     for (int j = 0; j < kFoldMax; ++j) {
         f.W[j] = j < J ? R[M / 2 + j + 1] - R[M / 2 + j] : 0;
         f.w[j] = f.W[j] / 65536.0;
+        f.wf[j] = (float)f.w[j];
     }
     for (int j = 0; j < J; ++j) {
         if (f.W[j] < 0) return false;
@@ -1222,7 +1292,7 @@ bool fold_args(const dq_tables* tab, int n, FoldArgs& f) {
 
 template <int VPL, int MB, bool TOK, int JM, bool POOL = false>
 int launch_encode_as(const EncArgs& a, dim3 grid, hipStream_t stream) {
-    const int smem = enc_layout(kWave * VPL, a.ta.C, a.ns, TOK).total;
+    const int smem = enc_layout(kWave * VPL, a.ta.C, a.ns, TOK, a.ta.M).total;
     if (int rc = hip_check("hipFuncSetAttribute",
                            hipFuncSetAttribute(reinterpret_cast<const void*>(&encode_kernel<VPL, MB, TOK, JM, POOL>),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, smem)))
@@ -1347,7 +1417,7 @@ int launch_encode_fixed(int32_t n, int32_t record_bytes, const Pages& pg, const 
         if (int rc = launch_key_mean(vpl, a, B, mean_q, mean_scale, stream)) return rc;
     a.ns = streams_per_group(kEncStreams, n_new, (int64_t)H * B);
     const dim3 grid((n_new + a.ns - 1) / a.ns, H, B);
-    const int smem = enc_layout(n, record_bytes, a.ns, false).total;
+    const int smem = enc_layout(n, record_bytes, a.ns, false, a.ta.M).total;
     switch (vpl) {
         case 1: encode_kernel<1, 0, false, -1, false, true><<<grid, kEncThreads, smem, stream>>>(a); break;
         case 2: encode_kernel<2, 0, false, -1, false, true><<<grid, kEncThreads, smem, stream>>>(a); break;
