@@ -5,6 +5,10 @@
 
 #include "dq_common.h"
 
+// a b + c inside one expression as one fused multiply-add (one rounding less);
+// the encoder, whose decisions are the format, does not include this file
+#pragma clang fp contract(on)
+
 namespace dq {
 
 __device__ __forceinline__ float half_lo(uint32_t w) { return half_bits_to_f32((uint16_t)(w & 0xFFFFu)); }
@@ -82,6 +86,7 @@ __device__ __forceinline__ void rotate_query_heads(const uint16_t* q, int nh, in
 }
 
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ v4i mfma(uint32_t a, uint32_t b, v4i c) {
     return __builtin_amdgcn_mfma_i32_4x4x4i8((int)a, (int)b, c, 0, 0, 0);
@@ -92,6 +97,12 @@ __device__ __forceinline__ v4i mfma(uint32_t a, uint32_t b, v4i c) {
 // of column l % 16.
 __device__ __forceinline__ v4i mfma16(uint64_t a, uint64_t b, v4i c) {
     return __builtin_amdgcn_mfma_i32_16x16x32_i8((long)a, (long)b, c, 0, 0, 0);
+}
+
+// v_mfma_i32_16x16x64_i8: 16 bytes of K per lane; A and B are loaded alike, so
+// which K a byte stands for does not matter.
+__device__ __forceinline__ v4i mfma64(const v4i& a, const v4i& b, const v4i& c) {
+    return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0);
 }
 
 // ds_read_b64_tr_b8 at LDS byte address off.  Within each group of 16 lanes,
@@ -111,6 +122,164 @@ __device__ __forceinline__ float pick4(const float* v, int slot) {
 
 __device__ __forceinline__ float combine(const v4i& d0, const v4i& d1, const v4i& d2, int r) {
     return (float)d2[r] * 65536.0f + (float)d1[r] * 256.0f + (float)d0[r];
+}
+
+// ---- a 64-token tile's scores, softmax and weighted values
+//
+// Work layout.  Lane l serves query-head slot l / 16 of a group of four and
+// token 16 tg + l % 16 of each 16-token group tg: the rows of the 16x16x64
+// products are (slot, digit) with a zero fourth digit, their columns tokens (q .
+// k) or channels (P . v), so that a lane receives the three digit sums of its
+// slot.  The running maximum, sums and corrections are then one per lane, and a
+// tile's maximum is four values and four DPP steps inside the row of 16 lanes.
+// (With v_mfma_i32_4x4x4_16b_i8 on the levels as they appear, a lane held all
+// four slots of its token: 96 products per tile instead of 8, four times the
+// reductions, and 32 reads of query digits.)
+constexpr int kRowT = 80;                 // bytes per row of a level or query-digit tile (64 channels + pad)
+constexpr int kQTile = 16 * kRowT;        // query digits of a group's 16 rows, one 64-channel slice
+constexpr int kColGroup = 16 * kRowT;     // 16 token rows of a level tile
+
+// Digits of rotated query head g (values r0, r1 of channels lane, lane + 64, unit
+// qs) into the tiles [group][slice][row 4 slot + digit][kRowT].
+__device__ __forceinline__ void query_digits(uint8_t* tiles, int g, int lane, float r0, float r1, float qs) {
+#pragma unroll
+    for (int sl = 0; sl < 2; ++sl) {
+        int v = 0;
+        if (qs > 0.f) {
+            v = (int)rintf((sl ? r1 : r0) / qs);
+            v = max(-4194304, min(4194304, v));
+        }
+        // adding 128 to every byte and flipping its top bit leaves the signed digits
+        const uint32_t w = ((uint32_t)v + 0x00808080u) ^ 0x00808080u;
+        uint8_t* dst = tiles + ((g / 4) * 2 + sl) * kQTile + 4 * (g % 4) * kRowT + lane;
+        dst[0] = (uint8_t)w;
+        dst[kRowT] = (uint8_t)(w >> 8);
+        dst[2 * kRowT] = (uint8_t)(w >> 16);
+        dst[3 * kRowT] = 0;
+    }
+}
+
+// Sixteen dwords (64 channels) of the lane's levels into its row.
+__device__ __forceinline__ void store_levels(uint32_t row, const uint32_t* lev) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        *LDS_PTR(v4i, row + 16 * q) =
+            v4i{(int)lev[4 * q], (int)lev[4 * q + 1], (int)lev[4 * q + 2], (int)lev[4 * q + 3]};
+}
+
+// d[hg][tg] += query digits . levels over one 64-channel slice: col is the
+// lane's operand in the level tile (row l % 16, bytes 16 (l / 16) ..), qa the
+// same in the slice's query tile of group 0.
+template <int HG>
+__device__ __forceinline__ void qk_slice(uint32_t col, uint32_t qa, v4i (&d)[HG][4]) {
+    v4i b[4], a[HG];
+#pragma unroll
+    for (int tg = 0; tg < 4; ++tg) b[tg] = *LDS_PTR(v4i, col + tg * kColGroup);
+#pragma unroll
+    for (int hg = 0; hg < HG; ++hg) a[hg] = *LDS_PTR(v4i, qa + hg * 2 * kQTile);
+#pragma unroll
+    for (int hg = 0; hg < HG; ++hg)
+#pragma unroll
+        for (int tg = 0; tg < 4; ++tg) d[hg][tg] = mfma64(a[hg], b[tg], d[hg][tg]);
+}
+
+// Maximum over each row of 16 lanes, in every lane of the row, of non-NaN
+// floats (wait states as in wave_max_f32).
+__device__ __forceinline__ float row_max16(float v) {
+    asm("s_nop 4\n\t"
+        "v_max_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_max_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_max_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_max_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1"
+        : "+v"(v));
+    return v;
+}
+__device__ __forceinline__ float row_sum16(float v) {
+    v += dpp0<0xB1, 0xF>(v);
+    v += dpp0<0x4E, 0xF>(v);
+    v += dpp0<0x141, 0xF>(v);
+    return v + dpp0<0x140, 0xF>(v);
+}
+
+constexpr float kLowest = -3.4028234663852886e38f;
+
+// Softmax of the lane's four tokens for its slot (Eq. fold-key), the value scale
+// folded into the weights (Eq. fold-value).
+//   d: digit sums; h[tg]: (s, o) of the token's key and value; qs, qsum, qm: the
+//   slot's digit unit, query sum and q . mu, all times softmax_scale log2(e);
+//   left: tokens from l % 16 to the sequence's end (token 16 tg is live while
+//   16 tg < left); m: running maximum.
+// Returns the correction of what was summed before; psum, osum: the lane's
+// parts of sum p and sum p o_v; w: the weights' digits (22-bit fixed point
+// relative to the tile's largest), wscale their unit.
+struct SlotWeights {
+    float corr, psum, osum, wscale;
+    uint32_t w[4];
+};
+__device__ __forceinline__ SlotWeights slot_softmax(const v4i (&d)[4], const float4 (&h)[4], float qs, float qsum,
+                                                    float qm, int left, bool whole, float& m) {
+    float s[4];
+#pragma unroll
+    for (int tg = 0; tg < 4; ++tg) {
+        // |digit sum| <= 128 127 63 < 2^20: the lower two meet exactly in int32
+        const float dot = (float)d[tg][2] * 65536.0f + (float)((d[tg][1] << 8) + d[tg][0]);
+        s[tg] = h[tg].x * (dot * qs) + (h[tg].y * qsum + qm);
+    }
+    if (!whole) {
+#pragma unroll
+        for (int tg = 0; tg < 4; ++tg) s[tg] = 16 * tg < left ? s[tg] : -INFINITY;
+    }
+    SlotWeights r;
+    const float mn = fmaxf(m, row_max16(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]))));
+    const float base = fmaxf(mn, kLowest);           // -inf - base stays -inf
+    // v_exp_f32 directly: arguments are <= 0 and results that would be denormal
+    // may flush to zero
+    r.corr = __builtin_amdgcn_exp2f(m - base);
+    m = mn;
+    float p[4], pw[4];
+#pragma unroll
+    for (int tg = 0; tg < 4; ++tg) {
+        p[tg] = __builtin_amdgcn_exp2f(s[tg] - base);
+        pw[tg] = p[tg] * h[tg].z;                    // >= 0: scales are non-negative
+    }
+    r.psum = (p[0] + p[1]) + (p[2] + p[3]);
+    r.osum = (p[0] * h[0].w + p[1] * h[1].w) + (p[2] * h[2].w + p[3] * h[3].w);
+    const float top = fmaxf(row_max16(fmaxf(fmaxf(pw[0], pw[1]), fmaxf(pw[2], pw[3]))), 1e-30f);
+    const float inv = 4194304.0f * __builtin_amdgcn_rcpf(top);
+    r.wscale = top * (1.0f / 4194304.0f);
+#pragma unroll
+    for (int tg = 0; tg < 4; ++tg) {
+        // 1.5 2^23 + v has v in its low bits, rounded to nearest even
+        const uint32_t v = __float_as_uint(pw[tg] * inv + 12582912.0f) - 0x4B400000u;
+        r.w[tg] = (v + 0x00808080u) ^ 0x00808080u;
+    }
+    return r;
+}
+
+// The lane's four weight words to byte 4 slot of their token rows (16 bytes
+// each); at: tile + 16 (l % 16) + 4 (l / 16).
+__device__ __forceinline__ void store_weights(uint32_t at, const uint32_t (&w)[4]) {
+#pragma unroll
+    for (int tg = 0; tg < 4; ++tg) *LDS_PTR(uint32_t, at + tg * 256) = w[tg];
+}
+
+// Weights of a tile as the A operand (rows (slot, digit), K = 64 tokens).
+__device__ __forceinline__ v4i load_weights(uint32_t a_lane) {
+    const uint64_t lo = lds_tr8(a_lane), hi = lds_tr8(a_lane + 32 * 16);
+    return v4i{(int)(uint32_t)lo, (int)(uint32_t)(lo >> 32), (int)(uint32_t)hi, (int)(uint32_t)(hi >> 32)};
+}
+// 16 channels of the value tile as the B operand.
+__device__ __forceinline__ v4i load_values(uint32_t b_lane) {
+    const uint64_t lo = lds_tr8(b_lane), hi = lds_tr8(b_lane + 32 * kRowT);
+    return v4i{(int)(uint32_t)lo, (int)(uint32_t)(lo >> 32), (int)(uint32_t)hi, (int)(uint32_t)(hi >> 32)};
+}
+// The digit sums of a slot and channel as one number.
+__device__ __forceinline__ float digit_sum(const v4i& d) {
+    return (float)d[2] * 65536.0f + (float)((d[1] << 8) + d[0]);
 }
 
 }  // namespace dq

@@ -28,7 +28,6 @@ constexpr int kD = 128;          // head_dim of the attention kernels
 constexpr int kTile = 64;        // tokens per wavefront tile (one per lane)
 constexpr int kMaxWaves = 16;    // wavefronts per workgroup (LDS permitting)
 constexpr int kVSlice = 64;      // value channels per PV pass
-constexpr int kVRowT = 80;       // bytes per token row of the value tile (64 channels + pad)
 constexpr int kMaxRecDwords = 16;
 constexpr int kMaxLds = 160 * 1024;
 constexpr int kMaxChunk = 16384;  // bounds the per-window q . mu table in LDS
@@ -90,28 +89,30 @@ __global__ void decode_symbols_kernel(TabArgs ta, const uint8_t* __restrict__ re
 // weights (with the value scale folded in) enter as three signed 8-bit digits
 // of a 22-bit fixed-point value, accumulated exactly in int32 and recombined
 // in fp32.
-//   q . k:  v_mfma_i32_4x4x4_16b_i8 (16 blocks of 4x4x4; lane l is column
-//           l % 4 of block l / 4), block = 4 tokens, K = 4 channels.  A = the
-//           query digits of head l % 4, B = the 4 levels the lane just
-//           decoded, D = the lane's own token's dot products for 4 heads.
-//   P . v:  v_mfma_i32_16x16x32_i8, rows = (query-head slot, digit), K = 32
-//           tokens, columns = 16 channels.  Each lane writes its token's
-//           levels and weight digits to token-major LDS rows as they are, and
-//           ds_read_b64_tr_b8 hands every lane the 8 tokens of one row or
-//           column the product wants; D = one slot's three digit sums (and a
-//           zero row) of channel l % 16.
+//   q . k:  v_mfma_i32_16x16x64_i8, rows = (query-head slot, digit), K = 64
+//           channels, columns = 16 tokens.  The levels of both streams wait in
+//           registers until the chains are done (the byte pairs fill the
+//           wavefront's LDS until then); each lane writes its token's key levels
+//           to a token-major row, 64 channels at a time, and reads 16 bytes of a
+//           column's row.  D = one slot's three digit sums (and a zero row) of
+//           token l % 16.
+//   P . v:  the same product, K = 64 tokens, columns = 16 channels: the value
+//           levels and the weight digits as token-major rows, read through
+//           ds_read_b64_tr_b8, which hands every lane the 8 tokens of one row or
+//           column.
 
 struct AttnLayout {
     int nw;             // wavefronts per workgroup
     int lut_k, lut_v;   // 8-byte tables (the same offset when K and V share one)
-    int qlimb;          // [32 channel groups][GP heads] x 16 B (three digit words)
+    int qtile;          // query digits: [HG][2 slices][16 rows][kRowT]
     int qscale, qsum;   // float [GP]
     int qmu;            // float [windows][GP]
     int waves;          // first wavefront region
     int wave_stride;
     int pk, pv;             // key / value byte-pair arrays: [position][64 lanes] x 2 B
-    int vtile;              // [64 tokens][kVRowT] level bytes of a 64-channel slice, over the pair arrays
+    int vtile;              // [64 tokens][kRowT] level bytes of a 64-channel slice, over the pair arrays
     int plimb;              // [HG][64 tokens][16] weight digits: byte 4 slot + digit (digit 3: zero)
+    int hdr;                // [64 tokens] float4: scale and offset of the key and of the value
     int total;
 };
 
@@ -176,28 +177,6 @@ __device__ __forceinline__ void dissue(uint32_t X, uint32_t Q, uint32_t mask8, i
 template <int N>
 __device__ __forceinline__ void dwait(uint32_t& r, uint64_t& e) {
     asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(r), "+v"(e) : "i"(N));
-}
-
-// The query digits of one group (16 bytes at LDS address a + off, off a
-// constant once unrolled), requested under the same rule: pending until a
-// dwaitq that follows it has run.
-typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void qissue(uint32_t a, int off, v4u& q) {
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(q) : "v"(a), "i"(off));
-}
-
-template <int N, int HG>
-__device__ __forceinline__ void dwaitq(uint32_t& r, uint64_t& e, v4u (&q)[HG]) {
-    if constexpr (HG == 1)
-        asm volatile("s_waitcnt lgkmcnt(%3)" : "+v"(r), "+v"(e), "+v"(q[0]) : "i"(N));
-    else
-        asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(r), "+v"(e), "+v"(q[0]), "+v"(q[1]) : "i"(N));
-}
-
-// The query digits alone (a single chain whose next reads stay in flight).
-template <int N>
-__device__ __forceinline__ void dwaitq1(v4u& q) {
-    asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(q) : "i"(N));
 }
 
 __device__ __forceinline__ uint32_t dfinish(uint32_t& X, uint32_t& Q, int p3, uint32_t r, uint64_t e) {
@@ -418,29 +397,12 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
     float* qscale = reinterpret_cast<float*>(smem + L.qscale);
     float* qsum = reinterpret_cast<float*>(smem + L.qsum);
     float* qmu = reinterpret_cast<float*>(smem + L.qmu);
-    uint8_t* qlimb = smem + L.qlimb;
+    uint8_t* qtile = smem + L.qtile;
     // wavefront g rotates query head g and forms its digits from the
     // registers (slots past G get zero digits); a workgroup with fewer
     // wavefronts than head slots loads the other heads here, the first head
     // of a wavefront needs no wait on the records
-    auto head_digits = [&](float r0, float r1, float qs, int g) {
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-            const int j = lane + 64 * hh;
-            int v = 0;
-            if (qs > 0.f) {
-                v = (int)rintf((hh ? r1 : r0) / qs);
-                v = max(-4194304, min(4194304, v));
-            }
-            int d0, d1, d2;
-            digits3(v, d0, d1, d2);
-            uint8_t* dst = qlimb + ((j / 4) * GP + g) * 16 + (j % 4);
-            dst[0] = (uint8_t)d0;
-            dst[4] = (uint8_t)d1;
-            dst[8] = (uint8_t)d2;
-            dst[12] = 0;
-        }
-    };
+    auto head_digits = [&](float r0, float r1, float qs, int g) { query_digits(qtile, g, lane, r0, r1, qs); };
     if (wave < G) {
         // consumed here, not where loaded: a wait there would hold back the
         // loads behind it
@@ -499,47 +461,109 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
             for (int g = 0; g < GP; ++g) sg[g] = half_sum_f32(sg[g]);
             if ((lane & 31) == 31 && wi < nwin) {
 #pragma unroll
-                for (int g = 0; g < GP; ++g) qmu[wi * GP + g] = g < G ? sg[g] : 0.f;
+                for (int g = 0; g < GP; ++g) qmu[wi * GP + g] = g < G ? sg[g] * a.scale_log2 : 0.f;
             }
         }
     }
     __syncthreads();
 
     // ---- per-wavefront state
-    uint8_t* wreg = smem + L.waves + wave * L.wave_stride;
     // lane l's column in a row of 64 pairs: lanes l and l + 32 share a dword,
     // so each half-wavefront reads 32 different banks
     const uint32_t col = (uint32_t)(4 * (lane & 31) + 2 * (lane >> 5));
     const uint32_t pk_lane = (uint32_t)(L.waves + wave * L.wave_stride + L.pk) + col;
     const uint32_t pv_lane = (uint32_t)(L.waves + wave * L.wave_stride + L.pv) + col;
-    uint8_t* vtile = wreg + L.vtile;     // overlays the pair arrays once both streams are decoded
-    uint8_t* plimb = wreg + L.plimb;
-    // P . v: lane l serves query-head slot l / 16 and channel l % 16 of each
-    // 16-channel block; its tr8 reads start at token row 8 (l / 16) +
-    // (l % 16) / 2 of a 32-token block, byte 8 (l % 2) of the row's block
-    const int slot = lane >> 4;
-    const uint32_t trow = (uint32_t)(8 * (lane >> 4) + ((lane & 15) >> 1));
-    const uint32_t a_lane = (uint32_t)(L.waves + wave * L.wave_stride + L.plimb) + trow * 16 + 8 * (lane & 1);
-    const uint32_t b_lane = (uint32_t)(L.waves + wave * L.wave_stride + L.vtile) + trow * kVRowT + 8 * (lane & 1);
+    const int slot = lane >> 4;      // query-head slot the lane serves
     const int pk3 = a.tk.p + 3, pv3 = a.tv.p + 3;
     const uint32_t mask8k = ((1u << a.tk.p) - 1u) << 3, mask8v = ((1u << a.tv.p) - 1u) << 3;
     const int64_t bh = (int64_t)b * a.Hkv + h;
 
-    // softmax state per query head (the same in every lane); the P . v sums
-    // of slot l / 16 of group hg, channel 64 s + 16 cb + l % 16 in acc[s][hg][cb]
-    float m_run[GP], l_part[GP], acco[GP], acc[2][HG][4];
+    const uint32_t wbase = (uint32_t)(L.waves + wave * L.wave_stride);
+    // With 16 wavefronts (128 VGPRs) the lane addresses of the score and value
+    // phases are formed where they are used, from a lane number the compiler
+    // cannot see through: hoisted, they would hold registers through the decode,
+    // where they run out.
+    auto lane_now = [&]() {
+        int l = lane;
+        if (WMAX > 12) asm volatile("" : "+v"(l));
+        return l;
+    };
+
+    // softmax state of slot l / 16 of each group of four query heads: the
+    // maximum the same in the 16 lanes, the sums in parts; the P . v sums of
+    // channel 64 s + 16 cb + l % 16 in acc[s][hg][cb]
+    float m_run[HG], l_run[HG], o_run[HG], qs_l[HG], qsum_l[HG], acc[2][HG][4];
 #pragma unroll
-    for (int g = 0; g < GP; ++g) {
-        m_run[g] = -INFINITY;
-        l_part[g] = 0.f;
-        acco[g] = 0.f;
-    }
-#pragma unroll
-    for (int hg = 0; hg < HG; ++hg)
+    for (int hg = 0; hg < HG; ++hg) {
+        m_run[hg] = -INFINITY;
+        l_run[hg] = 0.f;
+        o_run[hg] = 0.f;
+        qs_l[hg] = qscale[4 * hg + slot] * a.scale_log2;
+        qsum_l[hg] = qsum[4 * hg + slot] * a.scale_log2;
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb) acc[0][hg][cb] = acc[1][hg][cb] = 0.f;
+    }
     bool corrupt = false;
-    float l_tot[GP], o_tot[GP];
+
+    // ---- a decoded tile's scores and weights (in wavefront LDS): key levels
+    //      klev, headers, tokens from t_base; group hg's maximum in m
+    auto score_tile = [&](const uint32_t (&klev)[kD / 4], uint32_t hk, uint32_t hv, int t_base, SlotWeights (&sw)[HG]) {
+        const int ln = lane_now(), l16 = ln & 15, lq = ln >> 4;
+        const uint32_t row_lane = wbase + L.vtile + ln * kRowT;             // this lane's token row
+        const uint32_t operand = (uint32_t)(l16 * kRowT + 16 * lq);         // q . k operands
+        const uint32_t hdr = wbase + L.hdr;
+        *LDS_PTR(v4f, hdr + 16 * ln) = v4f{half_lo(hk), half_hi(hk), half_lo(hv), half_hi(hv)};
+        v4i d[HG][4];
+#pragma unroll
+        for (int hg = 0; hg < HG; ++hg)
+#pragma unroll
+            for (int tg = 0; tg < 4; ++tg) d[hg][tg] = v4i{0, 0, 0, 0};
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl) {
+            if (sl) wave_sync();   // the first slice's rows are no longer read
+            store_levels(row_lane, klev + 16 * sl);
+            wave_sync();           // rows are read by other lanes
+            qk_slice<HG>(wbase + L.vtile + operand, (uint32_t)(L.qtile + sl * kQTile) + operand, d);
+        }
+        float4 hd[4];
+#pragma unroll
+        for (int tg = 0; tg < 4; ++tg) {
+            const v4f v = *LDS_PTR(v4f, hdr + 16 * l16 + tg * 256);
+            hd[tg] = float4{v.x, v.y, v.z, v.w};
+        }
+        const int left = T - t_base - l16;
+        const bool whole = t_base + kTile <= T;
+        const float* qm = qmu + (t_base / DQ_MEAN_WINDOW - w0) * GP + lq;
+#pragma unroll
+        for (int hg = 0; hg < HG; ++hg) {
+            sw[hg] = slot_softmax(d[hg], hd, qs_l[hg], qsum_l[hg], qm[4 * hg], left, whole, m_run[hg]);
+            store_weights(wbase + L.plimb + 16 * l16 + 4 * lq + hg * (kTile * 16), sw[hg].w);
+        }
+    };
+    // ---- P . v over two slices of 64 channels with the weights of region wreg:
+    //      the lane's tr8 reads start at token row 8 (l / 16) + (l % 16) / 2 of a
+    //      32-token block, byte 8 (l % 2) of the row's block
+    auto value_tile = [&](const uint32_t (&vlev)[kD / 4], uint32_t wreg, auto&& add) {
+        const int ln = lane_now();
+        const uint32_t trow = (uint32_t)(8 * (ln >> 4) + ((ln & 15) >> 1)), half = 8 * (ln & 1);
+        const uint32_t row_lane = wbase + L.vtile + ln * kRowT, b_lane = wbase + L.vtile + trow * kRowT + half;
+        v4i pa[HG];
+#pragma unroll
+        for (int hg = 0; hg < HG; ++hg) pa[hg] = load_weights(wreg + L.plimb + trow * 16 + half + hg * (kTile * 16));
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl) {
+            wave_sync();           // the tile's previous rows are no longer read
+            store_levels(row_lane, vlev + 16 * sl);
+            wave_sync();
+            v4i vb[4];
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb) vb[cb] = load_values(b_lane + 16 * cb);
+#pragma unroll
+            for (int hg = 0; hg < HG; ++hg)
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb) add(sl, hg, cb, digit_sum(mfma64(pa[hg], vb[cb], v4i{0, 0, 0, 0})));
+        }
+    };
 
     if constexpr (SPLIT) {
         // One tile per pair of wavefronts: the even wavefront decodes the
@@ -552,8 +576,8 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
         // bounds the latency when one wavefront runs per SIMD).
         static_assert(HG == 1 && !FIXED, "split tiles: up to 4 query heads, entropy-coded records");
         const int tile = wave >> 1, role = wave & 1;
-        // [0, GP) weight scale of each slot, then maxima, sums, offset sums
-        float* kx = reinterpret_cast<float*>(smem + L.waves + (wave & ~1) * L.wave_stride + L.vtile);
+        // per slot: weight unit, maximum, sum, offset sum (after the key tile)
+        float* kx = reinterpret_cast<float*>(smem + L.waves + (wave & ~1) * L.wave_stride + L.vtile) + 4 * slot;
         uint32_t vlev[kD / 4];
         const int t_base = start + tile * kTile;
         const int t = t_base + lane;
@@ -567,11 +591,7 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
             asm volatile("" ::: "memory");
             uint32_t pq = pk_lane;
             const uint32_t pk_end = pk_lane + (uint32_t)((Ck - kPayloadOffset) * kPairRow);
-            v4i dk[3];
-#pragma unroll
-            for (int d = 0; d < 3; ++d) dk[d] = v4i{0, 0, 0, 0};
-            const uint32_t q_lane = (uint32_t)L.qlimb + (uint32_t)(lane & 3) * 16;
-            v4u qd;
+            uint32_t klev[kD / 4];
             dissue<0>(xk, pq, mask8k, 0, rr_, ee_);
 #pragma unroll
             for (int grp = 0; grp < kD / 4; ++grp) {
@@ -586,62 +606,18 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
                         pq += kWindow * kPairStep;
                         if (more) pq = min(pq, pk_end);
                     }
-                    if (u == 3) qissue(q_lane, (grp * GP) * 16, qd);
                     if (more) dissue<0>(xk, pq, mask8k, J1, rr_, ee_);
                 }
-                const uint32_t lk = pack4(kw[0], kw[1], kw[2], kw[3]);
-                // the digits were requested before the next step's two reads
-                if (grp + 1 < kD / 4) dwaitq1<2>(qd);
-                else dwaitq1<0>(qd);
-                dk[0] = mfma(qd.x, lk, dk[0]);
-                dk[1] = mfma(qd.y, lk, dk[1]);
-                dk[2] = mfma(qd.z, lk, dk[2]);
+                klev[grp] = pack4(kw[0], kw[1], kw[2], kw[3]);
+                asm volatile("" : "+v"(klev[grp]));
                 __builtin_amdgcn_sched_barrier(0);
             }
             corrupt |= valid && ((xk >> 3) != kRansL || pq > pk_end);
-            // scores (Eq. fold-key) and the tile's softmax; the value scale is
-            // folded into the weight (Eq. fold-value)
-            const float sk = half_lo(hk0), ok = half_hi(hk0);
-            const float sv = half_lo(hv0), ov = half_hi(hv0);
-            const float* qm = qmu + ((t / DQ_MEAN_WINDOW) - w0) * GP;
-            float score[4], tmax[4], pw[4], smax[4], lp[4], op[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float dot = combine(dk[0], dk[1], dk[2], r) * qscale[r];
-                score[r] = (valid && r < G) ? (sk * dot + ok * qsum[r] + qm[r]) * a.scale_log2 : -INFINITY;
-                tmax[r] = score[r];
-            }
-            wave_max4_f32(tmax);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float p = (score[r] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(score[r] - tmax[r]);
-                lp[r] = p;
-                op[r] = p * ov;
-                pw[r] = p * sv;
-                smax[r] = pw[r];
-            }
-            wave_max4_f32(smax);
-            uint32_t wd[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float inv = smax[r] > 0.f ? 4194304.0f * __builtin_amdgcn_rcpf(smax[r]) : 0.f;
-                const int pint = min(4194304, (int)rintf(pw[r] * inv));
-                int d0, d1, d2;
-                digits3(pint, d0, d1, d2);
-                wd[r] = ((uint32_t)d0 & 0xFFu) | (((uint32_t)d1 & 0xFFu) << 8) | (((uint32_t)d2 & 0xFFu) << 16);
-                l_tot[r] = wave_sum_f32(lp[r]);
-                o_tot[r] = wave_sum_f32(op[r]);
-            }
-            *reinterpret_cast<uint4*>(plimb + lane * 16) = uint4{wd[0], wd[1], wd[2], wd[3]};
-            if (lane == 0) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    kx[r] = smax[r] * (1.0f / 4194304.0f);
-                    kx[GP + r] = tmax[r];
-                    kx[2 * GP + r] = l_tot[r];
-                    kx[3 * GP + r] = o_tot[r];
-                }
-            }
+            SlotWeights sw[HG];
+            score_tile(klev, hk0, hv0, t_base, sw);
+            const float lt = row_sum16(sw[0].psum), ot = row_sum16(sw[0].osum);
+            wave_sync();           // the key rows are no longer read
+            if ((lane & 15) == 0) *reinterpret_cast<float4*>(kx) = float4{sw[0].wscale, m_run[0], lt, ot};
         } else if (tile < ntiles) {
             uint32_t xv = rv[1] << 3;
             build_pairs(rv, CWv, smem + pv_lane);
@@ -672,36 +648,12 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
         }
         __syncthreads();   // the weights and statistics of every pair are in LDS
         if (tile < ntiles && role == 1) {
-            // ---- P . v with the partner's weight digits, two slices of 64 channels
-            const uint32_t a_pair = a_lane - (uint32_t)L.wave_stride;
-            uint64_t pa[2];
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb) pa[kb] = lds_tr8(a_pair + kb * 32 * 16);
-            const float scale_l = pick4(kx, slot);
-#pragma unroll
-            for (int g = 0; g < GP; ++g) {
-                m_run[g] = kx[GP + g];
-                l_tot[g] = kx[2 * GP + g];
-                o_tot[g] = kx[3 * GP + g];
-            }
-#pragma unroll
-            for (int sl = 0; sl < 2; ++sl) {
-                if (sl) wave_sync();   // the first slice's value rows are no longer read
-#pragma unroll
-                for (int qq = 0; qq < 4; ++qq)
-                    *reinterpret_cast<uint4*>(vtile + lane * kVRowT + 16 * qq) =
-                        uint4{vlev[16 * sl + 4 * qq], vlev[16 * sl + 4 * qq + 1], vlev[16 * sl + 4 * qq + 2],
-                              vlev[16 * sl + 4 * qq + 3]};
-                wave_sync();
-#pragma unroll
-                for (int cb = 0; cb < 4; ++cb) {
-                    const uint64_t b0 = lds_tr8(b_lane + 16 * cb);
-                    const uint64_t b1 = lds_tr8(b_lane + 32 * kVRowT + 16 * cb);
-                    v4i d = mfma16(pa[0], b0, v4i{0, 0, 0, 0});
-                    d = mfma16(pa[1], b1, d);
-                    acc[sl][0][cb] = ((float)d[2] * 65536.0f + (float)d[1] * 256.0f + (float)d[0]) * scale_l;
-                }
-            }
+            // ---- P . v with the partner's weight digits
+            const float4 st = *reinterpret_cast<const float4*>(kx);
+            m_run[0] = st.y;
+            l_run[0] = st.z;
+            o_run[0] = st.w;
+            value_tile(vlev, wbase - (uint32_t)L.wave_stride, [&](int sl, int hg, int cb, float f) { acc[sl][hg][cb] = f * st.x; });
         }
     }
 
@@ -739,18 +691,8 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
         const uint32_t pv_end = pv_lane + (uint32_t)((Cv - kPayloadOffset) * kPairRow);
 
         // ---- keys and values decoded together: two independent rANS chains
-        //      per lane.  Key levels go straight into the q . k products; value
-        //      levels wait in registers until the softmax weights are known.
-        v4i dk[HG][3];
-#pragma unroll
-        for (int hg = 0; hg < HG; ++hg)
-#pragma unroll
-            for (int d = 0; d < 3; ++d) dk[hg][d] = v4i{0, 0, 0, 0};
-        uint32_t vlev[kD / 4];
-        // the query digits of group g are requested after the key step 4 g + 3,
-        // so that the wait for the value step 4 g + 3 covers them too
-        const uint32_t q_lane = (uint32_t)L.qlimb + (uint32_t)(lane & 3) * 16;
-        v4u qd[HG];
+        //      per lane, the levels packed in registers.
+        uint32_t klev[kD / 4], vlev[kD / 4];
         // step n of both chains: wait for its reads, finish it, request step
         // n + 1 (pointer windows advance and are clamped between n and n + 1;
         // a corrupt stream may run past its array, so clamp often enough
@@ -770,14 +712,10 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int grp = 0; grp < kD / 4; ++grp) {
-            uint32_t lk;
             if (FIXED) {
                 const int w = 1 + (FIXED ? grp / 4 : 0), sh = 8 * (grp % 4);
-                lk = spread2(__builtin_amdgcn_ubfe(ck[w], sh, 8));
+                klev[grp] = spread2(__builtin_amdgcn_ubfe(ck[w], sh, 8));
                 vlev[grp] = spread2(__builtin_amdgcn_ubfe(cv[w], sh, 8));
-#pragma unroll
-                for (int hg = 0; hg < HG; ++hg)
-                    qd[hg] = *reinterpret_cast<const v4u*>(qlimb + ((grp * GP) + hg * 4 + (lane & 3)) * 16);
             } else {
                 uint32_t kw[4], vw[4];
 #pragma unroll
@@ -790,16 +728,10 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
                         pq += kWindow * kPairStep;
                         if (more) pq = min(pq, pk_end);
                     }
-                    if (u == 3) {
-                        qissue(q_lane, (grp * GP) * 16, qd[0]);
-                        if constexpr (HG == 2) qissue(q_lane, (grp * GP + 4) * 16, qd[1]);
-                    }
                     if (more) dissue<0>(xk, pq, mask8k, J1, rk_, ek_);
-                    // the key reads of step n + 1 follow (and the digits at u = 3,
-                    // before them: this wait covers those too)
-                    if (u < 3) dwait<2>(rv_, ev_);
-                    else if (more) dwaitq<2>(rv_, ev_, qd);
-                    else dwaitq<0>(rv_, ev_, qd);
+                    // the key reads of step n + 1 follow
+                    if (more) dwait<2>(rv_, ev_);
+                    else dwait<0>(rv_, ev_);
                     vw[u] = dfinish(xv, pv, pv3, rv_, ev_);
                     if (J1 == 0) {
                         pv += kWindow * kPairStep;
@@ -807,17 +739,11 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
                     }
                     if (more) dissue<LUTV>(xv, pv, mask8v, J1, rv_, ev_);
                 }
-                lk = pack4(kw[0], kw[1], kw[2], kw[3]);
+                klev[grp] = pack4(kw[0], kw[1], kw[2], kw[3]);
                 vlev[grp] = pack4(vw[0], vw[1], vw[2], vw[3]);
-            }
-            // pack now: left alone, the packing sinks to the value pass and the
-            // four table words stay live until then
-            asm volatile("" : "+v"(vlev[grp]));
-#pragma unroll
-            for (int hg = 0; hg < HG; ++hg) {
-                dk[hg][0] = mfma(qd[hg].x, lk, dk[hg][0]);
-                dk[hg][1] = mfma(qd[hg].y, lk, dk[hg][1]);
-                dk[hg][2] = mfma(qd[hg].z, lk, dk[hg][2]);
+                // pack now: left alone, the packing sinks to where the levels
+                // are stored and the four table words stay live until then
+                asm volatile("" : "+v"(klev[grp]), "+v"(vlev[grp]));
             }
             // keep the scheduler inside one group: live ranges stay short
             __builtin_amdgcn_sched_barrier(0);
@@ -829,73 +755,17 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
         }
 
         __builtin_amdgcn_s_setprio(0);
-        // ---- scores (Eq. fold-key) and online softmax; the value scale is
-        //      folded into the weight (Eq. fold-value)
-        const float sk = half_lo(hk0), ok = half_hi(hk0);
-        const float sv = half_lo(hv0), ov = half_hi(hv0);
-        const float* qm = qmu + ((t / DQ_MEAN_WINDOW) - w0) * GP;
-        float pscale[GP], corrs[GP];
-        int pint[GP];
-        // four query heads at a time, their tile maxima reduced together
+        // ---- scores (Eq. fold-key), online softmax, weights (Eq. fold-value)
+        SlotWeights sw[HG];
+        score_tile(klev, hk0, hv0, t_base, sw);
 #pragma unroll
         for (int hg = 0; hg < HG; ++hg) {
-            float score[4], tmax[4], pw[4], smax[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int g = 4 * hg + r;
-                const float dot = combine(dk[hg][0], dk[hg][1], dk[hg][2], r) * qscale[g];
-                score[r] = (valid && g < G) ? (sk * dot + ok * qsum[g] + qm[g]) * a.scale_log2 : -INFINITY;
-                tmax[r] = score[r];
-            }
-            wave_max4_f32(tmax);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int g = 4 * hg + r;
-                const float mn = fmaxf(m_run[g], tmax[r]);
-                // v_exp_f32 directly: arguments are <= 0 and results that would
-                // be denormal may flush to zero
-                const float corr = (m_run[g] == -INFINITY || mn == -INFINITY) ? (m_run[g] == mn ? 1.f : 0.f)
-                                                                               : __builtin_amdgcn_exp2f(m_run[g] - mn);
-                const float p = (score[r] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(score[r] - mn);
-                l_part[g] = l_part[g] * corr + p;
-                acco[g] = acco[g] * corr + p * ov;
-                corrs[g] = corr;
-                m_run[g] = mn;
-                pw[r] = p * sv;                          // >= 0: scales are non-negative
-                smax[r] = pw[r];
-            }
-            wave_max4_f32(smax);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int g = 4 * hg + r;
-                pscale[g] = smax[r] * (1.0f / 4194304.0f);
-                // 22-bit fixed point of pw relative to the tile maximum
-                const float inv = smax[r] > 0.f ? 4194304.0f * __builtin_amdgcn_rcpf(smax[r]) : 0.f;
-                pint[g] = min(4194304, (int)rintf(pw[r] * inv));
-            }
-        }
-        // weight digits -> LDS, one 16-byte token row per slot group: byte
-        // 4 r + d holds digit d of slot r (byte 4 r + 3 stays zero)
-#pragma unroll
-        for (int hg = 0; hg < HG; ++hg) {
-            uint32_t w[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                int d0, d1, d2;
-                digits3(pint[4 * hg + r], d0, d1, d2);
-                w[r] = ((uint32_t)d0 & 0xFFu) | (((uint32_t)d1 & 0xFFu) << 8) | (((uint32_t)d2 & 0xFFu) << 16);
-            }
-            *reinterpret_cast<uint4*>(plimb + hg * (kTile * 16) + lane * 16) = uint4{w[0], w[1], w[2], w[3]};
-        }
-        float scale_l[HG];
-#pragma unroll
-        for (int hg = 0; hg < HG; ++hg) {
-            const float corr_l = pick4(corrs + 4 * hg, slot);
-            scale_l[hg] = pick4(pscale + 4 * hg, slot);
+            l_run[hg] = l_run[hg] * sw[hg].corr + sw[hg].psum;
+            o_run[hg] = o_run[hg] * sw[hg].corr + sw[hg].osum;
 #pragma unroll
             for (int cb = 0; cb < 4; ++cb) {
-                acc[0][hg][cb] *= corr_l;
-                acc[1][hg][cb] *= corr_l;
+                acc[0][hg][cb] *= sw[hg].corr;
+                acc[1][hg][cb] *= sw[hg].corr;
             }
         }
 
@@ -905,35 +775,8 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
             load_record(rv, a.vrec, tok, CWv);
         }
 
-        // ---- P . v over two slices of 64 channels
-        wave_sync();   // the weight rows (and, below, the value rows) are read by other lanes
-        uint64_t pa[HG][2];
-#pragma unroll
-        for (int hg = 0; hg < HG; ++hg)
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb) pa[hg][kb] = lds_tr8(a_lane + hg * (kTile * 16) + kb * 32 * 16);
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            if (s) wave_sync();   // the first slice's value rows are no longer read
-            // the lane's 64 levels of the slice: 4 x 16 bytes of its token row
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                *reinterpret_cast<uint4*>(vtile + lane * kVRowT + 16 * q) =
-                    uint4{vlev[16 * s + 4 * q], vlev[16 * s + 4 * q + 1], vlev[16 * s + 4 * q + 2],
-                          vlev[16 * s + 4 * q + 3]};
-            wave_sync();
-#pragma unroll
-            for (int cb = 0; cb < 4; ++cb) {
-                const uint64_t b0 = lds_tr8(b_lane + 16 * cb);
-                const uint64_t b1 = lds_tr8(b_lane + 32 * kVRowT + 16 * cb);
-#pragma unroll
-                for (int hg = 0; hg < HG; ++hg) {
-                    v4i d = mfma16(pa[hg][0], b0, v4i{0, 0, 0, 0});
-                    d = mfma16(pa[hg][1], b1, d);
-                    acc[s][hg][cb] += ((float)d[2] * 65536.0f + (float)d[1] * 256.0f + (float)d[0]) * scale_l[hg];
-                }
-            }
-        }
+        wave_sync();   // the weight rows are read by other lanes
+        value_tile(vlev, wbase, [&](int sl, int hg, int cb, float f) { acc[sl][hg][cb] += f * sw[hg].wscale; });
         wave_sync();   // the next tile rewrites the pair arrays over the value tile
     }
     if (__any(corrupt) && lane == 0 && a.status) atomicOr(a.status, DQ_STATUS_CORRUPT);
@@ -943,9 +786,9 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
     //      statistics the value wavefront has read from its partner)
     if constexpr (!SPLIT) {
 #pragma unroll
-        for (int g = 0; g < GP; ++g) {
-            l_tot[g] = wave_sum_f32(l_part[g]);
-            o_tot[g] = wave_sum_f32(acco[g]);
+        for (int hg = 0; hg < HG; ++hg) {
+            l_run[hg] = row_sum16(l_run[hg]);
+            o_run[hg] = row_sum16(o_run[hg]);
         }
     }
     __syncthreads();   // every wavefront is done with LDS
@@ -955,15 +798,12 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
     if (!SPLIT || ((wave & 1) && (wave >> 1) < ntiles)) {
         const int ws = SPLIT ? wave >> 1 : wave;
 #pragma unroll
-        for (int g = 0; g < GP; ++g) {
-            if (lane == 0) {
-                mw[ws * GP + g] = m_run[g];
-                lw[ws * GP + g] = l_tot[g];
-            }
-        }
-#pragma unroll
         for (int hg = 0; hg < HG; ++hg) {
-            const float o_l = pick4(o_tot + 4 * hg, slot);
+            if ((lane & 15) == 0) {
+                mw[ws * GP + 4 * hg + slot] = m_run[hg];
+                lw[ws * GP + 4 * hg + slot] = l_run[hg];
+            }
+            const float o_l = o_run[hg];
             float* row = aw + (ws * GP + 4 * hg + slot) * kD + (lane & 15);
 #pragma unroll
             for (int cb = 0; cb < 4; ++cb) {
@@ -1555,8 +1395,8 @@ AttnLayout attn_layout(int pk, int pvb, int Ck, int Cv, int G, bool shared_lut, 
         L.lut_v = (int)kLutVOffset;
         off = (int)kLutVOffset + align16(8 << pvb);
     }
-    L.qlimb = off;
-    off += align16((kD / 4) * GP * 16);
+    L.qtile = off;
+    off += HG * 2 * kQTile;
     L.qscale = off;
     off += align16(GP * 4);
     L.qsum = off;
@@ -1568,9 +1408,9 @@ AttnLayout attn_layout(int pk, int pvb, int Ck, int Cv, int G, bool shared_lut, 
     L.pk = w;                                      // key pairs, then value pairs
     L.pv = w + align16((Ck - kPayloadOffset) * kPairRow);
     L.vtile = w;                                   // reuses the pair arrays
-    L.plimb = w + align16(kTile * kVRowT);         // so do the weight digits
-    w = std::max(L.pv + align16((Cv - kPayloadOffset) * kPairRow),
-                 L.plimb + align16(HG * kTile * 16));
+    L.plimb = w + align16(kTile * kRowT);         // so do the weight digits
+    L.hdr = L.plimb + align16(HG * kTile * 16);
+    w = std::max(L.pv + align16((Cv - kPayloadOffset) * kPairRow), L.hdr + kTile * 16);
     L.wave_stride = w;
     int nw = (kMaxLds - kPairSlack - off) / w;
     if (nw > max_waves(HG, rw)) nw = max_waves(HG, rw);
