@@ -24,27 +24,14 @@ __device__ __forceinline__ uint32_t pack4(uint32_t e0, uint32_t e1, uint32_t e2,
     return lo | hi;
 }
 
-// 4x4 byte transpose inside each lane quad: lane 4q+i holds row i on input
-// and column i on output.
-__device__ __forceinline__ uint32_t quad_transpose(uint32_t w, uint32_t sel1, uint32_t sel2) {
-    const uint32_t p1 = (uint32_t)__builtin_amdgcn_mov_dpp((int)w, 0xB1, 0xF, 0xF, false);
-    const uint32_t r = __builtin_amdgcn_perm(p1, w, sel1);
-    const uint32_t p2 = (uint32_t)__builtin_amdgcn_mov_dpp((int)r, 0x4E, 0xF, 0xF, false);
-    return __builtin_amdgcn_perm(p2, r, sel2);
-}
-
-// Three signed 8-bit digits of v in [-2^22, 2^22]: v = d2 2^16 + d1 2^8 + d0.
-__device__ __forceinline__ void digits3(int v, int& d0, int& d1, int& d2) {
-    d0 = ((v + 128) & 255) - 128;
-    const int v1 = (v - d0) >> 8;
-    d1 = ((v1 + 128) & 255) - 128;
-    d2 = (v1 - d1) >> 8;
-}
+// Fixed-point range of the query and of the softmax weights: three signed 8-bit
+// digits reach 127 (2^16 + 2^8 + 1) = 8355711; what rounding adds stays below.
+constexpr float kDigitMax = 8355000.0f;
 
 // Rotates one query head held as channels l and l + 64 in lane l
 // (unnormalized Hadamard, stages h = 1, 2, ..., 64 in the order of the
 // definition) and stores it into qt[g][128] fp32, with qscale[g] = max |q_rot| /
-// 2^22 and qsum[g] = sum of q_rot.  rotate = 0: keys arrive in the rotated
+// kDigitMax and qsum[g] = sum of q_rot.  rotate = 0: keys arrive in the rotated
 // basis, and so does the query: it is taken as it is.  v0, v1 end as the
 // rotated channels; returns qscale[g].
 __device__ __forceinline__ float rotate_query_head(float& v0, float& v1, int g, int lane, float* qt, float* qscale,
@@ -59,7 +46,7 @@ __device__ __forceinline__ float rotate_query_head(float& v0, float& v1, int g, 
     qt[g * 128 + lane + 64] = v1;
     const float mx = wave_max_f32(fmaxf(fabsf(v0), fabsf(v1)));
     const float sm = wave_sum_f32(v0 + v1);
-    const float qs = mx * (1.0f / 4194304.0f);
+    const float qs = mx * (1.0f / kDigitMax);
     if (lane == 0) {
         qscale[g] = qs;
         qsum[g] = sm;
@@ -87,17 +74,7 @@ __device__ __forceinline__ void rotate_query_heads(const uint16_t* q, int nh, in
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ v4i mfma(uint32_t a, uint32_t b, v4i c) {
-    return __builtin_amdgcn_mfma_i32_4x4x4i8((int)a, (int)b, c, 0, 0, 0);
-}
-
-// v_mfma_i32_16x16x32_i8: lane l gives row l % 16 and K = 8 (l / 16) .. + 7
-// of A, the same K of column l % 16 of B, and receives rows 4 (l / 16) .. + 3
-// of column l % 16.
-__device__ __forceinline__ v4i mfma16(uint64_t a, uint64_t b, v4i c) {
-    return __builtin_amdgcn_mfma_i32_16x16x32_i8((long)a, (long)b, c, 0, 0, 0);
-}
+typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 
 // v_mfma_i32_16x16x64_i8: 16 bytes of K per lane; A and B are loaded alike, so
 // which K a byte stands for does not matter.
@@ -115,15 +92,6 @@ __device__ __forceinline__ uint64_t lds_tr8(uint32_t off) {
     return (uint64_t)(uint32_t)r.x | ((uint64_t)(uint32_t)r.y << 32);
 }
 
-// v[slot] for slot in 0..3 (v held in registers, slot per lane).
-__device__ __forceinline__ float pick4(const float* v, int slot) {
-    return slot == 0 ? v[0] : slot == 1 ? v[1] : slot == 2 ? v[2] : v[3];
-}
-
-__device__ __forceinline__ float combine(const v4i& d0, const v4i& d1, const v4i& d2, int r) {
-    return (float)d2[r] * 65536.0f + (float)d1[r] * 256.0f + (float)d0[r];
-}
-
 // ---- a 64-token tile's scores, softmax and weighted values
 //
 // Work layout.  Lane l serves query-head slot l / 16 of a group of four and
@@ -135,27 +103,30 @@ __device__ __forceinline__ float combine(const v4i& d0, const v4i& d1, const v4i
 // (With v_mfma_i32_4x4x4_16b_i8 on the levels as they appear, a lane held all
 // four slots of its token: 96 products per tile instead of 8, four times the
 // reductions, and 32 reads of query digits.)
-constexpr int kRowT = 80;                 // bytes per row of a level or query-digit tile (64 channels + pad)
-constexpr int kQTile = 16 * kRowT;        // query digits of a group's 16 rows, one 64-channel slice
+constexpr int kRowT = 80;                 // bytes per row of a level tile (64 channels + pad)
+constexpr int kQRow = 64;                 // bytes per row of a query-digit tile
+constexpr int kQTile = 16 * kQRow;        // query digits of a group's 16 rows, one 64-channel slice
 constexpr int kColGroup = 16 * kRowT;     // 16 token rows of a level tile
 
 // Digits of rotated query head g (values r0, r1 of channels lane, lane + 64, unit
-// qs) into the tiles [group][slice][row 4 slot + digit][kRowT].
+// qs) into the tiles [group][slice][row 4 slot + digit][kQRow].  The 16-byte
+// pieces of a row are exchanged (piece ^ slot), so that the 16 rows' pieces that
+// are read together fall in different banks without padding.
 __device__ __forceinline__ void query_digits(uint8_t* tiles, int g, int lane, float r0, float r1, float qs) {
 #pragma unroll
     for (int sl = 0; sl < 2; ++sl) {
         int v = 0;
         if (qs > 0.f) {
             v = (int)rintf((sl ? r1 : r0) / qs);
-            v = max(-4194304, min(4194304, v));
+            v = max(-8355711, min(8355711, v));
         }
         // adding 128 to every byte and flipping its top bit leaves the signed digits
         const uint32_t w = ((uint32_t)v + 0x00808080u) ^ 0x00808080u;
-        uint8_t* dst = tiles + ((g / 4) * 2 + sl) * kQTile + 4 * (g % 4) * kRowT + lane;
+        uint8_t* dst = tiles + ((g / 4) * 2 + sl) * kQTile + 4 * (g % 4) * kQRow + (lane ^ (16 * (g % 4)));
         dst[0] = (uint8_t)w;
-        dst[kRowT] = (uint8_t)(w >> 8);
-        dst[2 * kRowT] = (uint8_t)(w >> 16);
-        dst[3 * kRowT] = 0;
+        dst[kQRow] = (uint8_t)(w >> 8);
+        dst[2 * kQRow] = (uint8_t)(w >> 16);
+        dst[3 * kQRow] = 0;
     }
 }
 
@@ -167,9 +138,15 @@ __device__ __forceinline__ void store_levels(uint32_t row, const uint32_t* lev) 
             v4i{(int)lev[4 * q], (int)lev[4 * q + 1], (int)lev[4 * q + 2], (int)lev[4 * q + 3]};
 }
 
-// d[hg][tg] += query digits . levels over one 64-channel slice: col is the
-// lane's operand in the level tile (row l % 16, bytes 16 (l / 16) ..), qa the
-// same in the slice's query tile of group 0.
+// The lane's operands: bytes 16 (l / 16) .. of row l % 16, of a level tile and of
+// a query tile.
+__device__ __forceinline__ uint32_t level_operand(int lane) { return (lane & 15) * kRowT + 16 * (lane >> 4); }
+__device__ __forceinline__ uint32_t query_operand(int lane) {
+    return (lane & 15) * kQRow + 16 * ((lane >> 4) ^ ((lane >> 2) & 3));
+}
+
+// d[hg][tg] += query digits . levels over one 64-channel slice (col, qa: the
+// lane's operands in the level tile and in the slice's query tile of group 0).
 template <int HG>
 __device__ __forceinline__ void qk_slice(uint32_t col, uint32_t qa, v4i (&d)[HG][4]) {
     v4i b[4], a[HG];
@@ -209,32 +186,44 @@ constexpr float kLowest = -3.4028234663852886e38f;
 
 // Softmax of the lane's four tokens for its slot (Eq. fold-key), the value scale
 // folded into the weights (Eq. fold-value).
-//   d: digit sums; h[tg]: (s, o) of the token's key and value; qs, qsum, qm: the
-//   slot's digit unit, query sum and q . mu, all times softmax_scale log2(e);
+//   d: digit sums; h[tg]: scale and offset of the token's key and value, in fp32
+//   or as the records' first words; qs, qsum, qm: the slot's digit unit, query sum and
+//   q . mu; scale: softmax_scale log2(e) > 0 (its sign is in the query's terms);
 //   left: tokens from l % 16 to the sequence's end (token 16 tg is live while
-//   16 tg < left); m: running maximum.
+//   16 tg < left); m: running maximum, scaled.  The scale enters in the
+//   exponent's one fused multiply-add, so the unscaled score is rounded once.
 // Returns the correction of what was summed before; psum, osum: the lane's
-// parts of sum p and sum p o_v; w: the weights' digits (22-bit fixed point
-// relative to the tile's largest), wscale their unit.
+// parts of sum p and sum p o_v; w: the weights' digits (fixed point relative to
+// the tile's largest), wscale their unit.
 struct SlotWeights {
     float corr, psum, osum, wscale;
     uint32_t w[4];
 };
-__device__ __forceinline__ SlotWeights slot_softmax(const v4i (&d)[4], const float4 (&h)[4], float qs, float qsum,
-                                                    float qm, int left, bool whole, float& m) {
+__device__ __forceinline__ float key_scale(const float4& h) { return h.x; }
+__device__ __forceinline__ float key_offset(const float4& h) { return h.y; }
+__device__ __forceinline__ float value_scale(const float4& h) { return h.z; }
+__device__ __forceinline__ float value_offset(const float4& h) { return h.w; }
+__device__ __forceinline__ float key_scale(const uint2& h) { return half_lo(h.x); }
+__device__ __forceinline__ float key_offset(const uint2& h) { return half_hi(h.x); }
+__device__ __forceinline__ float value_scale(const uint2& h) { return half_lo(h.y); }
+__device__ __forceinline__ float value_offset(const uint2& h) { return half_hi(h.y); }
+
+template <typename H>
+__device__ __forceinline__ SlotWeights slot_softmax(const v4i (&d)[4], const H (&h)[4], float qs, float qsum,
+                                                    float qm, float scale, int left, bool whole, float& m) {
     float s[4];
 #pragma unroll
     for (int tg = 0; tg < 4; ++tg) {
         // |digit sum| <= 128 127 63 < 2^20: the lower two meet exactly in int32
         const float dot = (float)d[tg][2] * 65536.0f + (float)((d[tg][1] << 8) + d[tg][0]);
-        s[tg] = h[tg].x * (dot * qs) + (h[tg].y * qsum + qm);
+        s[tg] = key_scale(h[tg]) * (dot * qs) + (key_offset(h[tg]) * qsum + qm);
     }
     if (!whole) {
 #pragma unroll
         for (int tg = 0; tg < 4; ++tg) s[tg] = 16 * tg < left ? s[tg] : -INFINITY;
     }
     SlotWeights r;
-    const float mn = fmaxf(m, row_max16(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]))));
+    const float mn = fmaxf(m, scale * row_max16(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]))));
     const float base = fmaxf(mn, kLowest);           // -inf - base stays -inf
     // v_exp_f32 directly: arguments are <= 0 and results that would be denormal
     // may flush to zero
@@ -243,18 +232,20 @@ __device__ __forceinline__ SlotWeights slot_softmax(const v4i (&d)[4], const flo
     float p[4], pw[4];
 #pragma unroll
     for (int tg = 0; tg < 4; ++tg) {
-        p[tg] = __builtin_amdgcn_exp2f(s[tg] - base);
-        pw[tg] = p[tg] * h[tg].z;                    // >= 0: scales are non-negative
+        p[tg] = __builtin_amdgcn_exp2f(s[tg] * scale - base);
+        pw[tg] = p[tg] * value_scale(h[tg]);           // >= 0: scales are non-negative
     }
     r.psum = (p[0] + p[1]) + (p[2] + p[3]);
-    r.osum = (p[0] * h[0].w + p[1] * h[1].w) + (p[2] * h[2].w + p[3] * h[3].w);
+    r.osum = 0.f;
+#pragma unroll
+    for (int tg = 0; tg < 4; ++tg) r.osum = value_offset(h[tg]) * p[tg] + r.osum;
     const float top = fmaxf(row_max16(fmaxf(fmaxf(pw[0], pw[1]), fmaxf(pw[2], pw[3]))), 1e-30f);
-    const float inv = 4194304.0f * __builtin_amdgcn_rcpf(top);
-    r.wscale = top * (1.0f / 4194304.0f);
+    const float inv = kDigitMax * __builtin_amdgcn_rcpf(top);
+    r.wscale = top * (1.0f / kDigitMax);
 #pragma unroll
     for (int tg = 0; tg < 4; ++tg) {
-        // 1.5 2^23 + v has v in its low bits, rounded to nearest even
-        const uint32_t v = __float_as_uint(pw[tg] * inv + 12582912.0f) - 0x4B400000u;
+        // 2^23 + v has v in its low bits, rounded to nearest even
+        const uint32_t v = __float_as_uint(pw[tg] * inv + 8388608.0f) - 0x4B000000u;
         r.w[tg] = (v + 0x00808080u) ^ 0x00808080u;
     }
     return r;

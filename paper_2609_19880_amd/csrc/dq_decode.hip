@@ -17,6 +17,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 
 #include "dq_attn.h"
@@ -87,7 +88,7 @@ __global__ void decode_symbols_kernel(TabArgs ta, const uint8_t* __restrict__ re
 // Contractions (Eq. fold-key / fold-value) run on the matrix cores.  Decoded
 // levels are bytes and enter as they are; the rotated query and the softmax
 // weights (with the value scale folded in) enter as three signed 8-bit digits
-// of a 22-bit fixed-point value, accumulated exactly in int32 and recombined
+// of a fixed-point value (kDigitMax), accumulated exactly in int32 and recombined
 // in fp32.
 //   q . k:  v_mfma_i32_16x16x64_i8, rows = (query-head slot, digit), K = 64
 //           channels, columns = 16 tokens.  The levels of both streams wait in
@@ -104,7 +105,7 @@ __global__ void decode_symbols_kernel(TabArgs ta, const uint8_t* __restrict__ re
 struct AttnLayout {
     int nw;             // wavefronts per workgroup
     int lut_k, lut_v;   // 8-byte tables (the same offset when K and V share one)
-    int qtile;          // query digits: [HG][2 slices][16 rows][kRowT]
+    int qtile;          // query digits: [HG][2 slices][16 rows][kQRow]
     int qscale, qsum;   // float [GP]
     int qmu;            // float [windows][GP]
     int waves;          // first wavefront region
@@ -133,7 +134,8 @@ struct AttnArgs {
     const uint16_t* kms;
     const uint8_t* vrec;
     const int32_t* seq_lens;
-    float scale_log2;            // softmax_scale * log2(e) / d
+    float scale_log2;            // |softmax_scale| * log2(e) / d, at least 1e-37
+    float q_sign;                // the sign of softmax_scale
     int32_t* ws_hdr;             // [0] chunk, [1] chunk count NC, [2] residual slots written,
                                  // [3] 1 if the merge rotates the output back (values rotated online)
     int rot_q, rot_out;          // keys / values rotated online (tables not prerotated)
@@ -461,7 +463,7 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
             for (int g = 0; g < GP; ++g) sg[g] = half_sum_f32(sg[g]);
             if ((lane & 31) == 31 && wi < nwin) {
 #pragma unroll
-                for (int g = 0; g < GP; ++g) qmu[wi * GP + g] = g < G ? sg[g] * a.scale_log2 : 0.f;
+                for (int g = 0; g < GP; ++g) qmu[wi * GP + g] = g < G ? sg[g] * a.q_sign : 0.f;
             }
         }
     }
@@ -498,8 +500,8 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
         m_run[hg] = -INFINITY;
         l_run[hg] = 0.f;
         o_run[hg] = 0.f;
-        qs_l[hg] = qscale[4 * hg + slot] * a.scale_log2;
-        qsum_l[hg] = qsum[4 * hg + slot] * a.scale_log2;
+        qs_l[hg] = qscale[4 * hg + slot] * a.q_sign;
+        qsum_l[hg] = qsum[4 * hg + slot] * a.q_sign;
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb) acc[0][hg][cb] = acc[1][hg][cb] = 0.f;
     }
@@ -510,7 +512,6 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
     auto score_tile = [&](const uint32_t (&klev)[kD / 4], uint32_t hk, uint32_t hv, int t_base, SlotWeights (&sw)[HG]) {
         const int ln = lane_now(), l16 = ln & 15, lq = ln >> 4;
         const uint32_t row_lane = wbase + L.vtile + ln * kRowT;             // this lane's token row
-        const uint32_t operand = (uint32_t)(l16 * kRowT + 16 * lq);         // q . k operands
         const uint32_t hdr = wbase + L.hdr;
         *LDS_PTR(v4f, hdr + 16 * ln) = v4f{half_lo(hk), half_hi(hk), half_lo(hv), half_hi(hv)};
         v4i d[HG][4];
@@ -523,7 +524,8 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
             if (sl) wave_sync();   // the first slice's rows are no longer read
             store_levels(row_lane, klev + 16 * sl);
             wave_sync();           // rows are read by other lanes
-            qk_slice<HG>(wbase + L.vtile + operand, (uint32_t)(L.qtile + sl * kQTile) + operand, d);
+            qk_slice<HG>(wbase + L.vtile + level_operand(ln), (uint32_t)(L.qtile + sl * kQTile) + query_operand(ln),
+                         d);
         }
         float4 hd[4];
 #pragma unroll
@@ -536,7 +538,7 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
         const float* qm = qmu + (t_base / DQ_MEAN_WINDOW - w0) * GP + lq;
 #pragma unroll
         for (int hg = 0; hg < HG; ++hg) {
-            sw[hg] = slot_softmax(d[hg], hd, qs_l[hg], qsum_l[hg], qm[4 * hg], left, whole, m_run[hg]);
+            sw[hg] = slot_softmax(d[hg], hd, qs_l[hg], qsum_l[hg], qm[4 * hg], a.scale_log2, left, whole, m_run[hg]);
             store_weights(wbase + L.plimb + 16 * l16 + 4 * lq + hg * (kTile * 16), sw[hg].w);
         }
     };
@@ -1557,7 +1559,8 @@ int launch_attention_partial(const dq_tables* tk, const dq_tables* tv, const Pag
     a.rot_q = tk->cfg.prerotated ? 0 : 1;
     a.rot_out = tv->cfg.prerotated ? 0 : 1;
     // the rotated query and key meet with a factor d (H H = d I)
-    a.scale_log2 = scale * 1.4426950408889634f / (a.rot_q ? (float)kD : 1.0f);
+    a.scale_log2 = std::max(std::fabs(scale) * 1.4426950408889634f / (a.rot_q ? (float)kD : 1.0f), 1e-37f);
+    a.q_sign = scale < 0.f ? -1.f : 1.f;
     const int64_t slots = ws_slots_used > 0 ? ws_slots_used : plan.slots_max;
     a.ws_hdr = static_cast<int32_t*>(ws);
     a.ws_acc = reinterpret_cast<float*>(static_cast<uint8_t*>(ws) + kWsHeader);
@@ -1599,7 +1602,8 @@ int launch_attention_fixed_partial(const Pages& pg, const uint16_t* q, int32_t B
     a.vrec = vrec;
     a.seq_lens = seq_lens;
     a.rot_q = a.rot_out = 1;
-    a.scale_log2 = scale * 1.4426950408889634f / (float)kD;
+    a.scale_log2 = std::max(std::fabs(scale) * 1.4426950408889634f / (float)kD, 1e-37f);
+    a.q_sign = scale < 0.f ? -1.f : 1.f;
     a.ws_hdr = static_cast<int32_t*>(ws);
     a.ws_acc = reinterpret_cast<float*>(static_cast<uint8_t*>(ws) + kWsHeader);
     a.ws_m = a.ws_acc + plan.slots_max * kD;

@@ -7,12 +7,13 @@
 // takes 64-token tiles, one token per lane, and runs the token's key and
 // value streams as two interleaved rANS chains (Alg. 2).  After every 128
 // steps (one KV head) the head's G query heads get their q . k products
-// (Eq. fold-key, on the matrix cores as the levels appear), the online
-// softmax update and P . v (Eq. fold-value, on the 16x16x32 matrix cores);
+// (Eq. fold-key, on the 16x16x64 matrix cores, half of the head's channels at a
+// time), the online softmax update and P . v (Eq. fold-value, the same product);
 // the chains then continue into the next head with their state.  All query
 // heads' accumulators live in the wavefront: per KV head and group of 4
 // query-head slots (one group for up to 4 query heads per KV head, two for up
-// to 8), lane l holds slot l / 16 of the group for 8 of the 128 channels.
+// to 8), lane l holds slot l / 16 of the group for 8 of the 128 channels, and
+// the softmax state of head i in lane i of the row of 16 lanes.
 //
 // Record bytes.  Records (C bytes in S-byte slots, S a multiple of 16) are
 // stored per 64-token tile with 8-byte chunks outermost: chunk c of the tile's
@@ -35,6 +36,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "dq_attn.h"
 
@@ -44,7 +46,6 @@ namespace {
 constexpr int kD = 128;
 constexpr int kTile = 64;
 constexpr int kVSlice = 64;
-constexpr int kVRowT = 80;               // bytes per token row of the value tile (64 channels + pad)
 constexpr int kMaxLds = 160 * 1024;
 // wavefronts per workgroup at most: 12 with up to 4 query heads per KV head
 // (168 VGPRs), 8 with up to 8 (the accumulators of 64 query heads take 128)
@@ -60,14 +61,15 @@ constexpr int kGroups = kD / 4;           // 4-step groups per head
 struct TokLayout {
     int nw;
     int lut_k, lut_v;   // 8-byte tables (the same offset when K and V share one)
-    int qlimb;          // [H_kv][32 groups][4 HG slots] x 16 B (three digit words)
+    int qtile;          // query digits: [H_kv][HG][2 slices][16 rows][kQRow]
     int qscale, qsum;   // float [H_q]
     int qmu;            // float [windows][H_q]
     int waves;          // first wavefront region
     int wave_stride;
     int ring_k, ring_v; // per wavefront
-    int vtile;          // [64 tokens][kVRowT]: levels of a 64-channel slice
+    int vtile;          // [64 tokens][kRowT]: levels of a 64-channel slice, keys then values
     int plimb;          // [HG][64 tokens][16]: weight digits, byte 4 slot + digit (digit 3 zero)
+    int hdr;            // [64 tokens]: the first words of the key and value records (fp16 scale, offset)
     int total;
 };
 
@@ -82,7 +84,8 @@ struct TokArgs {
     int k_stride, v_stride;       // bytes per token record (multiples of 16)
     Pages pg;                     // block table of a paged cache (bt null: contiguous)
     const int32_t* seq_lens;
-    float scale_log2;             // softmax_scale * log2(e) / d (/ 1 for prerotated keys)
+    float scale_log2;             // |softmax_scale| * log2(e) / d (/ 1 for prerotated keys), at least 1e-37
+    float q_sign;                 // the sign of softmax_scale
     int rot_q, rot_out;           // keys / values rotated online (tables not prerotated)
     int32_t* ws_hdr;
     float* ws_m;
@@ -139,23 +142,6 @@ __device__ __forceinline__ void twait_a(TChain& c) {
 template <int N>
 __device__ __forceinline__ void twait_b(TChain& c) {
     asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(c.e) : "i"(N));
-}
-
-typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-
-// The query digits of one group (16 bytes at LDS address a + off, off a
-// constant once unrolled), requested under the same rule: pending until a
-// twait_bq that follows it has run.
-__device__ __forceinline__ void qissue(uint32_t a, int off, v4u& q) {
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(q) : "v"(a), "i"(off));
-}
-
-template <int N, int HG>
-__device__ __forceinline__ void twait_bq(TChain& c, v4u (&q)[HG]) {
-    if constexpr (HG == 1)
-        asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(c.e), "+v"(q[0]) : "i"(N));
-    else
-        asm volatile("s_waitcnt lgkmcnt(%3)" : "+v"(c.e), "+v"(q[0]), "+v"(q[1]) : "i"(N));
 }
 
 // sh of the first step, kept for the second
@@ -230,24 +216,17 @@ __device__ __forceinline__ void refill1(uint32_t pb, uint32_t& nc, uint32_t& thr
     }
 }
 
-// The query digits alone (a single chain whose next reads stay in flight).
-template <int N>
-__device__ __forceinline__ void twait_q(v4u& q) {
-    asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(q) : "i"(N));
-}
-
 // The 128 steps of one KV head on a single chain (the wavefront decodes only
 // the keys or only the values of its tile): per step pair the ring dwords
 // and the first table word, then the second table word, each awaited before
 // it is used; the ring is refilled after every block of 8 steps, whose last
-// reads come after the refill's writes.  Keys (KEYS): the query digits of
-// group g are requested in its last step pair and the q . k products formed
-// as the levels appear; values: the packed levels are returned in vlev.
-template <uint32_t LUT, bool KEYS>
+// reads come after the refill's writes.  level(grp, word) takes the packed
+// levels of four steps; no read of the chain is in flight when it is called for
+// an odd group.
+template <uint32_t LUT, typename Level>
 __device__ __forceinline__ void chain_head(TChain& c, uint32_t ring, uint32_t mask8, int p3, uint32_t& nc,
                                            uint32_t& thr, uint2& nxt, const uint8_t* rec, uint32_t last,
-                                           uint32_t q_lane, v4i (&dk)[3], uint32_t (&vlev)[kGroups]) {
-    v4u qd;
+                                           Level&& level) {
 #pragma unroll
     for (int grp = 0; grp < kGroups; ++grp) {
         if ((grp & 1) == 0) tissue_a<LUT>(c, ring, mask8);
@@ -259,27 +238,13 @@ __device__ __forceinline__ void chain_head(TChain& c, uint32_t ring, uint32_t ma
             twait_a<0>(c);
             w[2 * u] = tfinish_a(c, p3, sh);
             tissue_b<LUT>(c, mask8);
-            if (KEYS && u == 1) {
-                qissue(q_lane, (grp * 4) * 16, qd);
-                twait_b<1>(c);
-            } else {
-                twait_b<0>(c);
-            }
+            twait_b<0>(c);
             w[2 * u + 1] = tfinish_b(c, p3, sh);
             if (more) tissue_a<LUT>(c, ring, mask8);
         }
-        const uint32_t lev = pack4(w[0], w[1], w[2], w[3]);
-        if constexpr (KEYS) {
-            // the digits were requested before the next pair's two reads
-            if (grp & 1) twait_q<0>(qd);
-            else twait_q<2>(qd);
-            dk[0] = mfma(qd.x, lev, dk[0]);
-            dk[1] = mfma(qd.y, lev, dk[1]);
-            dk[2] = mfma(qd.z, lev, dk[2]);
-        } else {
-            vlev[grp] = lev;
-            asm volatile("" : "+v"(vlev[grp]));
-        }
+        uint32_t lev = pack4(w[0], w[1], w[2], w[3]);
+        asm volatile("" : "+v"(lev));
+        level(grp, lev);
         if (grp & 1) {
             refill1(c.pb, nc, thr, nxt, ring, rec, last);
             // a second chunk only where a lane is still short (rare)
@@ -291,6 +256,38 @@ __device__ __forceinline__ void chain_head(TChain& c, uint32_t ring, uint32_t ma
     }
 }
 
+// Key levels of group grp: every fourth group completes 16 bytes of the lane's
+// row, and after 64 channels the slice meets the query digits (kq: the slice's
+// operand of head h's query tiles).
+template <int HG>
+__device__ __forceinline__ void key_levels(int grp, uint32_t lev, uint32_t (&k4)[4], uint32_t row, uint32_t col,
+                                           uint32_t kq, v4i (&d)[HG][4]) {
+    k4[grp & 3] = lev;
+    if ((grp & 3) == 3) {
+        *LDS_PTR(v4i, row + 16 * ((grp >> 2) & 3)) = v4i{(int)k4[0], (int)k4[1], (int)k4[2], (int)k4[3]};
+        if ((grp & 15) == 15) {
+            wave_sync();       // rows are read by other lanes
+            qk_slice<HG>(col, kq + (grp >> 4) * kQTile, d);
+            wave_sync();       // and rewritten by the next slice or the values
+        }
+    }
+}
+
+// The softmax state of the head at hand sits in lane 0 of each row of 16 lanes;
+// the rows rotate by one lane per head.
+__device__ __forceinline__ float row_next(float v) { return __uint_as_float(dpp_u32<0x12F, 0xF>(__float_as_uint(v))); }
+__device__ __forceinline__ float row_first(float v) { return __uint_as_float(dpp_u32<0x150, 0xF>(__float_as_uint(v))); }
+
+// One tile's contribution to the state of the head at hand: m (the new maximum),
+// corr, and the row sums of psum and osum; then on to the next head.
+__device__ __forceinline__ void push_state(const SlotWeights& sw, float m, bool first, float& m_vec, float& l_vec,
+                                           float& o_vec) {
+    const float l = l_vec * sw.corr + row_sum16(sw.psum), o = o_vec * sw.corr + row_sum16(sw.osum);
+    m_vec = row_next(first ? m : m_vec);
+    l_vec = row_next(first ? l : l_vec);
+    o_vec = row_next(first ? o : o_vec);
+}
+
 // Accumulators of channel block cb of slice s and slot group hg: one vector
 // acc[s][hg][cb] over the KV heads, for query-head slot 4 hg + l / 16 and
 // channel 64 s + 16 cb + l mod 16 in lane l.  The head loop is not unrolled,
@@ -299,11 +296,6 @@ __device__ __forceinline__ void chain_head(TChain& c, uint32_t ring, uint32_t ma
 typedef float v8f __attribute__((ext_vector_type(kTokMaxHeads)));
 
 __device__ __forceinline__ v8f rot1(const v8f& v) { return v8f{v[1], v[2], v[3], v[4], v[5], v[6], v[7], v[0]}; }
-
-__device__ __forceinline__ float lane_get(float v, int i) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i));
-}
-__device__ __forceinline__ float lane_set(float v, int i, float x, int lane) { return lane == i ? x : v; }
 
 // PAGED: records and key means through the block table; a separate
 // instantiation, so that the contiguous kernel carries none of its state.
@@ -344,25 +336,15 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
     float* qscale = reinterpret_cast<float*>(smem + L.qscale);
     float* qsum = reinterpret_cast<float*>(smem + L.qsum);
     float* qmu = reinterpret_cast<float*>(smem + L.qmu);
-    uint8_t* qlimb = smem + L.qlimb;
+    uint8_t* qtile = smem + L.qtile;
     rotate_query_heads(a.q + (int64_t)b * Hq * kD, Hq, Hq, wave, L.nw, lane, qt, qscale, qsum, a.rot_q);
     __syncthreads();
-    // digits of head slot r of KV head h at ((h * 32 + j / 4) * GS + r) * 16 + j % 4 (+4, +8)
-    for (int i = tid; i < Hkv * GS * kD; i += nthr) {
-        const int h = i / (GS * kD), r = (i / kD) % GS, j = i % kD;
-        const int g = h * G + r;
-        int v = 0;
-        if (r < G && qscale[g] > 0.f) {
-            v = (int)rintf(qt[g * kD + j] / qscale[g]);
-            v = max(-4194304, min(4194304, v));
-        }
-        int d0, d1, d2;
-        digits3(v, d0, d1, d2);
-        uint8_t* dst = qlimb + ((h * kGroups + j / 4) * GS + r) * 16 + (j % 4);
-        dst[0] = (uint8_t)d0;
-        dst[4] = (uint8_t)d1;
-        dst[8] = (uint8_t)d2;
-        dst[12] = 0;
+    // a wavefront per query-head slot (slots past G get zero digits)
+    for (int i = wave; i < Hkv * GS; i += L.nw) {
+        const int h = i / GS, r = i % GS, g = h * G + r;
+        const bool live = r < G;
+        query_digits(qtile + h * HG * 2 * kQTile, r, lane, live ? qt[g * kD + lane] : 0.f,
+                     live ? qt[g * kD + lane + 64] : 0.f, live ? qscale[g] : 0.f);
     }
     const int nwin_total = a.t_cap / DQ_MEAN_WINDOW;
     const int w0 = start / DQ_MEAN_WINDOW;
@@ -390,32 +372,38 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
 #pragma unroll
                 for (int k = 0; k < 4; ++k) s = s + qt[g * kD + c4 + k] * f[k];
                 s = half_sum_f32(s);
-                if ((lane & 31) == 31 && it < nwin * Hkv) qmu[wi * Hq + g] = s;
+                if ((lane & 31) == 31 && it < nwin * Hkv) qmu[wi * Hq + g] = s * a.q_sign;
             }
         }
     }
     __syncthreads();
 
     // ---- per-wavefront state
-    uint8_t* wreg = smem + L.waves + wave * L.wave_stride;
     const uint32_t ring_k = (uint32_t)(L.waves + wave * L.wave_stride + L.ring_k) + 4u * lane;
     const uint32_t ring_v = (uint32_t)(L.waves + wave * L.wave_stride + L.ring_v) + 4u * lane;
-    uint8_t* vtile = wreg + L.vtile;
-    uint8_t* plimb = wreg + L.plimb;
     // P . v: lane l serves slot l / 16 of each group and channel l % 16 of each
     // 16-channel block; its tr8 reads start at token row 8 (l / 16) +
     // (l % 16) / 2 of a 32-token block, byte 8 (l % 2) of the row's block
-    const int pslot = lane >> 4;
+    const int pslot = lane >> 4, l16 = lane & 15;
+    const uint32_t wbase = (uint32_t)(L.waves + wave * L.wave_stride);
     const uint32_t trow = (uint32_t)(8 * (lane >> 4) + ((lane & 15) >> 1));
-    const uint32_t a_lane = (uint32_t)(L.waves + wave * L.wave_stride + L.plimb) + trow * 16 + 8 * (lane & 1);
-    const uint32_t b_lane = (uint32_t)(L.waves + wave * L.wave_stride + L.vtile) + trow * kVRowT + 8 * (lane & 1);
+    const uint32_t a_off = trow * 16 + 8 * (lane & 1);
+    const uint32_t b_lane = wbase + L.vtile + trow * kRowT + 8 * (lane & 1);
+    const uint32_t row_lane = wbase + L.vtile + lane * kRowT, col_lane = wbase + L.vtile + level_operand(lane);
+    const uint32_t kq_lane = (uint32_t)L.qtile + query_operand(lane);
+    const uint32_t w_off = 16 * l16 + 4 * pslot;
     const int pk3 = a.tk.p + 3, pv3 = a.tv.p + 3;
     const uint32_t mask8k = ((1u << a.tk.p) - 1u) << 3, mask8v = ((1u << a.tv.p) - 1u) << 3;
     const uint32_t last_k = (uint32_t)(a.k_stride / 8 - 1), last_v = (uint32_t)(a.v_stride / 8 - 1);
     const uint32_t endk = 8u * (uint32_t)a.tk.C, endv = 8u * (uint32_t)a.tv.C;
 
-    // running softmax state of query-head slot GS h + r in lane GS h + r
-    float m_vec = -INFINITY, l_vec = 0.f, o_vec = 0.f;
+    // running softmax state of slot l / 16 of KV head l % 16 (rotating)
+    float m_vec[HG], l_vec[HG], o_vec[HG];
+#pragma unroll
+    for (int hg = 0; hg < HG; ++hg) {
+        m_vec[hg] = -INFINITY;
+        l_vec[hg] = o_vec[hg] = 0.f;
+    }
     v8f acc[2][HG][4];
 #pragma unroll
     for (int s = 0; s < 2; ++s)
@@ -425,6 +413,53 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
             for (int cb = 0; cb < 4; ++cb) acc[s][hg][cb] = v8f{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     bool corrupt = false;
     const int ntiles = (min(a.chunk, T - start) + kTile - 1) / kTile;
+
+    // the weights of head h's groups from its digit sums (headers at hdr, in
+    // wavefront LDS), their digits to wt
+    auto score_head = [&](const v4i (&d)[HG][4], int h, uint32_t hdr, int t_base, uint32_t wt, SlotWeights (&sw)[HG],
+                          float (&m)[HG]) {
+        uint2 hd[4];
+#pragma unroll
+        for (int tg = 0; tg < 4; ++tg) {
+            const v2u v = *LDS_PTR(v2u, hdr + 8 * l16 + tg * 128);
+            hd[tg] = uint2{v.x, v.y};
+        }
+        const int left = T - t_base - l16;
+        const bool whole = t_base + kTile <= T;
+        const float* qm = qmu + (t_base / DQ_MEAN_WINDOW - w0) * Hq;
+#pragma unroll
+        for (int hg = 0; hg < HG; ++hg) {
+            const int r = 4 * hg + pslot, g = r < G ? h * G + r : 0;    // slots past G take no query head
+            m[hg] = row_first(m_vec[hg]);
+            sw[hg] = slot_softmax(d[hg], hd, qscale[g] * a.q_sign, qsum[g] * a.q_sign, qm[g], a.scale_log2, left, whole,
+                                  m[hg]);
+            store_weights(wt + w_off + hg * (kTile * 16), sw[hg].w);
+        }
+    };
+    // ---- P . v over two slices of 64 channels with the weights at wt
+    auto value_head = [&](const uint32_t (&vlev)[kGroups], uint32_t wt, auto&& add) {
+        v4i pa[HG];
+#pragma unroll
+        for (int hg = 0; hg < HG; ++hg) pa[hg] = load_weights(wt + a_off + hg * (kTile * 16));
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl) {
+            if (sl) wave_sync();   // the first slice's value rows are no longer read
+            store_levels(row_lane, vlev + 16 * sl);
+            wave_sync();
+            // all operands first, then the products
+            v4i vb[4];
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb) vb[cb] = load_values(b_lane + 16 * cb);
+#pragma unroll
+            for (int hg = 0; hg < HG; ++hg) {
+                v4i dv[4];
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb) dv[cb] = mfma64(pa[hg], vb[cb], v4i{0, 0, 0, 0});
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb) add(sl, hg, cb, digit_sum(dv[cb]));
+            }
+        }
+    };
 
     if constexpr (SPLIT) {
         // One tile per pair of wavefronts.  Per KV head the even wavefront
@@ -440,9 +475,9 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
         const int tile = wave >> 1, role = wave & 1;
         const bool has = tile < ntiles;
         const uint32_t kreg = (uint32_t)(L.waves + (wave & ~1) * L.wave_stride);
-        // in the key wavefront's value-tile area: weight tile 1, then
-        // [2][GS] corrections, [2][GS] weight scales, and the statistics
-        float* kx = reinterpret_cast<float*>(smem + kreg + L.vtile + kTile * 16);
+        // the key wavefront's value ring is free: weight tile 1, then [2][GS]
+        // corrections, [2][GS] weight units, and the statistics
+        float* kx = reinterpret_cast<float*>(smem + kreg + L.ring_v + kTile * 16);
         const int t_base = start + tile * kTile;
         const int t = t_base + lane;
         const bool valid = t < T;
@@ -457,7 +492,6 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
         TChain ch;
         uint32_t nc = 4, thr = 8u * (8u * 4u - 20u) - 1u;
         uint2 nxt{0u, 0u};
-        float sk = 0.f, ok = 0.f, sv = 0.f, ov = 0.f;
         if (has) {
             const uint2 c0 = load_chunk(rec, 0, last), c1 = load_chunk(rec, 1, last), c2 = load_chunk(rec, 2, last),
                         c3 = load_chunk(rec, 3, last);
@@ -470,107 +504,43 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
             put_chunk(ring, 3, c3);
             ch.X = c0.y << 3;
             ch.pb = 64;                             // payload starts at byte 8
-            sk = half_lo(c0.x);
-            ok = half_hi(c0.x);
-            sv = half_lo(vh);
-            ov = half_hi(vh);
+            if (!role) *LDS_PTR(v2u, kreg + L.hdr + 8 * lane) = v2u{c0.x, vh};
             asm volatile("" ::: "memory");
         }
-        const float* qm = qmu + ((t / DQ_MEAN_WINDOW) - w0) * Hq;
         for (int h = 0; h < Hkv; ++h) {
-            v4i dk[3] = {v4i{0, 0, 0, 0}, v4i{0, 0, 0, 0}, v4i{0, 0, 0, 0}};
             uint32_t vlev[kGroups];
             const int buf = h & 1;
+            const uint32_t wt = kreg + (uint32_t)(buf ? L.ring_v : L.plimb);
             if (has && role == 0) {
-                const uint32_t q_lane = (uint32_t)L.qlimb + (uint32_t)(h * kGroups * GS + (lane & 3)) * 16;
-                chain_head<0, true>(ch, ring, mask8, p3, nc, thr, nxt, rec, last, q_lane, dk, vlev);
-                // scores of the head's query heads and the online softmax
-                float score[4], tmax[4], pw[4], smax[4], corr[4];
+                v4i d[HG][4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const bool live = r < G;
-                    const int g = live ? h * G + r : 0;
-                    const float dot = combine(dk[0], dk[1], dk[2], r) * qscale[g];
-                    score[r] = (valid && live) ? (sk * dot + ok * qsum[g] + qm[g]) * a.scale_log2 : -INFINITY;
-                    tmax[r] = score[r];
+                for (int tg = 0; tg < 4; ++tg) d[0][tg] = v4i{0, 0, 0, 0};
+                uint32_t k4[4];
+                const uint32_t kq = kq_lane + (uint32_t)(h * HG * 2 * kQTile);
+                chain_head<0>(ch, ring, mask8, p3, nc, thr, nxt, rec, last, [&](int grp, uint32_t lev) {
+                    key_levels<HG>(grp, lev, k4, row_lane, col_lane, kq, d);
+                });
+                SlotWeights sw[HG];
+                float m[HG];
+                score_head(d, h, kreg + L.hdr, t_base, wt, sw, m);
+                if (l16 == 0) {
+                    kx[buf * GS + pslot] = sw[0].corr;
+                    kx[2 * GS + buf * GS + pslot] = sw[0].wscale;
                 }
-                wave_max4_f32(tmax);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int slot = h * GS + r;
-                    const float m_old = lane_get(m_vec, slot);
-                    const float mn = fmaxf(m_old, tmax[r]);
-                    corr[r] = (m_old == -INFINITY || mn == -INFINITY) ? (m_old == mn ? 1.f : 0.f)
-                                                                     : __builtin_amdgcn_exp2f(m_old - mn);
-                    const float p = (score[r] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(score[r] - mn);
-                    const float lt = wave_sum_f32(p);
-                    const float ot = wave_sum_f32(p * ov);
-                    m_vec = lane_set(m_vec, slot, mn, lane);
-                    l_vec = lane_set(l_vec, slot, lane_get(l_vec, slot) * corr[r] + lt, lane);
-                    o_vec = lane_set(o_vec, slot, lane_get(o_vec, slot) * corr[r] + ot, lane);
-                    pw[r] = p * sv;
-                    smax[r] = pw[r];
-                }
-                wave_max4_f32(smax);
-                uint32_t wd[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float inv = smax[r] > 0.f ? 4194304.0f * __builtin_amdgcn_rcpf(smax[r]) : 0.f;
-                    const int pint = min(4194304, (int)rintf(pw[r] * inv));
-                    int d0, d1, d2;
-                    digits3(pint, d0, d1, d2);
-                    wd[r] = ((uint32_t)d0 & 0xFFu) | (((uint32_t)d1 & 0xFFu) << 8) | (((uint32_t)d2 & 0xFFu) << 16);
-                }
-                uint8_t* wt = smem + kreg + (buf ? L.vtile : L.plimb);
-                *reinterpret_cast<uint4*>(wt + lane * 16) = uint4{wd[0], wd[1], wd[2], wd[3]};
-                if (lane == 0) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        kx[buf * GS + r] = corr[r];
-                        kx[2 * GS + buf * GS + r] = smax[r] * (1.0f / 4194304.0f);
-                    }
-                }
+                push_state(sw[0], m[0], l16 == 0, m_vec[0], l_vec[0], o_vec[0]);
             } else if (has) {
-                chain_head<LUTV, false>(ch, ring, mask8, p3, nc, thr, nxt, rec, last, 0u, dk, vlev);
+                chain_head<LUTV>(ch, ring, mask8, p3, nc, thr, nxt, rec, last,
+                                 [&](int grp, uint32_t lev) { vlev[grp] = lev; });
             }
             __syncthreads();   // the weights of the head are in LDS
             if (has && role == 1) {
-                // ---- P . v over two slices of 64 channels, the partner's weights
-                const uint32_t a_pair = kreg + (uint32_t)(buf ? L.vtile : L.plimb) + trow * 16 + 8 * (lane & 1);
-                uint64_t pa[2];
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb) pa[kb] = lds_tr8(a_pair + kb * 32 * 16);
-                const float corr_l = pick4(kx + buf * GS, pslot);
-                const float scale_l = pick4(kx + 2 * GS + buf * GS, pslot);
-#pragma unroll
-                for (int sl = 0; sl < 2; ++sl) {
-                    if (sl) wave_sync();   // the first slice's value rows are no longer read
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        *reinterpret_cast<uint4*>(vtile + lane * kVRowT + 16 * q) =
-                            uint4{vlev[16 * sl + 4 * q], vlev[16 * sl + 4 * q + 1], vlev[16 * sl + 4 * q + 2],
-                                  vlev[16 * sl + 4 * q + 3]};
-                    wave_sync();
-                    uint64_t vb[kVSlice / 16][2];
-#pragma unroll
-                    for (int cb = 0; cb < kVSlice / 16; ++cb) {
-                        vb[cb][0] = lds_tr8(b_lane + 16 * cb);
-                        vb[cb][1] = lds_tr8(b_lane + 32 * kVRowT + 16 * cb);
-                    }
-                    v4i dv[kVSlice / 16];
-#pragma unroll
-                    for (int cb = 0; cb < kVSlice / 16; ++cb) dv[cb] = mfma16(pa[0], vb[cb][0], v4i{0, 0, 0, 0});
-#pragma unroll
-                    for (int cb = 0; cb < kVSlice / 16; ++cb) dv[cb] = mfma16(pa[1], vb[cb][1], dv[cb]);
-#pragma unroll
-                    for (int cb = 0; cb < kVSlice / 16; ++cb) {
-                        const float pv =
-                            ((float)dv[cb][2] * 65536.0f + (float)dv[cb][1] * 256.0f + (float)dv[cb][0]) * scale_l;
-                        v8f tv = acc[sl][0][cb];
-                        tv[0] = tv[0] * corr_l + pv;
-                        acc[sl][0][cb] = rot1(tv);
-                    }
-                }
+                // ---- P . v with the partner's weights
+                const float corr_l = kx[buf * GS + pslot], scale_l = kx[2 * GS + buf * GS + pslot];
+                value_head(vlev, wt, [&](int sl, int hg, int cb, float f) {
+                    v8f tv = acc[sl][hg][cb];
+                    tv[0] = tv[0] * corr_l + f * scale_l;
+                    acc[sl][hg][cb] = rot1(tv);
+                });
                 wave_sync();   // the next head rewrites the value rows
             }
         }
@@ -584,17 +554,22 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
         // the softmax statistics go to the value wavefront
         float* kst = kx + 4 * GS;
         if (has && role == 0) {
-            kst[lane] = m_vec;
-            kst[kWave + lane] = l_vec;
-            kst[2 * kWave + lane] = o_vec;
+            for (int h = Hkv; h < 16; ++h) {
+                m_vec[0] = row_next(m_vec[0]);
+                l_vec[0] = row_next(l_vec[0]);
+                o_vec[0] = row_next(o_vec[0]);
+            }
+            kst[lane] = m_vec[0];
+            kst[kWave + lane] = l_vec[0];
+            kst[2 * kWave + lane] = o_vec[0];
         }
         __syncthreads();
         if (has && role == 1) {
-            m_vec = kst[lane];
-            l_vec = kst[kWave + lane];
-            o_vec = kst[2 * kWave + lane];
+            m_vec[0] = kst[lane];
+            l_vec[0] = kst[kWave + lane];
+            o_vec[0] = kst[2 * kWave + lane];
         } else {
-            m_vec = -INFINITY;
+            m_vec[0] = -INFINITY;
         }
     }
 
@@ -627,22 +602,19 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
         ck.X = k0.y << 3;
         cv.X = v0.y << 3;
         ck.pb = cv.pb = 64;                         // payload starts at byte 8
-        const float sk = half_lo(k0.x), ok = half_hi(k0.x);
-        const float sv = half_lo(v0.x), ov = half_hi(v0.x);
-        const float* qm = qmu + ((t / DQ_MEAN_WINDOW) - w0) * Hq;
+        *LDS_PTR(v2u, wbase + L.hdr + 8 * lane) = v2u{k0.x, v0.x};
         // the rings are read back by this lane only: order the reads after
         // the writes (LDS keeps a wavefront's accesses in order)
         asm volatile("" ::: "memory");
 
         for (int h = 0; h < Hkv; ++h) {
-            v4i dk[HG][3];
+            v4i d[HG][4];
 #pragma unroll
-            for (int hg = 0; hg < HG; ++hg) dk[hg][0] = dk[hg][1] = dk[hg][2] = v4i{0, 0, 0, 0};
-            uint32_t vlev[kGroups];
-            // the digits of group g are requested in its last step pair, so
-            // that the wait for the value step covers them too
-            const uint32_t q_lane = (uint32_t)L.qlimb + (uint32_t)(h * kGroups * GS + (lane & 3)) * 16;
-            v4u qd[HG];
+            for (int hg = 0; hg < HG; ++hg)
+#pragma unroll
+                for (int tg = 0; tg < 4; ++tg) d[hg][tg] = v4i{0, 0, 0, 0};
+            uint32_t vlev[kGroups], k4[4];
+            const uint32_t kq = kq_lane + (uint32_t)(h * HG * 2 * kQTile);
             // steps in blocks of 8 (two groups): the rings are refilled after
             // each block, so the block's last reads are awaited (and the next
             // block's requested) after the refill; inside a block, step pair u
@@ -669,26 +641,16 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
                     tissue_b<LUTV>(cv, mask8v);
                     twait_b<1>(ck);
                     kw[2 * u + 1] = tfinish_b(ck, pk3, shk);
-                    if (u == 1) {
-                        qissue(q_lane, (grp * GS) * 16, qd[0]);
-                        if constexpr (HG == 2) qissue(q_lane, (grp * GS + 4) * 16, qd[1]);
-                    }
                     if (more) tissue_a<0>(ck, ring_k, mask8k);
-                    if (u == 0) twait_b<2>(cv);
-                    else if (more) twait_bq<2>(cv, qd);
-                    else twait_bq<0>(cv, qd);
+                    if (more) twait_b<2>(cv);
+                    else twait_b<0>(cv);
                     vw[2 * u + 1] = tfinish_b(cv, pv3, shv);
                     if (more) tissue_a<LUTV>(cv, ring_v, mask8v);
                 }
-                const uint32_t lk = pack4(kw[0], kw[1], kw[2], kw[3]);
+                uint32_t lk = pack4(kw[0], kw[1], kw[2], kw[3]);
                 vlev[grp] = pack4(vw[0], vw[1], vw[2], vw[3]);
-                asm volatile("" : "+v"(vlev[grp]));
-#pragma unroll
-                for (int hg = 0; hg < HG; ++hg) {
-                    dk[hg][0] = mfma(qd[hg].x, lk, dk[hg][0]);
-                    dk[hg][1] = mfma(qd[hg].y, lk, dk[hg][1]);
-                    dk[hg][2] = mfma(qd[hg].z, lk, dk[hg][2]);
-                }
+                asm volatile("" : "+v"(lk), "+v"(vlev[grp]));
+                key_levels<HG>(grp, lk, k4, row_lane, col_lane, kq, d);
                 if (grp & 1) {
                     refill2(ck.pb, nck, thrk, nk, ring_k, kr, last_k, cv.pb, ncv, thrv, nv, ring_v, vr, last_v);
                     // a second chunk only where a lane is still short (rare): the
@@ -708,108 +670,27 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
             //      raising the decode instead, as the per-head kernel does,
             //      was 1 % slower here)
             __builtin_amdgcn_s_setprio(1);
-            float corr[GS], pscale[GS];
-            int pint[GS];
-            // four slots at a time, their tile maxima reduced together
+            SlotWeights sw[HG];
+            float m[HG];
+            score_head(d, h, wbase + L.hdr, t_base, wbase + L.plimb, sw, m);
 #pragma unroll
-            for (int hg = 0; hg < HG; ++hg) {
-                float score[4], tmax[4], pw[4], smax[4];
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr) {
-                    const int r = 4 * hg + rr;
-                    const bool live = r < G;
-                    const int g = live ? h * G + r : 0;       // slots past G take no query head
-                    const float dot = combine(dk[hg][0], dk[hg][1], dk[hg][2], rr) * qscale[g];
-                    score[rr] = (valid && live) ? (sk * dot + ok * qsum[g] + qm[g]) * a.scale_log2 : -INFINITY;
-                    tmax[rr] = score[rr];
-                }
-                wave_max4_f32(tmax);
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr) {
-                    const int r = 4 * hg + rr;
-                    const int slot = h * GS + r;
-                    const float m_old = lane_get(m_vec, slot);
-                    const float mn = fmaxf(m_old, tmax[rr]);
-                    corr[r] = (m_old == -INFINITY || mn == -INFINITY) ? (m_old == mn ? 1.f : 0.f)
-                                                                      : __builtin_amdgcn_exp2f(m_old - mn);
-                    const float p = (score[rr] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(score[rr] - mn);
-                    const float lt = wave_sum_f32(p);
-                    const float ot = wave_sum_f32(p * ov);
-                    m_vec = lane_set(m_vec, slot, mn, lane);
-                    l_vec = lane_set(l_vec, slot, lane_get(l_vec, slot) * corr[r] + lt, lane);
-                    o_vec = lane_set(o_vec, slot, lane_get(o_vec, slot) * corr[r] + ot, lane);
-                    pw[rr] = p * sv;                          // >= 0: scales are non-negative
-                    smax[rr] = pw[rr];
-                }
-                wave_max4_f32(smax);
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr) {
-                    const int r = 4 * hg + rr;
-                    pscale[r] = smax[rr] * (1.0f / 4194304.0f);
-                    const float inv = smax[rr] > 0.f ? 4194304.0f * __builtin_amdgcn_rcpf(smax[rr]) : 0.f;
-                    pint[r] = min(4194304, (int)rintf(pw[rr] * inv));
-                }
-            }
-            // weight digits -> LDS, one 16-byte token row per slot group: byte
-            // 4 r + d holds digit d of slot r (byte 4 r + 3 stays zero)
-            float corr_l[HG], scale_l[HG];
-#pragma unroll
-            for (int hg = 0; hg < HG; ++hg) {
-                uint32_t w[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    int d0, d1, d2;
-                    digits3(pint[4 * hg + r], d0, d1, d2);
-                    w[r] = ((uint32_t)d0 & 0xFFu) | (((uint32_t)d1 & 0xFFu) << 8) | (((uint32_t)d2 & 0xFFu) << 16);
-                }
-                *reinterpret_cast<uint4*>(plimb + hg * (kTile * 16) + lane * 16) = uint4{w[0], w[1], w[2], w[3]};
-                corr_l[hg] = pick4(corr + 4 * hg, pslot);
-                scale_l[hg] = pick4(pscale + 4 * hg, pslot);
-            }
-
+            for (int hg = 0; hg < HG; ++hg) push_state(sw[hg], m[hg], l16 == 0, m_vec[hg], l_vec[hg], o_vec[hg]);
             __builtin_amdgcn_s_setprio(0);
-            // ---- P . v over two slices of 64 channels
             wave_sync();   // the weight rows are read by other lanes
-            uint64_t pa[HG][2];
-#pragma unroll
-            for (int hg = 0; hg < HG; ++hg)
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb) pa[hg][kb] = lds_tr8(a_lane + hg * (kTile * 16) + kb * 32 * 16);
-#pragma unroll
-            for (int sl = 0; sl < 2; ++sl) {
-                if (sl) wave_sync();   // the first slice's value rows are no longer read
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    *reinterpret_cast<uint4*>(vtile + lane * kVRowT + 16 * q) =
-                        uint4{vlev[16 * sl + 4 * q], vlev[16 * sl + 4 * q + 1], vlev[16 * sl + 4 * q + 2],
-                              vlev[16 * sl + 4 * q + 3]};
-                wave_sync();
-                // all operands first, then the product chains
-                uint64_t vb[kVSlice / 16][2];
-#pragma unroll
-                for (int cb = 0; cb < kVSlice / 16; ++cb) {
-                    vb[cb][0] = lds_tr8(b_lane + 16 * cb);
-                    vb[cb][1] = lds_tr8(b_lane + 32 * kVRowT + 16 * cb);
-                }
-#pragma unroll
-                for (int hg = 0; hg < HG; ++hg) {
-                    v4i dv[kVSlice / 16];
-#pragma unroll
-                    for (int cb = 0; cb < kVSlice / 16; ++cb) dv[cb] = mfma16(pa[hg][0], vb[cb][0], v4i{0, 0, 0, 0});
-#pragma unroll
-                    for (int cb = 0; cb < kVSlice / 16; ++cb) dv[cb] = mfma16(pa[hg][1], vb[cb][1], dv[cb]);
-#pragma unroll
-                    for (int cb = 0; cb < kVSlice / 16; ++cb) {
-                        const float pv =
-                            ((float)dv[cb][2] * 65536.0f + (float)dv[cb][1] * 256.0f + (float)dv[cb][0]) *
-                            scale_l[hg];
-                        v8f t = acc[sl][hg][cb];
-                        t[0] = t[0] * corr_l[hg] + pv;
-                        acc[sl][hg][cb] = rot1(t);
-                    }
-                }
-            }
+            value_head(vlev, wbase + L.plimb, [&](int sl, int hg, int cb, float f) {
+                v8f t = acc[sl][hg][cb];
+                t[0] = t[0] * sw[hg].corr + f * sw[hg].wscale;
+                acc[sl][hg][cb] = rot1(t);
+            });
             wave_sync();   // the next head rewrites the weight and value rows
+        }
+        for (int h = Hkv; h < 16; ++h) {
+#pragma unroll
+            for (int hg = 0; hg < HG; ++hg) {
+                m_vec[hg] = row_next(m_vec[hg]);
+                l_vec[hg] = row_next(l_vec[hg]);
+                o_vec[hg] = row_next(o_vec[hg]);
+            }
         }
         for (int h = Hkv; h < kTokMaxHeads; ++h)
 #pragma unroll
@@ -842,20 +723,16 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
                     acc[s][hg][cb] = rot1(acc[s][hg][cb]);
                 }
         __syncthreads();   // LDS free (first head) / previous head merged
-        float ovs[GS];
-#pragma unroll
-        for (int r = 0; r < GS; ++r) {
-            const int slot = h * GS + r;
-            const float mv = lane_get(m_vec, slot), lv = lane_get(l_vec, slot);
-            ovs[r] = lane_get(o_vec, slot);
-            if (lane == 0) {
-                mw[wave * GS + r] = mv;
-                lw[wave * GS + r] = lv;
-            }
-        }
 #pragma unroll
         for (int hg = 0; hg < HG; ++hg) {
-            const float ovt = pick4(ovs + 4 * hg, pslot);
+            if (l16 == 0) {
+                mw[wave * GS + 4 * hg + pslot] = m_vec[hg];
+                lw[wave * GS + 4 * hg + pslot] = l_vec[hg];
+            }
+            const float ovt = row_first(o_vec[hg]);
+            m_vec[hg] = row_next(m_vec[hg]);
+            l_vec[hg] = row_next(l_vec[hg]);
+            o_vec[hg] = row_next(o_vec[hg]);
             float* row = aw + (wave * GS + 4 * hg + pslot) * kD + (lane & 15);
 #pragma unroll
             for (int s = 0; s < 2; ++s)
@@ -892,8 +769,8 @@ TokLayout tok_layout(int pk, int pv, bool shared_lut, int Hq, int Hkv, int chunk
     off += 8 << pk;
     L.lut_v = shared_lut ? L.lut_k : off;
     if (!shared_lut) off += 8 << pv;
-    L.qlimb = off;
-    off += Hkv * kGroups * 4 * HG * 16;
+    L.qtile = off;
+    off += Hkv * HG * 2 * kQTile;
     L.qscale = off;
     off += 4 * Hq;
     L.qsum = off;
@@ -905,8 +782,9 @@ TokLayout tok_layout(int pk, int pv, bool shared_lut, int Hq, int Hkv, int chunk
     L.ring_k = 0;
     L.ring_v = kRingBytes;
     L.vtile = 2 * kRingBytes;
-    L.plimb = L.vtile + kTile * kVRowT;
-    L.wave_stride = (L.plimb + HG * kTile * 16 + 15) & ~15;
+    L.plimb = L.vtile + kTile * kRowT;
+    L.hdr = L.plimb + HG * kTile * 16;
+    L.wave_stride = L.hdr + kTile * 8;
     L.nw = nw;
     // the prologue's query scratch and the epilogue's merge buffers use the
     // wavefront regions
@@ -1009,7 +887,8 @@ int launch_attention_token_partial(const dq_tables* tk, const dq_tables* tv, con
     a.seq_lens = seq_lens;
     a.rot_q = tk->cfg.prerotated ? 0 : 1;
     a.rot_out = tv->cfg.prerotated ? 0 : 1;
-    a.scale_log2 = scale * 1.4426950408889634f / (a.rot_q ? (float)kD : 1.0f);
+    a.scale_log2 = std::max(std::fabs(scale) * 1.4426950408889634f / (a.rot_q ? (float)kD : 1.0f), 1e-37f);
+    a.q_sign = scale < 0.f ? -1.f : 1.f;
     const int64_t slots = ws_slots(B, Hq, t_cap);
     a.ws_hdr = static_cast<int32_t*>(ws);
     a.ws_acc = reinterpret_cast<float*>(static_cast<uint8_t*>(ws) + kWsHeader);
