@@ -167,6 +167,28 @@ __device__ __forceinline__ uint32_t tfinish_b(TChain& c, int p3, uint32_t sha) {
     return eb;
 }
 
+// Four steps on one ring read, for p = 8: there a step reads at most one byte (x'
+// >= f 2^13, and one byte more brings it to L), so the four bytes at the lane's
+// position serve four steps, and a block between two refills is 16 steps of at
+// most 16 bytes, which the same 20 bytes cover.  U: step in the group; shp: the
+// shift of step U - 1.
+template <int U>
+__device__ __forceinline__ uint32_t tfinish4(TChain& c, int p3, uint32_t& shp) {
+    if (U == 0) {
+        const uint32_t lo = (uint32_t)c.rr, hi = (uint32_t)(c.rr >> 32);
+        c.w = __builtin_amdgcn_perm(0u, __builtin_amdgcn_alignbit(hi, lo, c.pb), 0x00010203u);
+    }
+    const uint32_t e = (uint32_t)c.e;
+    const uint32_t y = __umul24(e, c.X >> p3) + (uint32_t)(c.e >> 32);
+    const uint32_t sh = (uint32_t)__builtin_clz(y) & 24u;
+    const uint32_t q = c.w >> (sh ^ 29u);
+    asm("v_lshl_or_b32 %0, %1, %2, %3" : "=v"(c.X) : "v"(y), "v"(sh), "v"(q));
+    if (U < 3) c.w <<= sh;
+    if (U & 1) asm("v_add3_u32 %0, %1, %2, %3" : "=v"(c.pb) : "v"(c.pb), "v"(shp), "v"(sh));
+    shp = sh;
+    return e;
+}
+
 // rec: the lane's first chunk (tile + 8 lane); chunks are 512 bytes apart.
 __device__ __forceinline__ uint2 load_chunk(const uint8_t* rec, uint32_t c, uint32_t last) {
     return *reinterpret_cast<const uint2*>(rec + 512u * min(c, last));
@@ -222,30 +244,47 @@ __device__ __forceinline__ void refill1(uint32_t pb, uint32_t& nc, uint32_t& thr
 // it is used; the ring is refilled after every block of 8 steps, whose last
 // reads come after the refill's writes.  level(grp, word) takes the packed
 // levels of four steps; no read of the chain is in flight when it is called for
-// an odd group.
-template <uint32_t LUT, typename Level>
+// the last group of a block.  W4: four steps per ring read and blocks of 16
+// steps (p = 8).
+template <uint32_t LUT, bool W4, typename Level>
 __device__ __forceinline__ void chain_head(TChain& c, uint32_t ring, uint32_t mask8, int p3, uint32_t& nc,
                                            uint32_t& thr, uint2& nxt, const uint8_t* rec, uint32_t last,
                                            Level&& level) {
+    constexpr int kBlock = W4 ? 3 : 1;          // groups between two refills, less one
 #pragma unroll
     for (int grp = 0; grp < kGroups; ++grp) {
-        if ((grp & 1) == 0) tissue_a<LUT>(c, ring, mask8);
-        uint32_t w[4];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const bool more = !((grp & 1) && u == 1);
-            uint32_t sh;
+        const bool end = (grp & kBlock) == kBlock;
+        if ((grp & kBlock) == 0) tissue_a<LUT>(c, ring, mask8);
+        uint32_t w[4], sh;
+        if constexpr (W4) {
             twait_a<0>(c);
-            w[2 * u] = tfinish_a(c, p3, sh);
+            w[0] = tfinish4<0>(c, p3, sh);
             tissue_b<LUT>(c, mask8);
             twait_b<0>(c);
-            w[2 * u + 1] = tfinish_b(c, p3, sh);
-            if (more) tissue_a<LUT>(c, ring, mask8);
+            w[1] = tfinish4<1>(c, p3, sh);
+            tissue_b<LUT>(c, mask8);
+            twait_b<0>(c);
+            w[2] = tfinish4<2>(c, p3, sh);
+            tissue_b<LUT>(c, mask8);
+            twait_b<0>(c);
+            w[3] = tfinish4<3>(c, p3, sh);
+            if (!end) tissue_a<LUT>(c, ring, mask8);
+        } else {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const bool more = !(end && u == 1);
+                twait_a<0>(c);
+                w[2 * u] = tfinish_a(c, p3, sh);
+                tissue_b<LUT>(c, mask8);
+                twait_b<0>(c);
+                w[2 * u + 1] = tfinish_b(c, p3, sh);
+                if (more) tissue_a<LUT>(c, ring, mask8);
+            }
         }
         uint32_t lev = pack4(w[0], w[1], w[2], w[3]);
         asm volatile("" : "+v"(lev));
         level(grp, lev);
-        if (grp & 1) {
+        if (end) {
             refill1(c.pb, nc, thr, nxt, ring, rec, last);
             // a second chunk only where a lane is still short (rare)
             if (__any(c.pb > thr)) refill1(c.pb, nc, thr, nxt, ring, rec, last);
@@ -302,7 +341,8 @@ __device__ __forceinline__ v8f rot1(const v8f& v) { return v8f{v[1], v[2], v[3],
 // HG: groups of 4 query-head slots per KV head (1: G <= 4, 2: G <= 8).
 // SPLIT: one tile per pair of wavefronts, keys and values decoded by
 // different wavefronts (chunks of at most nw / 2 tiles: small batches).
-template <uint32_t LUTV, bool PAGED, int HG, bool SPLIT = false>
+// W4: both tables have p = 8 (see tfinish4).
+template <uint32_t LUTV, bool PAGED, int HG, bool SPLIT, bool W4>
 __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) void attn_token_kernel(TokArgs a) {
     constexpr int GS = 4 * HG;                 // query-head slots per KV head
     extern __shared__ __align__(16) uint8_t smem[];
@@ -503,6 +543,7 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
             put_chunk(ring, 2, c2);
             put_chunk(ring, 3, c3);
             ch.X = c0.y << 3;
+            if (W4) corrupt |= valid && (ch.X >> 3) < kRansL;   // (one byte a step needs a state from L on)
             ch.pb = 64;                             // payload starts at byte 8
             if (!role) *LDS_PTR(v2u, kreg + L.hdr + 8 * lane) = v2u{c0.x, vh};
             asm volatile("" ::: "memory");
@@ -517,7 +558,7 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
                 for (int tg = 0; tg < 4; ++tg) d[0][tg] = v4i{0, 0, 0, 0};
                 uint32_t k4[4];
                 const uint32_t kq = kq_lane + (uint32_t)(h * HG * 2 * kQTile);
-                chain_head<0>(ch, ring, mask8, p3, nc, thr, nxt, rec, last, [&](int grp, uint32_t lev) {
+                chain_head<0, W4>(ch, ring, mask8, p3, nc, thr, nxt, rec, last, [&](int grp, uint32_t lev) {
                     key_levels<HG>(grp, lev, k4, row_lane, col_lane, kq, d);
                 });
                 SlotWeights sw[HG];
@@ -529,7 +570,7 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
                 }
                 push_state(sw[0], m[0], l16 == 0, m_vec[0], l_vec[0], o_vec[0]);
             } else if (has) {
-                chain_head<LUTV>(ch, ring, mask8, p3, nc, thr, nxt, rec, last,
+                chain_head<LUTV, W4>(ch, ring, mask8, p3, nc, thr, nxt, rec, last,
                                  [&](int grp, uint32_t lev) { vlev[grp] = lev; });
             }
             __syncthreads();   // the weights of the head are in LDS
@@ -601,6 +642,7 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
         TChain ck, cv;
         ck.X = k0.y << 3;
         cv.X = v0.y << 3;
+        if (W4) corrupt |= valid && min(ck.X, cv.X) < kRansL << 3;   // (one byte a step needs a state from L on)
         ck.pb = cv.pb = 64;                         // payload starts at byte 8
         *LDS_PTR(v2u, wbase + L.hdr + 8 * lane) = v2u{k0.x, v0.x};
         // the rings are read back by this lane only: order the reads after
@@ -615,43 +657,72 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
                 for (int tg = 0; tg < 4; ++tg) d[hg][tg] = v4i{0, 0, 0, 0};
             uint32_t vlev[kGroups], k4[4];
             const uint32_t kq = kq_lane + (uint32_t)(h * HG * 2 * kQTile);
-            // steps in blocks of 8 (two groups): the rings are refilled after
+            // steps in blocks of 8 (two groups; W4: 16): the rings are refilled after
             // each block, so the block's last reads are awaited (and the next
             // block's requested) after the refill; inside a block, step pair u
             // of both chains: wait for the key chain's first reads (the value
             // chain's follow: 2), finish, request its second table word; the
             // same for the value chain (the key chain's word follows: 1); then
             // the second steps (1, and 2 or 0 at the block's end)
+            constexpr int kBlock = W4 ? 3 : 1;
 #pragma unroll
             for (int grp = 0; grp < kGroups; ++grp) {
-                if ((grp & 1) == 0) {
+                const bool end = (grp & kBlock) == kBlock;
+                if ((grp & kBlock) == 0) {
                     tissue_a<0>(ck, ring_k, mask8k);
                     tissue_a<LUTV>(cv, ring_v, mask8v);
                 }
-                uint32_t kw[4], vw[4];
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const bool more = !((grp & 1) && u == 1);
-                    uint32_t shk, shv;
+                uint32_t kw[4], vw[4], shk, shv;
+                if constexpr (W4) {
                     twait_a<2>(ck);
-                    kw[2 * u] = tfinish_a(ck, pk3, shk);
+                    kw[0] = tfinish4<0>(ck, pk3, shk);
                     tissue_b<0>(ck, mask8k);
                     twait_a<1>(cv);
-                    vw[2 * u] = tfinish_a(cv, pv3, shv);
+                    vw[0] = tfinish4<0>(cv, pv3, shv);
                     tissue_b<LUTV>(cv, mask8v);
                     twait_b<1>(ck);
-                    kw[2 * u + 1] = tfinish_b(ck, pk3, shk);
-                    if (more) tissue_a<0>(ck, ring_k, mask8k);
-                    if (more) twait_b<2>(cv);
+                    kw[1] = tfinish4<1>(ck, pk3, shk);
+                    tissue_b<0>(ck, mask8k);
+                    twait_b<1>(cv);
+                    vw[1] = tfinish4<1>(cv, pv3, shv);
+                    tissue_b<LUTV>(cv, mask8v);
+                    twait_b<1>(ck);
+                    kw[2] = tfinish4<2>(ck, pk3, shk);
+                    tissue_b<0>(ck, mask8k);
+                    twait_b<1>(cv);
+                    vw[2] = tfinish4<2>(cv, pv3, shv);
+                    tissue_b<LUTV>(cv, mask8v);
+                    twait_b<1>(ck);
+                    kw[3] = tfinish4<3>(ck, pk3, shk);
+                    if (!end) tissue_a<0>(ck, ring_k, mask8k);
+                    if (!end) twait_b<2>(cv);
                     else twait_b<0>(cv);
-                    vw[2 * u + 1] = tfinish_b(cv, pv3, shv);
-                    if (more) tissue_a<LUTV>(cv, ring_v, mask8v);
+                    vw[3] = tfinish4<3>(cv, pv3, shv);
+                    if (!end) tissue_a<LUTV>(cv, ring_v, mask8v);
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        const bool more = !(end && u == 1);
+                        twait_a<2>(ck);
+                        kw[2 * u] = tfinish_a(ck, pk3, shk);
+                        tissue_b<0>(ck, mask8k);
+                        twait_a<1>(cv);
+                        vw[2 * u] = tfinish_a(cv, pv3, shv);
+                        tissue_b<LUTV>(cv, mask8v);
+                        twait_b<1>(ck);
+                        kw[2 * u + 1] = tfinish_b(ck, pk3, shk);
+                        if (more) tissue_a<0>(ck, ring_k, mask8k);
+                        if (more) twait_b<2>(cv);
+                        else twait_b<0>(cv);
+                        vw[2 * u + 1] = tfinish_b(cv, pv3, shv);
+                        if (more) tissue_a<LUTV>(cv, ring_v, mask8v);
+                    }
                 }
                 uint32_t lk = pack4(kw[0], kw[1], kw[2], kw[3]);
                 vlev[grp] = pack4(vw[0], vw[1], vw[2], vw[3]);
                 asm volatile("" : "+v"(lk), "+v"(vlev[grp]));
                 key_levels<HG>(grp, lk, k4, row_lane, col_lane, kq, d);
-                if (grp & 1) {
+                if (end) {
                     refill2(ck.pb, nck, thrk, nk, ring_k, kr, last_k, cv.pb, ncv, thrv, nv, ring_v, vr, last_v);
                     // a second chunk only where a lane is still short (rare): the
                     // test is one wavefront vote, so blocks where none is skip it
@@ -809,7 +880,7 @@ int32_t token_chunk(int32_t B, int32_t t_cap) {
 
 namespace {
 
-template <uint32_t LUTV, int HG>
+template <uint32_t LUTV, int HG, bool W4>
 int launch_token_kernel(const TokArgs& a, dim3 grid, int nw, hipStream_t stream) {
     const bool paged = a.pg.bt != nullptr;
     // chunks of at most 4 tiles (small batches, short contexts): keys and
@@ -820,40 +891,47 @@ int launch_token_kernel(const TokArgs& a, dim3 grid, int nw, hipStream_t stream)
         s.L = tok_layout(a.tk.p, a.tv.p, a.L.lut_v == a.L.lut_k, a.Hq, a.Hkv, a.chunk, kTokSplitWaves, 1);
         // (two 4096-entry tables leave no room for 8 wavefronts: both chains in one)
         if (2 * ((a.chunk + kTile - 1) / kTile) <= kTokSplitWaves && s.L.total <= kMaxLds) {
-            const void* fn = paged ? reinterpret_cast<const void*>(&attn_token_kernel<LUTV, true, 1, true>)
-                                   : reinterpret_cast<const void*>(&attn_token_kernel<LUTV, false, 1, true>);
+            const void* fn = paged ? reinterpret_cast<const void*>(&attn_token_kernel<LUTV, true, 1, true, W4>)
+                                   : reinterpret_cast<const void*>(&attn_token_kernel<LUTV, false, 1, true, W4>);
             if (int rc = hip_check("hipFuncSetAttribute",
                                    hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, s.L.total)))
                 return rc;
             if (paged)
-                attn_token_kernel<LUTV, true, 1, true><<<grid, kTokSplitWaves * kWave, (size_t)s.L.total, stream>>>(s);
+                attn_token_kernel<LUTV, true, 1, true, W4><<<grid, kTokSplitWaves * kWave, (size_t)s.L.total, stream>>>(s);
             else
-                attn_token_kernel<LUTV, false, 1, true><<<grid, kTokSplitWaves * kWave, (size_t)s.L.total, stream>>>(s);
+                attn_token_kernel<LUTV, false, 1, true, W4><<<grid, kTokSplitWaves * kWave, (size_t)s.L.total, stream>>>(s);
             return hip_check("attn_token launch", hipGetLastError());
         }
     }
-    const void* fn = paged ? reinterpret_cast<const void*>(&attn_token_kernel<LUTV, true, HG>)
-                           : reinterpret_cast<const void*>(&attn_token_kernel<LUTV, false, HG>);
+    const void* fn = paged ? reinterpret_cast<const void*>(&attn_token_kernel<LUTV, true, HG, false, W4>)
+                           : reinterpret_cast<const void*>(&attn_token_kernel<LUTV, false, HG, false, W4>);
     if (int rc = hip_check("hipFuncSetAttribute",
                            hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, a.L.total)))
         return rc;
     const size_t smem = (size_t)a.L.total;
     if (paged)
-        attn_token_kernel<LUTV, true, HG><<<grid, nw * kWave, smem, stream>>>(a);
+        attn_token_kernel<LUTV, true, HG, false, W4><<<grid, nw * kWave, smem, stream>>>(a);
     else
-        attn_token_kernel<LUTV, false, HG><<<grid, nw * kWave, smem, stream>>>(a);
+        attn_token_kernel<LUTV, false, HG, false, W4><<<grid, nw * kWave, smem, stream>>>(a);
     return hip_check("attn_token launch", hipGetLastError());
 }
 
 template <int HG>
 int launch_token_hg(const TokArgs& a, dim3 grid, int nw, bool shared, hipStream_t stream) {
+    // four steps per ring read where both tables have p = 8 (16 x 32768 tokens:
+    // see the kernel's figures), else two
+    const bool w4 = a.tk.p == 8 && a.tv.p == 8;
     switch (shared ? 0u : (uint32_t)a.L.lut_v) {
-        case 0: return launch_token_kernel<0, HG>(a, grid, nw, stream);
-        case 8u << 8: return launch_token_kernel<8u << 8, HG>(a, grid, nw, stream);
-        case 8u << 9: return launch_token_kernel<8u << 9, HG>(a, grid, nw, stream);
-        case 8u << 10: return launch_token_kernel<8u << 10, HG>(a, grid, nw, stream);
-        case 8u << 11: return launch_token_kernel<8u << 11, HG>(a, grid, nw, stream);
-        case 8u << 12: return launch_token_kernel<8u << 12, HG>(a, grid, nw, stream);
+        case 0:
+            return w4 ? launch_token_kernel<0, HG, true>(a, grid, nw, stream)
+                      : launch_token_kernel<0, HG, false>(a, grid, nw, stream);
+        case 8u << 8:
+            return w4 ? launch_token_kernel<8u << 8, HG, true>(a, grid, nw, stream)
+                      : launch_token_kernel<8u << 8, HG, false>(a, grid, nw, stream);
+        case 8u << 9: return launch_token_kernel<8u << 9, HG, false>(a, grid, nw, stream);
+        case 8u << 10: return launch_token_kernel<8u << 10, HG, false>(a, grid, nw, stream);
+        case 8u << 11: return launch_token_kernel<8u << 11, HG, false>(a, grid, nw, stream);
+        case 8u << 12: return launch_token_kernel<8u << 12, HG, false>(a, grid, nw, stream);
         default: return DQ_ERR_INVALID_ARG;
     }
 }
