@@ -5,10 +5,6 @@
 
 #include "dq_common.h"
 
-// a b + c inside one expression as one fused multiply-add (one rounding less);
-// the encoder, whose decisions are the format, does not include this file
-#pragma clang fp contract(on)
-
 namespace dq {
 
 __device__ __forceinline__ float half_lo(uint32_t w) { return half_bits_to_f32((uint16_t)(w & 0xFFFFu)); }
@@ -24,9 +20,11 @@ __device__ __forceinline__ uint32_t pack4(uint32_t e0, uint32_t e1, uint32_t e2,
     return lo | hi;
 }
 
-// Fixed-point range of the query and of the softmax weights: three signed 8-bit
-// digits reach 127 (2^16 + 2^8 + 1) = 8355711; what rounding adds stays below.
-constexpr float kDigitMax = 8355000.0f;
+// Fixed-point range of the query and of the softmax weights, in three signed 8-bit
+// digits: 2^22, so that the weights' unit and its reciprocal scale exactly (an
+// error common to all channels shows in the output's channel 0, where the offsets'
+// sum and the levels' sums nearly cancel).
+constexpr float kDigitMax = 4194304.0f;
 
 // Rotates one query head held as channels l and l + 64 in lane l
 // (unnormalized Hadamard, stages h = 1, 2, ..., 64 in the order of the
@@ -118,7 +116,7 @@ __device__ __forceinline__ void query_digits(uint8_t* tiles, int g, int lane, fl
         int v = 0;
         if (qs > 0.f) {
             v = (int)rintf((sl ? r1 : r0) / qs);
-            v = max(-8355711, min(8355711, v));
+            v = max(-4194304, min(4194304, v));
         }
         // adding 128 to every byte and flipping its top bit leaves the signed digits
         const uint32_t w = ((uint32_t)v + 0x00808080u) ^ 0x00808080u;
@@ -182,6 +180,12 @@ __device__ __forceinline__ float row_sum16(float v) {
     return v + dpp0<0x140, 0xF>(v);
 }
 
+// The digit sums of a slot and token or channel as one number (each below 2^20 in
+// magnitude, so the upper two meet exactly in int32).
+__device__ __forceinline__ float digit_sum(const v4i& d) {
+    return fmaf((float)((d[2] << 8) + d[1]), 256.0f, (float)d[0]);
+}
+
 constexpr float kLowest = -3.4028234663852886e38f;
 
 // Softmax of the lane's four tokens for its slot (Eq. fold-key), the value scale
@@ -214,9 +218,8 @@ __device__ __forceinline__ SlotWeights slot_softmax(const v4i (&d)[4], const H (
     float s[4];
 #pragma unroll
     for (int tg = 0; tg < 4; ++tg) {
-        // |digit sum| <= 128 127 63 < 2^20: the lower two meet exactly in int32
-        const float dot = (float)d[tg][2] * 65536.0f + (float)((d[tg][1] << 8) + d[tg][0]);
-        s[tg] = key_scale(h[tg]) * (dot * qs) + (key_offset(h[tg]) * qsum + qm);
+        const float dot = digit_sum(d[tg]) * qs;
+        s[tg] = fmaf(key_scale(h[tg]), dot, fmaf(key_offset(h[tg]), qsum, qm));
     }
     if (!whole) {
 #pragma unroll
@@ -232,20 +235,21 @@ __device__ __forceinline__ SlotWeights slot_softmax(const v4i (&d)[4], const H (
     float p[4], pw[4];
 #pragma unroll
     for (int tg = 0; tg < 4; ++tg) {
-        p[tg] = __builtin_amdgcn_exp2f(s[tg] * scale - base);
+        p[tg] = __builtin_amdgcn_exp2f(fmaf(s[tg], scale, -base));
         pw[tg] = p[tg] * value_scale(h[tg]);           // >= 0: scales are non-negative
     }
     r.psum = (p[0] + p[1]) + (p[2] + p[3]);
     r.osum = 0.f;
 #pragma unroll
-    for (int tg = 0; tg < 4; ++tg) r.osum = value_offset(h[tg]) * p[tg] + r.osum;
+    for (int tg = 0; tg < 4; ++tg) r.osum = fmaf(value_offset(h[tg]), p[tg], r.osum);
     const float top = fmaxf(row_max16(fmaxf(fmaxf(pw[0], pw[1]), fmaxf(pw[2], pw[3]))), 1e-30f);
     const float inv = kDigitMax * __builtin_amdgcn_rcpf(top);
     r.wscale = top * (1.0f / kDigitMax);
 #pragma unroll
     for (int tg = 0; tg < 4; ++tg) {
-        // 2^23 + v has v in its low bits, rounded to nearest even
-        const uint32_t v = __float_as_uint(pw[tg] * inv + 8388608.0f) - 0x4B000000u;
+        // 2^23 + v has v in its low bits, rounded to nearest even; the reciprocal
+        // is good to 2^-23, so v ends at most one above 2^22
+        const uint32_t v = __float_as_uint(fmaf(pw[tg], inv, 8388608.0f)) - 0x4B000000u;
         r.w[tg] = (v + 0x00808080u) ^ 0x00808080u;
     }
     return r;
@@ -268,9 +272,4 @@ __device__ __forceinline__ v4i load_values(uint32_t b_lane) {
     const uint64_t lo = lds_tr8(b_lane), hi = lds_tr8(b_lane + 32 * kRowT);
     return v4i{(int)(uint32_t)lo, (int)(uint32_t)(lo >> 32), (int)(uint32_t)hi, (int)(uint32_t)(hi >> 32)};
 }
-// The digit sums of a slot and channel as one number.
-__device__ __forceinline__ float digit_sum(const v4i& d) {
-    return (float)d[2] * 65536.0f + (float)((d[1] << 8) + d[0]);
-}
-
 }  // namespace dq

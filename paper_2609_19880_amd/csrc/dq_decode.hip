@@ -494,14 +494,12 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
     // softmax state of slot l / 16 of each group of four query heads: the
     // maximum the same in the 16 lanes, the sums in parts; the P . v sums of
     // channel 64 s + 16 cb + l % 16 in acc[s][hg][cb]
-    float m_run[HG], l_run[HG], o_run[HG], qs_l[HG], qsum_l[HG], acc[2][HG][4];
+    float m_run[HG], l_run[HG], o_run[HG], acc[2][HG][4];
 #pragma unroll
     for (int hg = 0; hg < HG; ++hg) {
         m_run[hg] = -INFINITY;
         l_run[hg] = 0.f;
         o_run[hg] = 0.f;
-        qs_l[hg] = qscale[4 * hg + slot] * a.q_sign;
-        qsum_l[hg] = qsum[4 * hg + slot] * a.q_sign;
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb) acc[0][hg][cb] = acc[1][hg][cb] = 0.f;
     }
@@ -538,7 +536,9 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
         const float* qm = qmu + (t_base / DQ_MEAN_WINDOW - w0) * GP + lq;
 #pragma unroll
         for (int hg = 0; hg < HG; ++hg) {
-            sw[hg] = slot_softmax(d[hg], hd, qs_l[hg], qsum_l[hg], qm[4 * hg], a.scale_log2, left, whole, m_run[hg]);
+            const int g = 4 * hg + lq;
+            sw[hg] = slot_softmax(d[hg], hd, qscale[g] * a.q_sign, qsum[g] * a.q_sign, qm[4 * hg], a.scale_log2, left,
+                                  whole, m_run[hg]);
             store_weights(wbase + L.plimb + 16 * l16 + 4 * lq + hg * (kTile * 16), sw[hg].w);
         }
     };
@@ -762,8 +762,8 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
         score_tile(klev, hk0, hv0, t_base, sw);
 #pragma unroll
         for (int hg = 0; hg < HG; ++hg) {
-            l_run[hg] = l_run[hg] * sw[hg].corr + sw[hg].psum;
-            o_run[hg] = o_run[hg] * sw[hg].corr + sw[hg].osum;
+            l_run[hg] = fmaf(l_run[hg], sw[hg].corr, sw[hg].psum);
+            o_run[hg] = fmaf(o_run[hg], sw[hg].corr, sw[hg].osum);
 #pragma unroll
             for (int cb = 0; cb < 4; ++cb) {
                 acc[0][hg][cb] *= sw[hg].corr;
@@ -778,7 +778,7 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
         }
 
         wave_sync();   // the weight rows are read by other lanes
-        value_tile(vlev, wbase, [&](int sl, int hg, int cb, float f) { acc[sl][hg][cb] += f * sw[hg].wscale; });
+        value_tile(vlev, wbase, [&](int sl, int hg, int cb, float f) { acc[sl][hg][cb] = fmaf(f, sw[hg].wscale, acc[sl][hg][cb]); });
         wave_sync();   // the next tile rewrites the pair arrays over the value tile
     }
     if (__any(corrupt) && lane == 0 && a.status) atomicOr(a.status, DQ_STATUS_CORRUPT);

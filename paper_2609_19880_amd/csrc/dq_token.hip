@@ -321,7 +321,7 @@ __device__ __forceinline__ float row_first(float v) { return __uint_as_float(dpp
 // corr, and the row sums of psum and osum; then on to the next head.
 __device__ __forceinline__ void push_state(const SlotWeights& sw, float m, bool first, float& m_vec, float& l_vec,
                                            float& o_vec) {
-    const float l = l_vec * sw.corr + row_sum16(sw.psum), o = o_vec * sw.corr + row_sum16(sw.osum);
+    const float l = fmaf(l_vec, sw.corr, row_sum16(sw.psum)), o = fmaf(o_vec, sw.corr, row_sum16(sw.osum));
     m_vec = row_next(first ? m : m_vec);
     l_vec = row_next(first ? l : l_vec);
     o_vec = row_next(first ? o : o_vec);
@@ -579,7 +579,7 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
                 const float corr_l = kx[buf * GS + pslot], scale_l = kx[2 * GS + buf * GS + pslot];
                 value_head(vlev, wt, [&](int sl, int hg, int cb, float f) {
                     v8f tv = acc[sl][hg][cb];
-                    tv[0] = tv[0] * corr_l + f * scale_l;
+                    tv[0] = fmaf(f, scale_l, tv[0] * corr_l);
                     acc[sl][hg][cb] = rot1(tv);
                 });
                 wave_sync();   // the next head rewrites the value rows
@@ -750,7 +750,7 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
             wave_sync();   // the weight rows are read by other lanes
             value_head(vlev, wbase + L.plimb, [&](int sl, int hg, int cb, float f) {
                 v8f t = acc[sl][hg][cb];
-                t[0] = t[0] * sw[hg].corr + f * sw[hg].wscale;
+                t[0] = fmaf(f, sw[hg].wscale, t[0] * sw[hg].corr);
                 acc[sl][hg][cb] = rot1(t);
             });
             wave_sync();   // the next head rewrites the weight and value rows
