@@ -2,14 +2,14 @@
 // attention over them (Sec. 4.5 "Decoding", App. A Eq. fold-key/fold-value).
 //
 // decode_attention is split-K over context chunks:
-//  * attn_partial: one workgroup per (chunk, KV head, sequence), up to 12
+//  * attn_partial: one workgroup per (chunk, KV head, sequence), up to 16
 //    wavefronts.  The workgroup stages the rANS tables in LDS and rotates the
 //    G query heads that share the KV head (one FWHT in LDS).  Each wavefront
 //    then takes 64-token tiles, one token per lane: the lane stages its key
-//    and value payloads in LDS and runs the two rANS chains interleaved.  Key
-//    levels feed the q . k products on the matrix cores as they are decoded
-//    (Eq. fold-key); value levels wait in registers until the tile's softmax
-//    weights are known, then meet them on the matrix cores (Eq. fold-value).
+//    and value payloads in LDS and runs the two rANS chains interleaved.  The
+//    levels wait in registers; after the decode the key levels meet the query on
+//    the matrix cores (Eq. fold-key), and the value levels the tile's softmax
+//    weights (Eq. fold-value).
 //    Online softmax state stays per wavefront; the wavefronts are merged in
 //    LDS at the end.
 //  * attn_merge: log-sum-exp merge of the chunk partials per (sequence, query
@@ -275,6 +275,12 @@ __device__ __forceinline__ uint32_t spread2(uint32_t x) {
     return u & 0x03030303u;
 }
 
+// What bounds it: the rANS steps' table reads, whose lanes hit arbitrary LDS banks
+// (LDS is active 87 % of the time at 16 x 32768 tokens, G = 4).  There the products
+// hide behind the decode (339 us with the 4x4x4 products during the decode, 334 us
+// with 16x16x64 products after it); with G = 8 they don't, and 16 times fewer
+// product instructions and a quarter of the reductions count (32 x 32768 tokens,
+// 48- and 32-byte records: 886 -> 761 us; 1 x 130873, 48 bytes: 106.6 -> 102 us).
 // FIXED: the fixed-width comparator at matched storage; levels come straight
 // from the record words (no tables, no byte pairs, no rANS state).
 // WMAX: the wavefront bound of the instantiation (max_waves, or 8).

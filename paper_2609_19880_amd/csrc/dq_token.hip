@@ -23,10 +23,11 @@
 // [dword row][lane] so that every lane stays in its own bank; a ninth row
 // repeats row 0 so that two consecutive dwords are always rows r, r + 1.  A
 // decode step reads the two dwords holding its byte position and takes the
-// next 16 bits with a funnel shift and a byte permute.  Every 8 steps a lane
-// whose ring holds fewer than 20 bytes from its position writes its next
+// next 16 bits with a funnel shift and a byte permute; with two 2^8-entry tables
+// a step takes at most one byte and one read serves four steps.  Every 8 steps (16
+// with such tables) a lane whose ring holds fewer than 20 bytes from its position writes its next
 // chunk (held in registers since the previous refill) and loads the one
-// after, and does so once more in the rare case that it is still short: 8
+// after, and does so once more in the rare case that it is still short: those
 // steps read at most 16 bytes, and their two-dword windows reach at most 19
 // bytes past the position.  A chunk is written only while the ring is short,
 // so the chunk four back that it replaces lies wholly behind the position
@@ -241,7 +242,7 @@ __device__ __forceinline__ void refill1(uint32_t pb, uint32_t& nc, uint32_t& thr
 // The 128 steps of one KV head on a single chain (the wavefront decodes only
 // the keys or only the values of its tile): per step pair the ring dwords
 // and the first table word, then the second table word, each awaited before
-// it is used; the ring is refilled after every block of 8 steps, whose last
+// it is used; the ring is refilled after every block of 8 steps (W4: 16), whose last
 // reads come after the refill's writes.  level(grp, word) takes the packed
 // levels of four steps; no read of the chain is in flight when it is called for
 // the last group of a block.  W4: four steps per ring read and blocks of 16
@@ -342,6 +343,9 @@ __device__ __forceinline__ v8f rot1(const v8f& v) { return v8f{v[1], v[2], v[3],
 // SPLIT: one tile per pair of wavefronts, keys and values decoded by
 // different wavefronts (chunks of at most nw / 2 tiles: small batches).
 // W4: both tables have p = 8 (see tfinish4).
+// What bounds it: LDS (ring, table and row reads) and the vector unit nearly alike.
+// 16 x 32768 tokens, 8 KV heads, G = 4, p = 8: 469 us with the 4x4x4 products, 434
+// with the 16x16x64 ones, 386 with W4; 1 x 4096 tokens (SPLIT): 106.5, 96 and 87.
 template <uint32_t LUTV, bool PAGED, int HG, bool SPLIT, bool W4>
 __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) void attn_token_kernel(TokArgs a) {
     constexpr int GS = 4 * HG;                 // query-head slots per KV head
@@ -918,8 +922,8 @@ int launch_token_kernel(const TokArgs& a, dim3 grid, int nw, hipStream_t stream)
 
 template <int HG>
 int launch_token_hg(const TokArgs& a, dim3 grid, int nw, bool shared, hipStream_t stream) {
-    // four steps per ring read where both tables have p = 8 (16 x 32768 tokens:
-    // see the kernel's figures), else two
+    // four steps per ring read where both tables have p = 8, whose steps take at
+    // most one byte, else two (16 x 32768 tokens at p = 8: 386 and 434 us)
     const bool w4 = a.tk.p == 8 && a.tv.p == 8;
     switch (shared ? 0u : (uint32_t)a.L.lut_v) {
         case 0:
