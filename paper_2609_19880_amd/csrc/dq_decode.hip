@@ -276,7 +276,7 @@ __device__ __forceinline__ uint32_t spread2(uint32_t x) {
 }
 
 // What bounds it: the rANS steps' table reads, whose lanes hit arbitrary LDS banks
-// (LDS is active 87 % of the time at 16 x 32768 tokens, G = 4).  There the products
+// (LDS is active 86 % of the time, vector issue 82 % at 16 x 32768 tokens, G = 4).  There the products
 // hide behind the decode (339 us with the 4x4x4 products during the decode, 334 us
 // with 16x16x64 products after it); with G = 8 they don't, and 16 times fewer
 // product instructions and a quarter of the reductions count (32 x 32768 tokens,

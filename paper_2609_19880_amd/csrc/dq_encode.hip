@@ -893,8 +893,8 @@ __host__ __device__ constexpr int enc_waves(int vpl, int mb, bool tok, int jm) {
 }
 
 // What bounds it: vector instructions (twelve steps of the search, then the coder's
-// 128 serial steps per lane); memory is idle.  Keys and values together, 4 x 8192
-// tokens of 8 heads, 36-byte records (6 levels): 2398 us when every step of the
+// 128 serial steps per lane); memory, register spills included, moves 0.35 TB/s.
+// Keys and values together, 4 x 8192 tokens of 8 heads, 36-byte records (6 levels): 2398 us when every step of the
 // search assigned every level anew in 64 bits, 792 with the folded drift;
 // 48- and 32-byte records, 2 x 4096: 981 and 320; per token, 4 x 8192: 2936 and
 // 777; 4 x 128, with key means and grids that fill the CUs: 475 and 63.

@@ -343,7 +343,7 @@ __device__ __forceinline__ v8f rot1(const v8f& v) { return v8f{v[1], v[2], v[3],
 // SPLIT: one tile per pair of wavefronts, keys and values decoded by
 // different wavefronts (chunks of at most nw / 2 tiles: small batches).
 // W4: both tables have p = 8 (see tfinish4).
-// What bounds it: LDS (ring, table and row reads) and the vector unit nearly alike.
+// What bounds it: vector issue (93 % at p = 8; LDS is active 64 % of the time).
 // 16 x 32768 tokens, 8 KV heads, G = 4, p = 8: 469 us with the 4x4x4 products, 434
 // with the 16x16x64 ones, 386 with W4; 1 x 4096 tokens (SPLIT): 106.5, 96 and 87.
 template <uint32_t LUTV, bool PAGED, int HG, bool SPLIT, bool W4>
