@@ -186,7 +186,8 @@ __device__ __forceinline__ uint32_t dfinish(uint32_t& X, uint32_t& Q, int p3, ui
     const uint32_t y = __umul24(ex, X >> p3) + ey;
     const uint32_t s = (((uint32_t)__builtin_clz(y) - 3u) & 24u) ^ 29u;
     X = __builtin_amdgcn_alignbit(y, r, s);
-    asm("v_mad_i32_i24 %0, %1, -16, %2" : "=v"(Q) : "v"(s), "v"(Q));
+    // (in place: the compiler does not keep assembly clear of products in flight)
+    asm("v_mad_i32_i24 %0, %1, -16, %0" : "+v"(Q) : "v"(s));
     return ex;
 }
 
@@ -269,10 +270,10 @@ constexpr uint32_t kLutVOffset = 8u << 12;   // value table when it differs from
 // payload byte x, one per byte: x | (x >> 4) << 16 puts the two nibbles in
 // the two halves, | << 6 brings bits 2-3 of each half up to its second byte.
 __device__ __forceinline__ uint32_t spread2(uint32_t x) {
-    uint32_t t, u;
-    asm("v_lshl_or_b32 %0, %1, 16, %2" : "=v"(t) : "v"(x >> 4), "v"(x));
-    asm("v_lshl_or_b32 %0, %1, 6, %1" : "=v"(u) : "v"(t));
-    return u & 0x03030303u;
+    uint32_t t = x >> 4;
+    asm("v_lshl_or_b32 %0, %0, 16, %1" : "+v"(t) : "v"(x));
+    asm("v_lshl_or_b32 %0, %0, 6, %0" : "+v"(t));
+    return t & 0x03030303u;
 }
 
 // What bounds it: the rANS steps' table reads, whose lanes hit arbitrary LDS banks

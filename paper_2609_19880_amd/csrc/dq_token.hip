@@ -115,6 +115,12 @@ struct TokArgs {
 // awaited one, and operations the compiler adds in between only make the wait
 // stricter).  The finish steps return the table words (levels in their top
 // bytes).
+//
+// Arithmetic in inline assembly works in place (its result takes the register of
+// an operand).  The compiler keeps ordinary instructions clear of matrix products
+// in flight (8 wait states before a register of their result is written), but not
+// instructions in assembly: a fresh result register could be one that a product
+// issued just before still writes.
 struct TChain {
     uint32_t X, pb, w;
     uint64_t rr, e;      // pending: ring dwords (lo, hi), table word
@@ -122,8 +128,8 @@ struct TChain {
 
 template <uint32_t LUT_OFF>
 __device__ __forceinline__ void tissue_a(TChain& c, uint32_t ring_lane, uint32_t mask8) {
-    uint32_t addr;
-    asm("v_lshl_add_u32 %0, %1, 8, %2" : "=v"(addr) : "v"(__builtin_amdgcn_ubfe(c.pb, 5, 3)), "v"(ring_lane));
+    uint32_t addr = __builtin_amdgcn_ubfe(c.pb, 5, 3);
+    asm("v_lshl_add_u32 %0, %0, 8, %1" : "+v"(addr) : "v"(ring_lane));
     asm volatile("ds_read2st64_b32 %0, %2 offset1:1\n\t"
                  "ds_read_b64 %1, %3 offset:%4"
                  : "=&v"(c.rr), "=&v"(c.e)
@@ -150,21 +156,23 @@ __device__ __forceinline__ uint32_t tfinish_a(TChain& c, int p3, uint32_t& sh) {
     const uint32_t lo = (uint32_t)c.rr, hi = (uint32_t)(c.rr >> 32);
     const uint32_t w = __builtin_amdgcn_perm(0u, __builtin_amdgcn_alignbit(hi, lo, c.pb), 0x00010203u);
     const uint32_t ea = (uint32_t)c.e;
-    const uint32_t y = __umul24(ea, c.X >> p3) + (uint32_t)(c.e >> 32);
+    uint32_t y = __umul24(ea, c.X >> p3) + (uint32_t)(c.e >> 32);
     sh = (uint32_t)__builtin_clz(y) & 24u;
     const uint32_t q = w >> (sh ^ 29u);
-    asm("v_lshl_or_b32 %0, %1, %2, %3" : "=v"(c.X) : "v"(y), "v"(sh), "v"(q));
+    asm("v_lshl_or_b32 %0, %0, %1, %2" : "+v"(y) : "v"(sh), "v"(q));
+    c.X = y;
     c.w = w << sh;
     return ea;
 }
 
 __device__ __forceinline__ uint32_t tfinish_b(TChain& c, int p3, uint32_t sha) {
     const uint32_t eb = (uint32_t)c.e;
-    const uint32_t y = __umul24(eb, c.X >> p3) + (uint32_t)(c.e >> 32);
+    uint32_t y = __umul24(eb, c.X >> p3) + (uint32_t)(c.e >> 32);
     const uint32_t sh = (uint32_t)__builtin_clz(y) & 24u;
     const uint32_t q = c.w >> (sh ^ 29u);
-    asm("v_lshl_or_b32 %0, %1, %2, %3" : "=v"(c.X) : "v"(y), "v"(sh), "v"(q));
-    asm("v_add3_u32 %0, %1, %2, %3" : "=v"(c.pb) : "v"(c.pb), "v"(sha), "v"(sh));
+    asm("v_lshl_or_b32 %0, %0, %1, %2" : "+v"(y) : "v"(sh), "v"(q));
+    c.X = y;
+    asm("v_add3_u32 %0, %0, %1, %2" : "+v"(c.pb) : "v"(sha), "v"(sh));
     return eb;
 }
 
@@ -180,12 +188,13 @@ __device__ __forceinline__ uint32_t tfinish4(TChain& c, int p3, uint32_t& shp) {
         c.w = __builtin_amdgcn_perm(0u, __builtin_amdgcn_alignbit(hi, lo, c.pb), 0x00010203u);
     }
     const uint32_t e = (uint32_t)c.e;
-    const uint32_t y = __umul24(e, c.X >> p3) + (uint32_t)(c.e >> 32);
+    uint32_t y = __umul24(e, c.X >> p3) + (uint32_t)(c.e >> 32);
     const uint32_t sh = (uint32_t)__builtin_clz(y) & 24u;
     const uint32_t q = c.w >> (sh ^ 29u);
-    asm("v_lshl_or_b32 %0, %1, %2, %3" : "=v"(c.X) : "v"(y), "v"(sh), "v"(q));
+    asm("v_lshl_or_b32 %0, %0, %1, %2" : "+v"(y) : "v"(sh), "v"(q));
+    c.X = y;
     if (U < 3) c.w <<= sh;
-    if (U & 1) asm("v_add3_u32 %0, %1, %2, %3" : "=v"(c.pb) : "v"(c.pb), "v"(shp), "v"(sh));
+    if (U & 1) asm("v_add3_u32 %0, %0, %1, %2" : "+v"(c.pb) : "v"(shp), "v"(sh));
     shp = sh;
     return e;
 }

@@ -1,11 +1,11 @@
-"""Static check of the kernels' hand-issued LDS reads (CPU only: needs hipcc).
+"""Static checks of the kernels' inline assembly (CPU only: needs hipcc), on the
+gfx950 device assembly of every instantiation, built with the library's own flags.
 
-The decode loops of attn_partial_kernel and attn_token_kernel issue their
+Hand-issued LDS reads.  The decode loops of attn_partial_kernel and attn_token_kernel issue their
 table, pair and query reads in inline assembly and wait for them with their
 own `s_waitcnt lgkmcnt(N)`, so that the key and value chains overlap.  The
 compiler sees neither the reads nor what they are waiting for: correctness
-rests on two facts about the code it emits, checked here on the gfx950
-device assembly of every instantiation, built with the library's own flags:
+rests on two facts about the code it emits:
 
 * no instruction reads or writes the destination registers of such a read
   (a register copy, a spill, reuse for another value) before a wait covers
@@ -14,6 +14,14 @@ device assembly of every instantiation, built with the library's own flags:
   issued after it (LDS operations of a wavefront complete in order; scalar
   loads, which also count, only make a wait stricter), and no branch or
   label lies between a read and its wait.
+
+Wait states.  The compiler puts the wait states that the hardware asks for
+between ordinary instructions, but does not look into assembly:
+
+* arithmetic in assembly must not read or write a register of a matrix product's
+  result within the product's latency (8 wait states after the 16x16x64 int8 and
+  16x16x32 bf16 products, the least the compiler itself leaves), unless an
+  ordinary instruction, which the compiler keeps clear, has written it in between.
 """
 
 import os
@@ -107,6 +115,41 @@ def check_function(body):
     return problems, nreads
 
 
+PRODUCT_WAIT = 8
+
+
+def _operands(ops):
+    return re.split(r",(?![^\[]*\])", ops)
+
+
+def check_wait_states(body):
+    """Wait-state problems around inline assembly in one function's lines."""
+    problems, products = [], []    # products in flight: (registers of the result, wait state of issue)
+    in_asm, now = False, 0
+    for no, line in enumerate(body):
+        s = line.strip()
+        if s in (";;#ASMSTART", ";;#ASMEND"):
+            in_asm = s == ";;#ASMSTART"
+            continue
+        if not line[:1].isspace() or not s or s[0] in ";.":
+            continue
+        mn, _, ops = s.split(";")[0].strip().partition(" ")
+        if mn == "s_nop":
+            now += int(ops, 0) + 1
+            continue
+        products = [p for p in products if now - p[1] - 1 < PRODUCT_WAIT]
+        if mn.startswith("v_mfma"):
+            products.append((_regs(_operands(ops)[0]), now))
+        elif mn.startswith("v_"):
+            for dest, at in products:
+                if in_asm and dest & _regs(ops):
+                    problems.append((no, f"{now - at - 1} wait states after a product", s))
+            written = _regs(_operands(ops)[0])
+            products = [(dest - written, at) for dest, at in products]
+        now += 1
+    return problems
+
+
 def _fn(lines):
     return [l if l.split(";")[0].strip().endswith(":") else "\t" + l for l in lines]
 
@@ -134,23 +177,50 @@ def test_checker_catches_planted_mistakes():
     assert ok(read + ["v_mov_b32 v9, v4", "s_waitcnt lgkmcnt(0)"] + use)
 
 
-@pytest.mark.timeout(600)
-def test_inline_lds_reads_are_waited_for(tmp_path):
+def test_wait_state_checker_catches_planted_mistakes():
+    mfma = ["v_mfma_i32_16x16x64_i8 v[50:53], v[60:63], v[140:143], v[26:29]"]
+    fill = ["v_mov_b32 v9, v8"]
+    in_asm = lambda x: [";;#ASMSTART", x, ";;#ASMEND"]
+    ok = lambda lines: check_wait_states(_fn(lines)) == []
+    late = in_asm("v_lshl_or_b32 v53, v0, v57, v1")
+    assert not ok(mfma + fill * 7 + late)
+    assert ok(mfma + fill * 8 + late)
+    assert ok(mfma + fill + ["s_nop 6"] + late)
+    assert not ok(mfma + fill + ["s_nop 5"] + late)
+    assert not ok(mfma + in_asm("v_add3_u32 v1, v0, v51, v1"))                  # a read
+    assert not ok(mfma + ["s_cbranch_scc1 .LBB0_2", ".LBB0_3:"] + late)         # across a branch not taken
+    # other registers; a register written by an ordinary instruction since; ordinary instructions alone
+    assert ok(mfma + in_asm("v_lshl_or_b32 v54, v0, v57, v1"))
+    assert ok(mfma + fill * 3 + ["v_mad_u32_u24 v53, v1, v2, v3"] + in_asm("v_lshl_or_b32 v53, v53, v57, v1"))
+    assert ok(mfma + ["v_mov_b32 v53, v1"])
+
+
+@pytest.fixture(scope="module")
+def device_code(tmp_path_factory):
+    """{source: [(function, lines)]} of the device code."""
     import __graft_entry__ as ge
 
     if not os.path.exists(ge.HIPCC) and shutil.which("hipcc") is None:
         pytest.skip("hipcc not available")
     flags = [f for f in ge.FLAGS if f not in ("-shared", "-fPIC")]
-    procs = {}
-    for src in ("dq_decode.hip", "dq_token.hip"):
-        out = str(tmp_path / (src + ".s"))
+    tmp, procs = tmp_path_factory.mktemp("asm"), {}
+    for src in (s for s in ge.SOURCES if s.endswith(".hip")):
+        out = str(tmp / (src + ".s"))
         cmd = [ge.HIPCC, *flags, "--cuda-device-only", "-S", os.path.join(ge.CSRC, src), "-o", out]
         procs[src] = (subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT), out)
-    reads = {}
+    code = {}
     for src, (p, out) in procs.items():
         log = p.communicate()[0]
         assert p.returncode == 0, log.decode(errors="replace")[-2000:]
-        for name, body in _functions(open(out).read()):
+        code[src] = list(_functions(open(out).read()))
+    return code
+
+
+@pytest.mark.timeout(600)
+def test_inline_lds_reads_are_waited_for(device_code):
+    reads = {}
+    for src in ("dq_decode.hip", "dq_token.hip"):
+        for name, body in device_code[src]:
             problems, n = check_function(body)
             assert problems == [], (name, problems[:5])
             reads[name] = n
@@ -161,3 +231,12 @@ def test_inline_lds_reads_are_waited_for(tmp_path):
     # (the fixed-width one does not decode)
     assert sum(n > 0 for n in partial) >= len(partial) - 1
     assert all(n > 0 for n in token)
+
+
+@pytest.mark.timeout(600)
+def test_inline_assembly_keeps_wait_states(device_code):
+    for src, functions in device_code.items():
+        assert functions
+        for name, body in functions:
+            problems = check_wait_states(body)
+            assert problems == [], (src, name, problems[:5])
