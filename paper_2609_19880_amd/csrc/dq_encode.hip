@@ -239,12 +239,18 @@ __device__ __forceinline__ double wave_ext_nn(double v) {
     return lane63(v);
 }
 
+// The two wait states between an arithmetic result and a lane swap that reads it,
+// for results of assembly, which the compiler does not count (max_nn, min_nn).
+__device__ __forceinline__ void settle(double& a, double& b) { asm("s_nop 1" : "+v"(a), "+v"(b)); }
+
 // Wavefront minimum and maximum of non-NaN doubles as one reduction of
 // max(-x) and max(x) (the sign of a zero result is not kept).
 __device__ __forceinline__ void wave_minmax_nn(double& mn, double& mx) {
     double a = join(lo32(mn), hi32(mn) ^ 0x80000000u), b = mx;
+    settle(a, b);
     swap_halves(a, b);
     double v = max_nn(a, b), t = v;
+    settle(v, t);
     swap_rows(v, t);
     v = max_nn(v, t);
     v = max_nn(v, dpp_copy<0xB1, 0xF>(v));

@@ -21,7 +21,9 @@ between ordinary instructions, but does not look into assembly:
 * arithmetic in assembly must not read or write a register of a matrix product's
   result within the product's latency (8 wait states after the 16x16x64 int8 and
   16x16x32 bf16 products, the least the compiler itself leaves), unless an
-  ordinary instruction, which the compiler keeps clear, has written it in between.
+  ordinary instruction, which the compiler keeps clear, has written it in between;
+* a lane swap (v_permlane16_swap, v_permlane32_swap) must not follow arithmetic in
+  assembly whose result it exchanges by fewer than 2 wait states.
 """
 
 import os
@@ -116,6 +118,7 @@ def check_function(body):
 
 
 PRODUCT_WAIT = 8
+SWAP_WAIT = 2
 
 
 def _operands(ops):
@@ -124,7 +127,8 @@ def _operands(ops):
 
 def check_wait_states(body):
     """Wait-state problems around inline assembly in one function's lines."""
-    problems, products = [], []    # products in flight: (registers of the result, wait state of issue)
+    problems = []
+    products, inline = [], []      # products in flight, results of assembly: (registers, wait state of issue)
     in_asm, now = False, 0
     for no, line in enumerate(body):
         s = line.strip()
@@ -138,14 +142,22 @@ def check_wait_states(body):
             now += int(ops, 0) + 1
             continue
         products = [p for p in products if now - p[1] - 1 < PRODUCT_WAIT]
+        inline = [p for p in inline if now - p[1] - 1 < SWAP_WAIT]
         if mn.startswith("v_mfma"):
             products.append((_regs(_operands(ops)[0]), now))
         elif mn.startswith("v_"):
             for dest, at in products:
                 if in_asm and dest & _regs(ops):
                     problems.append((no, f"{now - at - 1} wait states after a product", s))
-            written = _regs(_operands(ops)[0])
+            swap = mn.startswith(("v_permlane16_swap", "v_permlane32_swap"))
+            for dest, at in inline:
+                if swap and dest & _regs(ops):
+                    problems.append((no, f"{now - at - 1} wait states after its operand", s))
+            written = _regs(ops if swap else _operands(ops)[0])
             products = [(dest - written, at) for dest, at in products]
+            inline = [(dest - written, at) for dest, at in inline]
+            if in_asm:
+                inline.append((written, now))
         now += 1
     return problems
 
@@ -193,6 +205,12 @@ def test_wait_state_checker_catches_planted_mistakes():
     assert ok(mfma + in_asm("v_lshl_or_b32 v54, v0, v57, v1"))
     assert ok(mfma + fill * 3 + ["v_mad_u32_u24 v53, v1, v2, v3"] + in_asm("v_lshl_or_b32 v53, v53, v57, v1"))
     assert ok(mfma + ["v_mov_b32 v53, v1"])
+    # a swap of either operand after assembly, and of a register copied from it
+    top, swap = in_asm("v_max_f64 v[10:11], v[10:11], v[6:7]"), ["v_permlane32_swap_b32_e32 v8, v10"]
+    assert not ok(top + swap) and not ok(top + fill + swap)
+    assert not ok(top + fill + ["v_permlane16_swap_b32_e32 v11, v8"])
+    assert ok(top + fill * 2 + swap) and ok(top + ["s_nop 1"] + swap) and ok(top + in_asm("s_nop 1") + swap)
+    assert ok(top + ["v_mov_b32 v10, v3"] + swap) and ok(top + ["v_permlane32_swap_b32_e32 v8, v9"])
 
 
 @pytest.fixture(scope="module")
