@@ -594,7 +594,7 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
         uint32_t rr_;
         uint64_t ee_;
         if (tile < ntiles && role == 0) {
-            const uint32_t hk0 = rk[0], hv0 = rv[0];
+            const uint32_t hk0 = valid ? rk[0] : 0u, hv0 = valid ? rv[0] : 0u;     // (as below)
             uint32_t xk = rk[1] << 3;
             build_pairs(rk, CWk, smem + pk_lane);
             asm volatile("" ::: "memory");
@@ -677,8 +677,10 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
         }
 
         // ---- both records of the lane's token -> headers + byte-pair arrays
-        const uint32_t hk0 = rk[0], xk0 = rk[1] << 3;
-        const uint32_t hv0 = rv[0], xv0 = rv[1] << 3;
+        //      (rows past the length may hold anything, and a weight of 0 does not
+        //      clear an infinity or NaN: their scale and offset are taken as zeros)
+        const uint32_t hk0 = valid ? rk[0] : 0u, xk0 = rk[1] << 3;
+        const uint32_t hv0 = valid ? rv[0] : 0u, xv0 = rv[1] << 3;
         uint32_t ck[FIXED ? 9 : 1], cv[FIXED ? 9 : 1];   // this tile's fixed-width records
         if (FIXED) {
 #pragma unroll

@@ -558,7 +558,7 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
             ch.X = c0.y << 3;
             if (W4) corrupt |= valid && (ch.X >> 3) < kRansL;   // (one byte a step needs a state from L on)
             ch.pb = 64;                             // payload starts at byte 8
-            if (!role) *LDS_PTR(v2u, kreg + L.hdr + 8 * lane) = v2u{c0.x, vh};
+            if (!role) *LDS_PTR(v2u, kreg + L.hdr + 8 * lane) = v2u{valid ? c0.x : 0u, valid ? vh : 0u};
             asm volatile("" ::: "memory");
         }
         for (int h = 0; h < Hkv; ++h) {
@@ -657,7 +657,9 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
         cv.X = v0.y << 3;
         if (W4) corrupt |= valid && min(ck.X, cv.X) < kRansL << 3;   // (one byte a step needs a state from L on)
         ck.pb = cv.pb = 64;                         // payload starts at byte 8
-        *LDS_PTR(v2u, wbase + L.hdr + 8 * lane) = v2u{k0.x, v0.x};
+        // (rows past the length may hold anything, and a weight of 0 does not clear an
+        // infinity or NaN: their scale and offset are taken as zeros)
+        *LDS_PTR(v2u, wbase + L.hdr + 8 * lane) = v2u{valid ? k0.x : 0u, valid ? v0.x : 0u};
         // the rings are read back by this lane only: order the reads after
         // the writes (LDS keeps a wavefront's accesses in order)
         asm volatile("" ::: "memory");
