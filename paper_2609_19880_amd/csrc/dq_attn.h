@@ -101,7 +101,9 @@ __device__ __forceinline__ uint64_t lds_tr8(uint32_t off) {
 // (With v_mfma_i32_4x4x4_16b_i8 on the levels as they appear, a lane held all
 // four slots of its token: 96 products per tile instead of 8, four times the
 // reductions, and 32 reads of query digits.)
-constexpr int kRowT = 80;                 // bytes per row of a level tile (64 channels + pad)
+constexpr int kRowT = 80;                 // bytes per row of a level tile (64 channels, then 16 bytes of row padding)
+constexpr int kRowHdr = 64;               // the padding holds the headers of the row's token (no LDS of their own: it
+                                          // would cost wavefronts); 16 rows' headers fall in different banks
 constexpr int kQRow = 64;                 // bytes per row of a query-digit tile
 constexpr int kQTile = 16 * kQRow;        // query digits of a group's 16 rows, one 64-channel slice
 constexpr int kColGroup = 16 * kRowT;     // 16 token rows of a level tile

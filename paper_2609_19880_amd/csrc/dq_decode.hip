@@ -111,13 +111,13 @@ struct AttnLayout {
     int waves;          // first wavefront region
     int wave_stride;
     int pk, pv;             // key / value byte-pair arrays: [position][64 lanes] x 2 B
-    int vtile;              // [64 tokens][kRowT] level bytes of a 64-channel slice, over the pair arrays
+    int vtile;              // [64 tokens][kRowT] level bytes of a 64-channel slice, over the pair arrays, and (kRowHdr)
+                            // float4: scale and offset of the key and of the value
     int plimb;              // [HG][64 tokens][16] weight digits: byte 4 slot + digit (digit 3: zero)
-    int hdr;                // [64 tokens] float4: scale and offset of the key and of the value
     int total;
 };
 
-__host__ inline int align16(int v) { return (v + 15) & ~15; }
+__host__ constexpr int align16(int v) { return (v + 15) & ~15; }
 
 constexpr int kPairRow = 2 * kTile;     // bytes per payload position: one pair per lane
 constexpr int kPairSlack = 4096;         // LDS above the last array that a corrupt stream may read
@@ -517,8 +517,7 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
     auto score_tile = [&](const uint32_t (&klev)[kD / 4], uint32_t hk, uint32_t hv, int t_base, SlotWeights (&sw)[HG]) {
         const int ln = lane_now(), l16 = ln & 15, lq = ln >> 4;
         const uint32_t row_lane = wbase + L.vtile + ln * kRowT;             // this lane's token row
-        const uint32_t hdr = wbase + L.hdr;
-        *LDS_PTR(v4f, hdr + 16 * ln) = v4f{half_lo(hk), half_hi(hk), half_lo(hv), half_hi(hv)};
+        *LDS_PTR(v4f, row_lane + kRowHdr) = v4f{half_lo(hk), half_hi(hk), half_lo(hv), half_hi(hv)};
         v4i d[HG][4];
 #pragma unroll
         for (int hg = 0; hg < HG; ++hg)
@@ -535,7 +534,7 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
         float4 hd[4];
 #pragma unroll
         for (int tg = 0; tg < 4; ++tg) {
-            const v4f v = *LDS_PTR(v4f, hdr + 16 * l16 + tg * 256);
+            const v4f v = *LDS_PTR(v4f, wbase + L.vtile + kRowHdr + l16 * kRowT + tg * kColGroup);
             hd[tg] = float4{v.x, v.y, v.z, v.w};
         }
         const int left = T - t_base - l16;
@@ -1381,7 +1380,7 @@ __global__ void residual_commit_kernel(int32_t* __restrict__ seq_lens, int32_t* 
 
 // Record length in dwords of the instantiation that serves (Ck, Cv); 0 = the
 // general kernel.
-int compiled_rw(int Ck, int Cv) {
+constexpr int compiled_rw(int Ck, int Cv) {
     const int p = (Ck % 4 || Cv % 4) ? 0 : rw_pair(Ck / 4, Cv / 4);
     switch (p) {
         case rw_pair(8, 8): case rw_pair(9, 9): case rw_pair(12, 12): case rw_pair(16, 16):
@@ -1393,9 +1392,9 @@ int compiled_rw(int Ck, int Cv) {
 }
 
 // LDS layout for given coding sizes; picks the largest wavefront count that fits.
-AttnLayout attn_layout(int pk, int pvb, int Ck, int Cv, int G, bool shared_lut, int rw) {
+constexpr AttnLayout attn_layout(int pk, int pvb, int Ck, int Cv, int G, bool shared_lut, int rw) {
     const int GP = G <= 4 ? 4 : 8, HG = GP / 4;
-    AttnLayout L;
+    AttnLayout L{};
     int off = 0;
     // key table at 0; a distinct value table at a fixed 32 KB (the DS offset field)
     L.lut_k = 0;
@@ -1420,8 +1419,7 @@ AttnLayout attn_layout(int pk, int pvb, int Ck, int Cv, int G, bool shared_lut, 
     L.pv = w + align16((Ck - kPayloadOffset) * kPairRow);
     L.vtile = w;                                   // reuses the pair arrays
     L.plimb = w + align16(kTile * kRowT);         // so do the weight digits
-    L.hdr = L.plimb + align16(HG * kTile * 16);
-    w = std::max(L.pv + align16((Cv - kPayloadOffset) * kPairRow), L.hdr + kTile * 16);
+    w = std::max(L.pv + align16((Cv - kPayloadOffset) * kPairRow), L.plimb + align16(HG * kTile * 16));
     L.wave_stride = w;
     int nw = (kMaxLds - kPairSlack - off) / w;
     if (nw > max_waves(HG, rw)) nw = max_waves(HG, rw);

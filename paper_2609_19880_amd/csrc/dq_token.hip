@@ -68,9 +68,9 @@ struct TokLayout {
     int waves;          // first wavefront region
     int wave_stride;
     int ring_k, ring_v; // per wavefront
-    int vtile;          // [64 tokens][kRowT]: levels of a 64-channel slice, keys then values
+    int vtile;          // [64 tokens][kRowT]: levels of a 64-channel slice, keys then values, and (kRowHdr) the
+                        // first words of the key and value records (fp16 scale, offset)
     int plimb;          // [HG][64 tokens][16]: weight digits, byte 4 slot + digit (digit 3 zero)
-    int hdr;            // [64 tokens]: the first words of the key and value records (fp16 scale, offset)
     int total;
 };
 
@@ -467,14 +467,14 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
     bool corrupt = false;
     const int ntiles = (min(a.chunk, T - start) + kTile - 1) / kTile;
 
-    // the weights of head h's groups from its digit sums (headers at hdr, in
-    // wavefront LDS), their digits to wt
-    auto score_head = [&](const v4i (&d)[HG][4], int h, uint32_t hdr, int t_base, uint32_t wt, SlotWeights (&sw)[HG],
+    // the weights of head h's groups from its digit sums (headers in the rows of
+    // this wavefront), their digits to wt
+    auto score_head = [&](const v4i (&d)[HG][4], int h, int t_base, uint32_t wt, SlotWeights (&sw)[HG],
                           float (&m)[HG]) {
         uint2 hd[4];
 #pragma unroll
         for (int tg = 0; tg < 4; ++tg) {
-            const v2u v = *LDS_PTR(v2u, hdr + 8 * l16 + tg * 128);
+            const v2u v = *LDS_PTR(v2u, wbase + L.vtile + kRowHdr + l16 * kRowT + tg * kColGroup);
             hd[tg] = uint2{v.x, v.y};
         }
         const int left = T - t_base - l16;
@@ -558,7 +558,7 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
             ch.X = c0.y << 3;
             if (W4) corrupt |= valid && (ch.X >> 3) < kRansL;   // (one byte a step needs a state from L on)
             ch.pb = 64;                             // payload starts at byte 8
-            if (!role) *LDS_PTR(v2u, kreg + L.hdr + 8 * lane) = v2u{valid ? c0.x : 0u, valid ? vh : 0u};
+            if (!role) *LDS_PTR(v2u, row_lane + kRowHdr) = v2u{valid ? c0.x : 0u, valid ? vh : 0u};
             asm volatile("" ::: "memory");
         }
         for (int h = 0; h < Hkv; ++h) {
@@ -576,7 +576,7 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
                 });
                 SlotWeights sw[HG];
                 float m[HG];
-                score_head(d, h, kreg + L.hdr, t_base, wt, sw, m);
+                score_head(d, h, t_base, wt, sw, m);
                 if (l16 == 0) {
                     kx[buf * GS + pslot] = sw[0].corr;
                     kx[2 * GS + buf * GS + pslot] = sw[0].wscale;
@@ -659,7 +659,7 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
         ck.pb = cv.pb = 64;                         // payload starts at byte 8
         // (rows past the length may hold anything, and a weight of 0 does not clear an
         // infinity or NaN: their scale and offset are taken as zeros)
-        *LDS_PTR(v2u, wbase + L.hdr + 8 * lane) = v2u{valid ? k0.x : 0u, valid ? v0.x : 0u};
+        *LDS_PTR(v2u, row_lane + kRowHdr) = v2u{valid ? k0.x : 0u, valid ? v0.x : 0u};
         // the rings are read back by this lane only: order the reads after
         // the writes (LDS keeps a wavefront's accesses in order)
         asm volatile("" ::: "memory");
@@ -758,7 +758,7 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
             __builtin_amdgcn_s_setprio(1);
             SlotWeights sw[HG];
             float m[HG];
-            score_head(d, h, wbase + L.hdr, t_base, wbase + L.plimb, sw, m);
+            score_head(d, h, t_base, wbase + L.plimb, sw, m);
 #pragma unroll
             for (int hg = 0; hg < HG; ++hg) push_state(sw[hg], m[hg], l16 == 0, m_vec[hg], l_vec[hg], o_vec[hg]);
             __builtin_amdgcn_s_setprio(0);
@@ -848,8 +848,8 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
     }
 }
 
-TokLayout tok_layout(int pk, int pv, bool shared_lut, int Hq, int Hkv, int chunk, int nw, int HG) {
-    TokLayout L;
+constexpr TokLayout tok_layout(int pk, int pv, bool shared_lut, int Hq, int Hkv, int chunk, int nw, int HG) {
+    TokLayout L{};
     int off = 0;
     L.lut_k = off;
     off += 8 << pk;
@@ -869,8 +869,7 @@ TokLayout tok_layout(int pk, int pv, bool shared_lut, int Hq, int Hkv, int chunk
     L.ring_v = kRingBytes;
     L.vtile = 2 * kRingBytes;
     L.plimb = L.vtile + kTile * kRowT;
-    L.hdr = L.plimb + HG * kTile * 16;
-    L.wave_stride = L.hdr + kTile * 8;
+    L.wave_stride = L.plimb + HG * kTile * 16;
     L.nw = nw;
     // the prologue's query scratch and the epilogue's merge buffers use the
     // wavefront regions
