@@ -307,12 +307,29 @@ __device__ __forceinline__ int assign_cost(const double (&x)[VPL], const double 
             const double t = s * (double)mm;
             const double u = o + t;
             const double pen = lam * c.rate[mm];
+            if constexpr (VPL <= 2) {
+                // the costs of all values before any comparison: left alone, the
+                // scheduler takes value after value (0.8 % at 64 levels)
+                double J[VPL];
 #pragma unroll
-            for (int k = 0; k < VPL; ++k) {
-                const double e = x[k] - u;
-                const double J = e * e + pen;
-                m[k] = J < best[k] ? mm : m[k];
-                best[k] = min_nn(best[k], J);
+                for (int k = 0; k < VPL; ++k) {
+                    const double e = x[k] - u;
+                    J[k] = e * e + pen;
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int k = 0; k < VPL; ++k) {
+                    m[k] = J[k] < best[k] ? mm : m[k];
+                    best[k] = min_nn(best[k], J[k]);
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < VPL; ++k) {
+                    const double e = x[k] - u;
+                    const double J = e * e + pen;
+                    m[k] = J < best[k] ? mm : m[k];
+                    best[k] = min_nn(best[k], J);
+                }
             }
         }
     }
@@ -888,14 +905,19 @@ __device__ __forceinline__ void nearest(const double (&x)[VPL], double s, double
     }
 }
 
-// Wavefronts per SIMD that the registers are held to: for the folded search of
-// streams of up to 128 values six (two thresholds: 4 x 8192 tokens, K and V, 787
-// us, 808 with five and 837 with eight) or five (four thresholds spill with six:
-// 328 and 314 us for 2 x 4096 tokens), four for per-token streams (their LDS, 36
-// KB, fits four workgroups), three where every step tries every level of those or
-// holds 16 levels.
+// Wavefronts per SIMD that the registers are held to.  The folded search: six for
+// streams of up to 128 values with two thresholds (4 x 8192 tokens, K and V, 787
+// us, 808 with five and 837 with eight), five with more (four thresholds spill with
+// six: 328 and 314 us for 2 x 4096 tokens), four for longer streams (per token
+// their LDS fits four workgroups).  Where every step tries every level: as many as
+// the distortions leave room for in registers (three with those of 16 levels or of
+// 256-value streams), else six or five, which a few registers more would cost:
+// unbounded, 2 x 16384 tokens of 8 heads, head_dim 256, 2 levels take 1454 us, not
+// 1146, 1 x 8192, 64 levels 6.13 ms, not 5.98.
 __host__ __device__ constexpr int enc_waves(int vpl, int mb, bool tok, int jm) {
-    return tok && jm >= 0 ? 4 : tok || mb == 16 ? 3 : jm >= 0 ? (vpl > 2 ? 4 : jm == 2 ? 6 : 5) : 1;
+    if (jm >= 0) return tok || vpl > 2 ? 4 : jm == 2 ? 6 : 5;
+    if (mb == 0) return vpl <= 2 ? 6 : vpl == 4 && !tok ? 5 : 3;
+    return mb == 16 || tok || vpl == 4 ? 3 : 1;
 }
 
 // What bounds it: vector instructions (twelve steps of the search, then the coder's

@@ -214,8 +214,8 @@ def test_wait_state_checker_catches_planted_mistakes():
 
 
 @pytest.fixture(scope="module")
-def device_code(tmp_path_factory):
-    """{source: [(function, lines)]} of the device code."""
+def assembly(tmp_path_factory):
+    """{source: device assembly}."""
     import __graft_entry__ as ge
 
     if not os.path.exists(ge.HIPCC) and shutil.which("hipcc") is None:
@@ -230,8 +230,14 @@ def device_code(tmp_path_factory):
     for src, (p, out) in procs.items():
         log = p.communicate()[0]
         assert p.returncode == 0, log.decode(errors="replace")[-2000:]
-        code[src] = list(_functions(open(out).read()))
+        code[src] = open(out).read()
     return code
+
+
+@pytest.fixture(scope="module")
+def device_code(assembly):
+    """{source: [(function, lines)]} of the device code."""
+    return {src: list(_functions(text)) for src, text in assembly.items()}
 
 
 @pytest.mark.timeout(600)
@@ -258,3 +264,28 @@ def test_inline_assembly_keeps_wait_states(device_code):
         for name, body in functions:
             problems = check_wait_states(body)
             assert problems == [], (src, name, problems[:5])
+
+
+def _wavefronts(text):
+    """{kernel: wavefronts per SIMD that its registers allow}."""
+    found = re.findall(r"\.amdhsa_kernel (\S+).*?\.amdhsa_next_free_vgpr (\d+)", text, re.S)
+    return {name: 512 // ((int(n) + 7) // 8 * 8) for name, n in found}
+
+
+# encode_kernel<values per lane, distortions kept, per token, -1>: the search that
+# tries every level, and the wavefronts per SIMD that its registers
+# are held to
+GENERAL_SEARCH = {(2, 0, 0): 6, (4, 0, 0): 5, (4, 8, 0): 3, (2, 8, 0): 4, (2, 16, 0): 3, (1, 8, 0): 5,
+                  (2, 0, 1): 6, (16, 0, 1): 3, (8, 0, 1): 4}
+
+
+@pytest.mark.timeout(600)
+def test_general_search_keeps_its_wavefronts(assembly):
+    """Few registers more than a bound cost a wavefront per SIMD where no timed
+    call looks (2 levels at head_dim 256: 3 to 2, a tenth of the time)."""
+    got = _wavefronts(assembly["dq_encode.hip"])
+    for (vpl, mb, tok), want in GENERAL_SEARCH.items():
+        key = f"encode_kernelILi{vpl}ELi{mb}ELb{tok}ELin1ELb0ELb0E"
+        names = [n for n in got if key in n]
+        assert len(names) == 1, key
+        assert got[names[0]] >= want, (key, got[names[0]])
