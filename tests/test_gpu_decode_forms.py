@@ -1,8 +1,10 @@
 """Decode attention in every form of its kernels (keys and values in one
 wavefront or in two, up to 4 and up to 8 query heads per KV head, one table or
 two, compiled and general record lengths, fixed-width records, per-token streams
-at p = 8 and 12, contiguous and paged), at a sequence's end: record rows past
-the length may hold anything."""
+at p = 8 and 12, contiguous and paged): against 64 bits, closely enough that
+every digit of the fixed-point operands counts, with scales of both signs and
+zero; and at a sequence's end, where record rows past the length may hold
+anything."""
 
 from dataclasses import dataclass
 
@@ -12,6 +14,7 @@ import torch
 
 import dq_workloads as wlmod
 import paper_2609_19880_amd as dq
+from oracle import attention, fixed, hadamard, kmean, kv, tables
 
 DEV = "cuda:0"
 B, LENS = 2, (1373, 130)         # last tiles of 29 and 2 live tokens
@@ -119,6 +122,28 @@ class Cache:
             for h in range(f.H):
                 yield 0, r[b, h, :2048]
 
+    def levels(self, i, b):
+        """Levels [H, T, 128], scales and offsets [H, T] of sequence b."""
+        f, T = self.f, LENS[b]
+        parts = sorted(((t, j, rows.cpu().numpy()) for j, (t, rows) in enumerate(self.rows(i, b)) if t < T),
+                       key=lambda e: e[:2])
+        n, per_head = (128 * f.H, 1) if f.token else (128, f.H)
+        rec = np.concatenate([r.reshape(1, r.shape[0], -1) for _, _, r in parts])
+        rec = rec.reshape(-1, per_head, *rec.shape[1:]).transpose(1, 0, 2, 3)
+        rec = np.ascontiguousarray(rec.reshape(per_head, -1, rec.shape[-1])[:, :T, :self.C[i]])
+        if f.ck is None:
+            return fixed.unpack(rec, 128, 2)
+        M, C, p = (f.ck, f.cv)[i]
+        sym, s, o, ok = kv.decode_records(rec, tables.build_tables(n, M, p, 1.4, C), n)
+        assert ok.all()
+        return tuple(x[0] for x in kv.tokenwise_as_heads(sym, s, o, f.H)) if f.token else (sym, s, o)
+
+    def means(self, b):
+        """Dequantized key means [H, windows, 128]."""
+        rows = self.bt[b].long() if self.f.page else [b]
+        mq, ms = (x[rows].transpose(0, 1).flatten(1, 2).contiguous().cpu().numpy() for x in (self.mq, self.ms))
+        return kmean.dequantize_mean(mq, ms.view(np.float16))[:, :(LENS[b] + 127) // 128]
+
     def fill_past_end(self, i, header, body):
         """Rows from the length on: the first four bytes (fp16 scale and
         offset) as given, the rest `body`."""
@@ -171,3 +196,68 @@ def test_rows_past_the_length_are_ignored(form):
             c.fill_past_end(i, s + o, body)
         got = c.step()
         assert np.array_equal(got, want), (s, o, np.abs(got - want).max())
+
+
+# Query and weights are 22-bit fixed point, sums and softmax fp32: 1e-6 to 3e-6
+# from 64 bits (relative 2-norm over a sequence's heads).  Without the lowest of
+# the three digits of either operand it would be 6e-5 and more.
+LIMIT = 1.2e-5
+
+
+def _without_digit(v, digit):
+    """Integers v less their digit-th signed 8-bit digit."""
+    if digit is None:
+        return v
+    w = (v.astype(np.int64) + 0x808080) ^ 0x808080
+    return v - ((((w >> (8 * digit)) & 255) ^ 128) - 128) * 256.0 ** digit
+
+
+def fixed_point(q, keys, mu, values, scale, query=None, weight=None):
+    """One query head in the kernels' arithmetic: the rotated query in units of
+    its largest value / 2^22, the weights (value scales folded in) in those of
+    their 64-token tile's; the rest in 64 bits.  query, weight: the digit that
+    is left out."""
+    (ks, s, o), (vs, sv, ov) = keys, values
+    qr, T = hadamard.fwht(q), len(s)
+    unit = np.abs(qr).max() / 2 ** 22
+    dot = ks @ (_without_digit(np.rint(qr / unit), query) * unit)
+    logit = (s * dot + o * qr.sum() + np.repeat(mu @ qr, 128)[:T]) * scale / 128
+    p = np.exp(logit - logit.max())
+    acc = np.full(128, (p * ov).sum())
+    for t in range(0, T, 64):
+        w = p[t:t + 64] * sv[t:t + 64]
+        unit = w.max() / 2 ** 22
+        acc += (_without_digit(np.rint(w / unit), weight) * unit) @ vs[t:t + 64]
+    return hadamard.fwht(acc) / 128 / p.sum()
+
+
+def _error(got, want):
+    return np.linalg.norm(got - want) / np.linalg.norm(want)
+
+
+@pytest.mark.gpu
+@by_form
+@pytest.mark.parametrize("sign", [1, -1, 0])
+def test_step_against_64_bits(form, sign):
+    """Keys with non-zero means, lengths that end inside a tile; and, for the
+    limit's worth, the same arithmetic less one digit does not meet it."""
+    c = Cache(form, 62)
+    assert bool((c.ms != 0).any())
+    scale = sign / np.sqrt(128)
+    got, q, G = c.step(float(scale)), c.q.cpu().double().numpy(), form.G
+    for b, T in enumerate(LENS):
+        keys, values = ([x.astype(np.float64) for x in c.levels(i, b)] for i in (0, 1))    # (levels, scales, offsets)
+        mu = c.means(b)
+        want = attention.attention_folded(q[b:b + 1], *(x[None] for x in keys), mu[None], *(x[None] for x in values),
+                                          [T], G, scale)[0]
+        assert _error(got[b], want) < LIMIT, b
+
+        def model(**less):
+            return np.stack([fixed_point(q[b, g], [x[g // G] for x in keys], mu[g // G], [x[g // G] for x in values],
+                                         scale, **less) for g in range(form.H * G)])
+
+        assert _error(model(), want) < LIMIT / 2
+        # (at a scale of 0 the query has no part, and equal weights err alike)
+        for digit in range(3 if sign else 0):
+            assert _error(model(query=digit), want) > 3 * LIMIT
+            assert _error(model(weight=digit), want) > 3 * LIMIT
