@@ -1,9 +1,10 @@
 """The encoder's threshold search against the oracle where it can go wrong:
 every way rates decide its form (two to four thresholds in registers, any
 number, the outermost pair sharing their mean, rates it does not take), stream
-lengths, grids of 4 to 64 streams per workgroup with ragged ends, record sizes
-that are no multiple of 4, and streams it must hand back to the plain search
-(values on a tie, a few distinct values, a large offset)."""
+lengths, record sizes that are no multiple of 4, and streams it must hand back
+to the plain search (values on a tie, a few distinct values, a large offset).
+These are small appends, of 4 streams per workgroup; those of 8 to 64 (32 per
+token), with partly filled last workgroups, are compared with them."""
 
 import numpy as np
 import pytest
@@ -82,12 +83,60 @@ def test_search_matches_oracle_per_token(H, levels, C, p):
     assert np.array_equal(got, want)
 
 
-@pytest.mark.parametrize("B,T,H", [(1, 128, 1), (1, 128, 8), (5, 384, 8), (16, 1024, 8)])
-def test_records_do_not_depend_on_the_grid(B, T, H):
-    """4, 8, 16, 32 or 64 streams per workgroup by the size of the append: the
-    same bytes as the same tokens appended one window at a time."""
+def _streams_per_group(most, tokens, rows):
+    """The grid's rule: as many streams per workgroup as leave four workgroups per CU."""
+    ns, cus = most, torch.cuda.get_device_properties(0).multi_processor_count
+    while ns > 4 and -(-tokens // ns) * rows < 4 * cus:
+        ns //= 2
+    return ns
+
+
+def _batch(seed, B, T, H):
+    """[B, T, H, 128]: eight sequences, then the same with their channels rotated."""
+    x = _streams(seed, min(B, 8), T, H, 128).to(DEV)
+    return torch.stack([torch.roll(x[b % 8], b // 8, dims=-1) for b in range(B)])
+
+
+# (sequences, streams per workgroup): 203 tokens leave 11 or 3 for the last one
+@pytest.mark.parametrize("levels,C,alpha", [(6, 36, 1.4), (9, 47, 1.4), (32, 48, 7.6)])
+@pytest.mark.parametrize("B,ns", [(5, 8), (10, 16), (20, 32), (32, 64)])
+def test_records_do_not_depend_on_the_grid_per_head(B, ns, levels, C, alpha):
+    """A batch in one append against its sequences one at a time."""
+    T, H = 203, 8
+    assert _streams_per_group(64, T, H * B) == ns and _streams_per_group(64, T, H) == 4
+    tab = dq.Tables(128, levels, 12, C, alpha)
+    x = _batch(B, B, T, H)
+    whole, parts = (torch.zeros((B, H, 256, C), dtype=torch.uint8, device=DEV) for _ in range(2))
+    dq.dq_encode_kv(tab, x, 0, 256, whole)
+    for b in range(B):
+        dq.dq_encode_kv(tab, x[b:b + 1], 0, 256, parts[b:b + 1])
+    assert torch.equal(whole, parts)
+    assert not whole[:, :, T:].any()
+
+
+@pytest.mark.parametrize("levels,C,p", [(8, 335, 8), (17, 460, 12)])
+@pytest.mark.parametrize("B,ns", [(40, 8), (79, 16), (147, 32)])
+def test_records_do_not_depend_on_the_grid_per_token(B, ns, levels, C, p):
+    """Symbols packed (8 levels) and not (17)."""
+    T, H = 203, 8
+    assert _streams_per_group(32, T, B) == ns and _streams_per_group(32, T, 1) == 4
+    tab = dq.Tables(128 * H, levels, p, C, 1.4)
+    x = _batch(B, B, T, H)
+    whole, parts = (torch.zeros(dq.token_records_shape(tab, B, 256), dtype=torch.uint8, device=DEV) for _ in range(2))
+    dq.dq_encode_kv_token(tab, x, 0, 256, whole)
+    for b in range(B):
+        dq.dq_encode_kv_token(tab, x[b:b + 1], 0, 256, parts[b:b + 1])
+    assert torch.equal(whole, parts)
+
+
+@pytest.mark.parametrize("B,T,whole_ns,part_ns", [(5, 384, 8, 4), (10, 384, 16, 8), (20, 384, 32, 16), (16, 1024, 64, 16)])
+def test_caches_do_not_depend_on_the_grid(B, T, whole_ns, part_ns):
+    """Keys with means and values: the same bytes as the same tokens appended
+    one window at a time."""
+    H = 8
+    assert (_streams_per_group(64, T, H * B), _streams_per_group(64, 128, H * B)) == (whole_ns, part_ns)
     tab = dq.Tables(128, 6, 12, 36, 1.4)
-    x = _streams(B + T, B, T, H, 128).to(DEV)
+    x = _batch(B + T, B, T, H)
     whole = dq.KVCache(B, H, H, T, tab, tab, device=DEV)
     parts = dq.KVCache(B, H, H, T, tab, tab, device=DEV)
     whole.append(x, x, 0)
