@@ -28,18 +28,21 @@ constexpr float kDigitMax = 4194304.0f;
 
 // Rotates one query head held as channels l and l + 64 in lane l
 // (unnormalized Hadamard, stages h = 1, 2, ..., 64 in the order of the
-// definition) and stores it into qt[g][128] fp32, with qscale[g] = max |q_rot| /
-// kDigitMax and qsum[g] = sum of q_rot.  rotate = 0: keys arrive in the rotated
+// definition), multiplies it by scale (the softmax's, for exponents of 2, so that
+// the scores come out as such) and stores it into qt[g][128] fp32, with qscale[g] =
+// max |q_rot| / kDigitMax and qsum[g] = sum of q_rot.  rotate = 0: keys arrive in the rotated
 // basis, and so does the query: it is taken as it is.  v0, v1 end as the
 // rotated channels; returns qscale[g].
 __device__ __forceinline__ float rotate_query_head(float& v0, float& v1, int g, int lane, float* qt, float* qscale,
-                                                   float* qsum, int rotate) {
+                                                   float* qsum, int rotate, float scale) {
     if (rotate) {
         hadamard_lanes(v0, v1, lane);
         const float r0 = v0 + v1, r1 = v0 - v1;
         v0 = r0;
         v1 = r1;
     }
+    v0 *= scale;
+    v1 *= scale;
     qt[g * 128 + lane] = v0;
     qt[g * 128 + lane + 64] = v1;
     const float mx = wave_max_f32(fmaxf(fabsf(v0), fabsf(v1)));
@@ -56,7 +59,7 @@ __device__ __forceinline__ float rotate_query_head(float& v0, float& v1, int g, 
 // q, and qscale = qsum = 0 for the slots nh .. slots - 1.
 __device__ __forceinline__ void rotate_query_heads(const uint16_t* q, int nh, int slots, int wave, int nw,
                                                    int lane, float* qt, float* qscale, float* qsum,
-                                                   int rotate = 1) {
+                                                   int rotate, float scale) {
     for (int g = wave; g < slots; g += nw) {
         if (g >= nh) {
             if (lane == 0) {
@@ -66,7 +69,7 @@ __device__ __forceinline__ void rotate_query_heads(const uint16_t* q, int nh, in
             continue;
         }
         float v0 = bf16_to_f32(q[g * 128 + lane]), v1 = bf16_to_f32(q[g * 128 + lane + 64]);
-        rotate_query_head(v0, v1, g, lane, qt, qscale, qsum, rotate);
+        rotate_query_head(v0, v1, g, lane, qt, qscale, qsum, rotate, scale);
     }
 }
 
@@ -194,10 +197,12 @@ constexpr float kLowest = -3.4028234663852886e38f;
 // folded into the weights (Eq. fold-value).
 //   d: digit sums; h[tg]: scale and offset of the token's key and value, in fp32
 //   or as the records' first words; qs, qsum, qm: the slot's digit unit, query sum and
-//   q . mu; scale: softmax_scale log2(e) > 0 (its sign is in the query's terms);
+//   q . mu, all with the softmax's scale in them, so that a score is an exponent of 2
+//   (a scale that enters with the subtraction of the rounded maximum, as one fused
+//   multiply-add, leaves the maximum itself an exponent of half a unit in the last
+//   place: more than the range for scores beyond 2^30);
 //   left: tokens from l % 16 to the sequence's end (token 16 tg is live while
-//   16 tg < left); m: running maximum, scaled.  The scale enters in the
-//   exponent's one fused multiply-add, so the unscaled score is rounded once.
+//   16 tg < left); m: running maximum.
 // Returns the correction of what was summed before; psum, osum: the lane's
 // parts of sum p and sum p o_v; w: the weights' digits (fixed point relative to
 // the tile's largest), wscale their unit.
@@ -216,7 +221,7 @@ __device__ __forceinline__ float value_offset(const uint2& h) { return half_hi(h
 
 template <typename H>
 __device__ __forceinline__ SlotWeights slot_softmax(const v4i (&d)[4], const H (&h)[4], float qs, float qsum,
-                                                    float qm, float scale, int left, bool whole, float& m) {
+                                                    float qm, int left, bool whole, float& m) {
     float s[4];
 #pragma unroll
     for (int tg = 0; tg < 4; ++tg) {
@@ -228,7 +233,7 @@ __device__ __forceinline__ SlotWeights slot_softmax(const v4i (&d)[4], const H (
         for (int tg = 0; tg < 4; ++tg) s[tg] = 16 * tg < left ? s[tg] : -INFINITY;
     }
     SlotWeights r;
-    const float mn = fmaxf(m, scale * row_max16(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]))));
+    const float mn = fmaxf(m, row_max16(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]))));
     const float base = fmaxf(mn, kLowest);           // -inf - base stays -inf
     // v_exp_f32 directly: arguments are <= 0 and results that would be denormal
     // may flush to zero
@@ -237,7 +242,7 @@ __device__ __forceinline__ SlotWeights slot_softmax(const v4i (&d)[4], const H (
     float p[4], pw[4];
 #pragma unroll
     for (int tg = 0; tg < 4; ++tg) {
-        p[tg] = __builtin_amdgcn_exp2f(fmaf(s[tg], scale, -base));
+        p[tg] = __builtin_amdgcn_exp2f(s[tg] - base);
         pw[tg] = p[tg] * value_scale(h[tg]);           // >= 0: scales are non-negative
     }
     r.psum = (p[0] + p[1]) + (p[2] + p[3]);

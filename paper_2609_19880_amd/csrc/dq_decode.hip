@@ -17,7 +17,6 @@
 #include <math.h>
 
 #include <algorithm>
-#include <cmath>
 #include <mutex>
 
 #include "dq_attn.h"
@@ -134,8 +133,7 @@ struct AttnArgs {
     const uint16_t* kms;
     const uint8_t* vrec;
     const int32_t* seq_lens;
-    float scale_log2;            // |softmax_scale| * log2(e) / d, at least 1e-37
-    float q_sign;                // the sign of softmax_scale
+    float q_scale;               // softmax_scale * log2(e) / d (/ 1 for prerotated keys)
     int32_t* ws_hdr;             // [0] chunk, [1] chunk count NC, [2] residual slots written,
                                  // [3] 1 if the merge rotates the output back (values rotated online)
     int rot_q, rot_out;          // keys / values rotated online (tables not prerotated)
@@ -418,7 +416,7 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
         uint32_t w0 = qb0, w1 = qb1;
         asm volatile("" : "+v"(w0), "+v"(w1));
         float v0 = bf16_to_f32((uint16_t)w0), v1 = bf16_to_f32((uint16_t)w1);
-        const float qs = rotate_query_head(v0, v1, wave, lane, qt, qscale, qsum, a.rot_q);
+        const float qs = rotate_query_head(v0, v1, wave, lane, qt, qscale, qsum, a.rot_q, a.q_scale);
         head_digits(v0, v1, qs, wave);
     } else if (wave < GP) {
         if (lane == 0) qscale[wave] = qsum[wave] = 0.f;
@@ -432,7 +430,7 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
         }
         const uint16_t* qh = a.q + ((int64_t)b * a.Hq + hq0 + g) * kD;
         float v0 = bf16_to_f32(qh[lane]), v1 = bf16_to_f32(qh[lane + 64]);
-        const float qs = rotate_query_head(v0, v1, g, lane, qt, qscale, qsum, a.rot_q);
+        const float qs = rotate_query_head(v0, v1, g, lane, qt, qscale, qsum, a.rot_q, a.q_scale);
         head_digits(v0, v1, qs, g);
     }
     __syncthreads();
@@ -470,7 +468,7 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
             for (int g = 0; g < GP; ++g) sg[g] = half_sum_f32(sg[g]);
             if ((lane & 31) == 31 && wi < nwin) {
 #pragma unroll
-                for (int g = 0; g < GP; ++g) qmu[wi * GP + g] = g < G ? sg[g] * a.q_sign : 0.f;
+                for (int g = 0; g < GP; ++g) qmu[wi * GP + g] = g < G ? sg[g] : 0.f;
             }
         }
     }
@@ -543,8 +541,7 @@ __global__ __launch_bounds__(WMAX * kWave) void attn_partial_kernel(AttnArgs a) 
 #pragma unroll
         for (int hg = 0; hg < HG; ++hg) {
             const int g = 4 * hg + lq;
-            sw[hg] = slot_softmax(d[hg], hd, qscale[g] * a.q_sign, qsum[g] * a.q_sign, qm[4 * hg], a.scale_log2, left,
-                                  whole, m_run[hg]);
+            sw[hg] = slot_softmax(d[hg], hd, qscale[g], qsum[g], qm[4 * hg], left, whole, m_run[hg]);
             store_weights(wbase + L.plimb + 16 * l16 + 4 * lq + hg * (kTile * 16), sw[hg].w);
         }
     };
@@ -1566,8 +1563,7 @@ int launch_attention_partial(const dq_tables* tk, const dq_tables* tv, const Pag
     a.rot_q = tk->cfg.prerotated ? 0 : 1;
     a.rot_out = tv->cfg.prerotated ? 0 : 1;
     // the rotated query and key meet with a factor d (H H = d I)
-    a.scale_log2 = std::max(std::fabs(scale) * 1.4426950408889634f / (a.rot_q ? (float)kD : 1.0f), 1e-37f);
-    a.q_sign = scale < 0.f ? -1.f : 1.f;
+    a.q_scale = scale * 1.4426950408889634f / (a.rot_q ? (float)kD : 1.0f);
     const int64_t slots = ws_slots_used > 0 ? ws_slots_used : plan.slots_max;
     a.ws_hdr = static_cast<int32_t*>(ws);
     a.ws_acc = reinterpret_cast<float*>(static_cast<uint8_t*>(ws) + kWsHeader);
@@ -1609,8 +1605,7 @@ int launch_attention_fixed_partial(const Pages& pg, const uint16_t* q, int32_t B
     a.vrec = vrec;
     a.seq_lens = seq_lens;
     a.rot_q = a.rot_out = 1;
-    a.scale_log2 = std::max(std::fabs(scale) * 1.4426950408889634f / (float)kD, 1e-37f);
-    a.q_sign = scale < 0.f ? -1.f : 1.f;
+    a.q_scale = scale * 1.4426950408889634f / (float)kD;
     a.ws_hdr = static_cast<int32_t*>(ws);
     a.ws_acc = reinterpret_cast<float*>(static_cast<uint8_t*>(ws) + kWsHeader);
     a.ws_m = a.ws_acc + plan.slots_max * kD;

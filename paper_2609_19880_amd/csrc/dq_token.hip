@@ -37,7 +37,6 @@
 #include <math.h>
 
 #include <algorithm>
-#include <cmath>
 
 #include "dq_attn.h"
 
@@ -85,8 +84,7 @@ struct TokArgs {
     int k_stride, v_stride;       // bytes per token record (multiples of 16)
     Pages pg;                     // block table of a paged cache (bt null: contiguous)
     const int32_t* seq_lens;
-    float scale_log2;             // |softmax_scale| * log2(e) / d (/ 1 for prerotated keys), at least 1e-37
-    float q_sign;                 // the sign of softmax_scale
+    float q_scale;                // softmax_scale * log2(e) / d (/ 1 for prerotated keys)
     int rot_q, rot_out;           // keys / values rotated online (tables not prerotated)
     int32_t* ws_hdr;
     float* ws_m;
@@ -390,7 +388,7 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
     float* qsum = reinterpret_cast<float*>(smem + L.qsum);
     float* qmu = reinterpret_cast<float*>(smem + L.qmu);
     uint8_t* qtile = smem + L.qtile;
-    rotate_query_heads(a.q + (int64_t)b * Hq * kD, Hq, Hq, wave, L.nw, lane, qt, qscale, qsum, a.rot_q);
+    rotate_query_heads(a.q + (int64_t)b * Hq * kD, Hq, Hq, wave, L.nw, lane, qt, qscale, qsum, a.rot_q, a.q_scale);
     __syncthreads();
     // a wavefront per query-head slot (slots past G get zero digits)
     for (int i = wave; i < Hkv * GS; i += L.nw) {
@@ -425,7 +423,7 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
 #pragma unroll
                 for (int k = 0; k < 4; ++k) s = s + qt[g * kD + c4 + k] * f[k];
                 s = half_sum_f32(s);
-                if ((lane & 31) == 31 && it < nwin * Hkv) qmu[wi * Hq + g] = s * a.q_sign;
+                if ((lane & 31) == 31 && it < nwin * Hkv) qmu[wi * Hq + g] = s;
             }
         }
     }
@@ -484,8 +482,7 @@ __global__ __launch_bounds__((SPLIT ? kTokSplitWaves : tok_waves(HG)) * kWave) v
         for (int hg = 0; hg < HG; ++hg) {
             const int r = 4 * hg + pslot, g = r < G ? h * G + r : 0;    // slots past G take no query head
             m[hg] = row_first(m_vec[hg]);
-            sw[hg] = slot_softmax(d[hg], hd, qscale[g] * a.q_sign, qsum[g] * a.q_sign, qm[g], a.scale_log2, left, whole,
-                                  m[hg]);
+            sw[hg] = slot_softmax(d[hg], hd, qscale[g], qsum[g], qm[g], left, whole, m[hg]);
             store_weights(wt + w_off + hg * (kTile * 16), sw[hg].w);
         }
     };
@@ -979,8 +976,7 @@ int launch_attention_token_partial(const dq_tables* tk, const dq_tables* tv, con
     a.seq_lens = seq_lens;
     a.rot_q = tk->cfg.prerotated ? 0 : 1;
     a.rot_out = tv->cfg.prerotated ? 0 : 1;
-    a.scale_log2 = std::max(std::fabs(scale) * 1.4426950408889634f / (a.rot_q ? (float)kD : 1.0f), 1e-37f);
-    a.q_sign = scale < 0.f ? -1.f : 1.f;
+    a.q_scale = scale * 1.4426950408889634f / (a.rot_q ? (float)kD : 1.0f);
     const int64_t slots = ws_slots(B, Hq, t_cap);
     a.ws_hdr = static_cast<int32_t*>(ws);
     a.ws_acc = reinterpret_cast<float*>(static_cast<uint8_t*>(ws) + kWsHeader);

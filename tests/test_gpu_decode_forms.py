@@ -261,3 +261,20 @@ def test_step_against_64_bits(form, sign):
         for digit in range(3 if sign else 0):
             assert _error(model(query=digit), want) > 3 * LIMIT
             assert _error(model(weight=digit), want) > 3 * LIMIT
+
+
+@pytest.mark.gpu
+@by_form
+@pytest.mark.parametrize("size", [2e5, 1e10, 1e30])
+def test_scores_of_any_size(form, size):
+    """Queries so large that the scores' spacing exceeds an exponent's range: the
+    softmax is one token's weight, and finite."""
+    c = Cache(form, 63)
+    c.q = (c.q.float() * size).to(torch.bfloat16)
+    got, q, G = c.step(), c.q.cpu().double().numpy(), form.G
+    for b, T in enumerate(LENS):
+        keys, values = ([x.astype(np.float64) for x in c.levels(i, b)] for i in (0, 1))
+        want = attention.attention_folded(q[b:b + 1], *(x[None] for x in keys), c.means(b)[None],
+                                          *(x[None] for x in values), [T], G, 1 / np.sqrt(128))[0]
+        assert np.isfinite(got[b]).all()
+        assert _error(got[b], want) < LIMIT, b
