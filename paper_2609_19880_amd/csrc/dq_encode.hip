@@ -1054,8 +1054,8 @@ __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void enco
             fin = uniform_all(fin);
             wave_minmax_nn(mn, mx);
             if (!uniform_all(fin && mn != 0.0 && mx != 0.0)) {
-                // NaN, and which zero it is, as plain comparisons have it
-                // (rare: kept a branch)
+                // NaN, and which zero it is, as plain comparisons over lanes in
+                // channel order have it (rare: kept a branch)
                 asm volatile("" : "+v"(x[0]));
                 mn = mx = x[0];
 #pragma unroll
@@ -1063,8 +1063,13 @@ __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void enco
                     mn = fmin(mn, x[k]);
                     mx = fmax(mx, x[k]);
                 }
-                mn = wave_min(mn);
-                mx = wave_max(mx);
+                // (row_channel: the second and fourth quad of a row reversed)
+                auto quads = [](uint32_t v) {
+                    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x1B, 0xF, 0xA, false);
+                };
+                auto ordered = [&](double v) { return join(quads(lo32(v)), quads(hi32(v))); };
+                mn = wave_min(ordered(mn));
+                mx = wave_max(ordered(mx));
             }
             // the two drifts of Alg. 1: on the min-max grid, then on the
             // refitted grid in fp16 (a retry repeats only the second)

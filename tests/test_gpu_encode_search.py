@@ -144,3 +144,22 @@ def test_caches_do_not_depend_on_the_grid(B, T, whole_ns, part_ns):
         parts.append(x[:, t:t + 128], x[:, t:t + 128], t)
     for name in ("k_records", "v_records", "k_mean_q", "k_mean_scale", "status"):
         assert torch.equal(getattr(whole, name), getattr(parts, name)), name
+
+
+@pytest.mark.parametrize("d,H,levels,C", [(64, 1, 6, 22), (128, 2, 2, 26), (128, 2, 6, 36), (256, 1, 9, 90)])
+def test_zeros_of_both_signs(d, H, levels, C):
+    """Streams of zeros that come rotated already: scale 0, and as the offset a
+    zero whose sign is the smallest's where the reduction over the wavefront
+    ends, channels 4, 68, ...: the bytes do not change with the layout of the
+    channels over the lanes."""
+    T = 96
+    alpha = dq.smallest_feasible_alpha(d, levels, 12, C)
+    tab = dq.Tables(d, levels, 12, C, alpha, True)
+    neg = torch.from_numpy(np.random.default_rng(d + levels).random((1, T, H, d)) < 0.3)
+    x = torch.where(neg, -0.0, 0.0).to(torch.bfloat16)
+    rec = torch.zeros((1, H, 128, C), dtype=torch.uint8, device=DEV)
+    dq.dq_encode_kv(tab, x.to(DEV), 0, 128, rec)
+    head = rec[0, :, :T, :4].cpu()
+    want = neg[0, :, :, 4::64].any(dim=-1).T
+    assert bool(want.any()) and not bool(want.all())
+    assert not head[:, :, :3].any() and torch.equal(head[:, :, 3], want.to(torch.uint8) * 0x80)
