@@ -1,25 +1,27 @@
 // Append path: bf16 K/V tokens -> fixed-size D-Quant records (Fig. 1, Alg. 1).
 //
 // Two kernels:
-//  * key_mean: one wavefront per (batch, head, 128-token window).  Rotates
-//    each token (Hadamard, Sec. 4.2), sums the window left to right in fp64,
-//    and stores the channel mean as INT8 with one fp16 scale (Sec. 4.2,
-//    App. B).
-//  * encode: one workgroup per (batch, head, 64 consecutive tokens; 32 for
-//    per-token streams).  Each wavefront takes a stream at a time with its n
-//    values spread over the lanes and keeps them in registers through Alg. 1
-//    (FitMinMax -> Drift -> Refit -> fp16 -> Drift); no n x M distortion
-//    matrix goes to memory (the distortions of up to 8 or 16 levels stay in
-//    registers for the assignments of a drift, more levels are recomputed on
-//    the fly) and the code length is reduced across the wavefront, as
-//    Sec. 4.5 describes for the encoder.  The symbols of the workgroup's
-//    streams then go through LDS to lane-per-stream backward rANS (divisions
-//    by f as exact multiply-high reciprocals), and the records are written as
-//    one contiguous span.
+//  * key_mean: eight wavefronts per (batch, head, 128-token window).  They
+//    rotate the tokens (Hadamard, Sec. 4.2), whose channels are then summed in
+//    token order in fp64, and the channel mean is stored as INT8 with one fp16
+//    scale (Sec. 4.2, App. B).
+//  * encode: one workgroup per (batch, head, 4 to 64 consecutive tokens; at most
+//    32 for per-token streams, see streams_per_group).  Each wavefront takes a
+//    stream at a time with its n values spread over the lanes and keeps them in
+//    registers through Alg. 1 (FitMinMax -> Drift -> Refit -> fp16 -> Drift); no
+//    n x M distortion matrix goes to memory.  A drift counts values beyond level
+//    thresholds where the rates allow it (fold_drift); elsewhere it tries every
+//    level (drift; the distortions of up to 8 or 16 levels stay in registers,
+//    those of more are formed again at every step), and the code length is
+//    reduced across the wavefront, as Sec. 4.5 describes for the encoder.  The
+//    symbols of the workgroup's streams then go through LDS to lane-per-stream
+//    backward rANS (divisions by f as exact multiply-high reciprocals), and the
+//    records are written as one contiguous span.
 //
-// Every floating-point step is fp64 in a fixed order without contraction
-// (this file is built with -ffp-contract=off), so the records are
-// bit-identical to the reference definition of the format.
+// What decides the bytes is fp64 in a fixed order without contraction (this file
+// is built with -ffp-contract=off), so the records are bit-identical to the
+// reference definition of the format.  The threshold search of long streams runs in
+// fp32, but only finds the point that fp64 bounds then certify.
 #include <float.h>
 #include <limits.h>
 
@@ -31,11 +33,11 @@ namespace dq {
 namespace {
 
 constexpr int kEncStreams = 64;   // streams per workgroup
-// Per-token streams (n = 1024) stage 32: their symbols and records then take
-// about 48 KB of LDS, so that three workgroups share a CU (64 streams would
-// leave one wavefront per SIMD).
+// Per-token streams (n = 1024) stage 32: their symbols and records then take about
+// 27 KB of a workgroup's 36 KB of LDS up to 16 levels (packed_symbols), so that four
+// workgroups share a CU, and 48 of 56 KB above (64 streams would leave one
+// wavefront per SIMD).
 constexpr int kEncStreamsTok = 32;
-__host__ __device__ constexpr int enc_streams(bool tok) { return tok ? kEncStreamsTok : kEncStreams; }
 constexpr int kEncWaves = 4;
 constexpr int kEncThreads = kEncWaves * kWave;
 constexpr int kD = 128;           // head_dim of the heads in a per-token stream
@@ -920,8 +922,10 @@ __host__ __device__ constexpr int enc_waves(int vpl, int mb, bool tok, int jm) {
     return mb == 16 || tok || vpl == 4 ? 3 : 1;
 }
 
-// What bounds it: vector instructions (twelve steps of the search, then the coder's
-// 128 serial steps per lane); memory, register spills included, moves 0.35 TB/s.
+// What bounds it: instruction issue (eleven steps of the search per drift, then the
+// coder's 128 serial steps per lane): vector instructions are 79 % of the time at 4
+// cycles each, scalar ones 71 % at one a cycle.  Memory, register spills included
+// (1.0 GB of writes beyond the 0.15 GB of records), moves 0.47 TB/s.
 // Keys and values together, 4 x 8192 tokens of 8 heads, 36-byte records (6 levels): 2398 us when every step of the
 // search assigned every level anew in 64 bits, 792 with the folded drift;
 // 48- and 32-byte records, 2 x 4096: 981 and 320; per token, 4 x 8192: 2936 and
@@ -1289,7 +1293,7 @@ __global__ __launch_bounds__(kEncThreads, enc_waves(VPL, MB, TOK, JM)) void enco
 }
 
 // Streams per workgroup: as many as the coder has lanes for (64, or 32 for
-// per-token streams, whose symbols and records then take 28 KB of LDS), fewer
+// per-token streams: kEncStreamsTok), fewer
 // while the grid would leave a CU with fewer than four workgroups: a small append
 // is bound by the streams that a wavefront takes in turn.  K and V, us, stopping
 // at one / two / four workgroups per CU: 16 x 128 tokens 164 / 121 / 108, 1 x
