@@ -925,7 +925,8 @@ __host__ __device__ constexpr int enc_waves(int vpl, int mb, bool tok, int jm) {
 // What bounds it: instruction issue (eleven steps of the search per drift, then the
 // coder's 128 serial steps per lane): vector instructions are 79 % of the time at 4
 // cycles each, scalar ones 71 % at one a cycle.  Memory, register spills included
-// (1.0 GB of writes beyond the 0.15 GB of records), moves 0.47 TB/s.
+// (about 1 GB of writes beyond the 0.15 GB of records at 16 x 32768 tokens), moves
+// 0.5 TB/s.
 // Keys and values together, 4 x 8192 tokens of 8 heads, 36-byte records (6 levels): 2398 us when every step of the
 // search assigned every level anew in 64 bits, 792 with the folded drift;
 // 48- and 32-byte records, 2 x 4096: 981 and 320; per token, 4 x 8192: 2936 and
